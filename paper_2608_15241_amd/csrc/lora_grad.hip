@@ -7,19 +7,14 @@
 //   dx_t = dy_t W + g_t A_a.
 //
 // Design (HBM-bound for the adapter gradients: 4 T r (K + N) flop, shrinks
-// included, against T (K + N) bf16 read), four launches:
+// included, against T (K + N) bf16 read), three launches:
 //  * set-up: the tokens bucketed by adapter (a stable counting sort in one
 //    workgroup, as in SGMV) while the other workgroups transpose B per
 //    adapter to [r_max][N];
-//  * u = x A^T and dy B from the long-chunk shrink of the forward path, as
-//    float32 partial sums over K slices (two launches);
-//  * dB and dA as segmented outer products, both in one launch: a workgroup
-//    per (64 tokens of one adapter, 256 threads x PT columns of dy or x)
-//    forms the tokens' coefficients in LDS (slices summed in order, times
-//    s_t, 0 past the rank), then each thread keeps PT x r_max float32 sums
-//    over the tokens, each token's row read once, coalesced;
-//  * the partial sums of the 64-token units added in unit order by a reduce
-//    pass: deterministic, no atomics.
+//  * u = x A^T and dy B for every projection in one launch (lora_shrink.hip);
+//  * dB and dA as segmented outer products in one launch, each workgroup over
+//    all of one adapter's tokens: sums of 64 tokens added in token order,
+//    deterministic, no partial sums in memory, no atomics.
 //  dx runs the forward fused projection on the transposed weights: with
 //  x := dy, W := W^T, A := B^T and B := A^T, its shrink is dy B and its
 //  delta s (dy B) A, so dx needs no kernel of its own.
@@ -54,9 +49,8 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
 }
 
 // ---- tokens bucketed by adapter, stable: perm[seg[a] .. seg[a+1]) holds the
-// tokens of adapter a in ascending order; tokens without one are left out.
-// useg[a] = sum over b < a of ceil(T_b / 64): the first 64-token unit of a;
-// utab[k] = (adapter, first position in perm, token count) of unit k.
+// tokens of adapter a in ascending order, pscale their scales; tokens without
+// one are left out.
 // One workgroup of kPrepThreads: wave w owns a contiguous chunk of the
 // tokens. It counts its chunk per adapter (ballots over equal adapters),
 // then one prefix over (adapter, wave) gives every wave its own running
@@ -65,8 +59,8 @@ constexpr int kPrepThreads = 1024;
 constexpr int kPrepWaves = kPrepThreads / kWave;
 
 __device__ void bucket_tokens(const int32_t* __restrict__ idx, int64_t T, int n_ad,
-                              int32_t* __restrict__ perm, int32_t* __restrict__ seg,
-                              int32_t* __restrict__ useg, i32x4* __restrict__ utab) {
+                              const float* __restrict__ scale, int32_t* __restrict__ perm,
+                              float* __restrict__ pscale, int32_t* __restrict__ seg) {
   __shared__ int cnt[kPrepWaves][kGrMaxAdapters];  // per wave: count, then running offset
   __shared__ int tot[kGrMaxAdapters];
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
@@ -98,27 +92,19 @@ __device__ void bucket_tokens(const int32_t* __restrict__ idx, int64_t T, int n_
   }
   __syncthreads();
   if (wave == 0) {
-    int run = 0, urun = 0;
+    int run = 0;
     for (int a0 = 0; a0 < n_ad; a0 += kWave) {
       const int a = a0 + lane;
       const int c = a < n_ad ? tot[a] : 0;
-      const int u = (c + kGrUnit - 1) / kGrUnit;
-      const int ic = wave_incl_scan(c), iu = wave_incl_scan(u);
+      const int ic = wave_incl_scan(c);
       if (a < n_ad) {
-        const int s0 = run + ic - c, u0 = urun + iu - u;
+        const int s0 = run + ic - c;
         seg[a] = s0;
-        useg[a] = u0;
         tot[a] = s0;
-        for (int k = 0; k < u; ++k)
-          utab[u0 + k] = i32x4{a, s0 + kGrUnit * k, min(kGrUnit, c - kGrUnit * k), 0};
       }
       run += __shfl(ic, kWave - 1);
-      urun += __shfl(iu, kWave - 1);
     }
-    if (lane == 0) {
-      seg[n_ad] = run;
-      useg[n_ad] = urun;
-    }
+    if (lane == 0) seg[n_ad] = run;
   }
   __syncthreads();
   for (int a = tid; a < n_ad; a += kPrepThreads) {
@@ -133,12 +119,17 @@ __device__ void bucket_tokens(const int32_t* __restrict__ idx, int64_t T, int n_
   // 3. the wave places its chunk in order
   for (int64_t t0 = c0; t0 < c1; t0 += kWave) {
     const int my = adapter_at(t0 + lane);
+    const float sc = my >= 0 ? scale[t0 + lane] : 0.f;
     uint64_t pending = __ballot(my >= 0);
     while (pending) {
       const int ad = __builtin_amdgcn_readlane(my, __ffsll(static_cast<long long>(pending)) - 1);
       const uint64_t m = __ballot(my == ad);
       const int base = cnt[wave][ad];
-      if (my == ad) perm[base + __popcll(m & ((1ull << lane) - 1ull))] = static_cast<int32_t>(t0 + lane);
+      if (my == ad) {
+        const int at = base + __popcll(m & ((1ull << lane) - 1ull));
+        perm[at] = static_cast<int32_t>(t0 + lane);
+        pscale[at] = sc;
+      }
       if (lane == 0) cnt[wave][ad] = base + __popcll(m);
       pending &= ~m;
     }
@@ -214,10 +205,11 @@ struct PrepArgs {
   TransposeJob job[kGrGroup];
   int n_jobs;
   const int32_t* idx;
+  const float* scale;
   int64_t T;
   int n_ad;
-  int32_t *perm, *seg, *useg;
-  i32x4* utab;
+  int32_t *perm, *seg;
+  float* pscale;
 };
 
 __global__ __launch_bounds__(kPrepThreads) void grad_prep_kernel(PrepArgs a) {
@@ -225,7 +217,7 @@ __global__ __launch_bounds__(kPrepThreads) void grad_prep_kernel(PrepArgs a) {
   int wg = blockIdx.x;
   if (a.idx) {
     if (wg == 0) {
-      bucket_tokens(a.idx, a.T, a.n_ad, a.perm, a.seg, a.useg, a.utab);
+      bucket_tokens(a.idx, a.T, a.n_ad, a.scale, a.perm, a.pscale, a.seg);
       return;
     }
     --wg;
@@ -249,295 +241,320 @@ local_status_t run_prep(hipStream_t s, const PrepArgs& a) {
   return local_check_launch("lora_grad (prep)");
 }
 
-// Coefficients of a unit's tokens into LDS: cl[i][j] = s_i * (sum over the
-// shrink's K slices, in slice order) for j below the rank, 0 elsewhere and
-// for i >= nt. Each thread forms 4 consecutive j of one token at a time with
-// 16-byte loads, 8 slices in flight (the sum stays in slice order).
-template <int RJ>
-__device__ __forceinline__ void stage_coefficients(float (*cl)[RJ], const int* tok,
-                                                   const float* tsc, const float* S, int ks,
-                                                   int64_t T, int r_max, int nt, int rk) {
-  for (int e = threadIdx.x; e < kGrUnit * RJ / 4; e += kGrThreads) {
-    const int i = e / (RJ / 4), j = 4 * (e % (RJ / 4));
-    f32x4 sum{0.f, 0.f, 0.f, 0.f};
-    if (i < nt && j < rk) {
-      const float* src = S + static_cast<int64_t>(tok[i]) * r_max + j;
-      for (int z0 = 0; z0 < ks; z0 += 8) {
-        f32x4 v[8];
-#pragma unroll
-        for (int z = 0; z < 8; ++z)
-          v[z] = z0 + z < ks
-                     ? *reinterpret_cast<const f32x4*>(src + static_cast<int64_t>(z0 + z) * T * r_max)
-                     : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int z = 0; z < 8; ++z) sum += v[z];
-      }
-      sum *= tsc[i];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (j + q >= rk) sum[q] = 0.f;
-    }
-    *reinterpret_cast<f32x4*>(&cl[i][j]) = sum;
-  }
-}
-
-// ---- segmented outer products, every gradient of the call in one launch.
+// ---- segmented outer products, every gradient of the call in one launch:
 // blockIdx.y = job: 2g = dB of projection g (V = dy_g, P = N_g, coefficients
-// s u_g, partials [P][r_max]), 2g + 1 = dA of projection g (V = x, P = K,
-// coefficients g_g = s dy_g B_g, partials [r_max][P]).
-// Workgroup = (unit, column tile of 256 PT columns). The unit's 64 token
-// rows are loaded at once, ahead of everything else, so that a workgroup
-// waits for memory about three times (unit table, token ids, rows and
-// coefficients together). The coefficients are formed in LDS from the
-// shrink's K-slice partial sums (u = x A^T, or dy B): summed over the slices
-// in order, times s_t, 0 at or past the adapter's rank. Each thread then
-// keeps PT x RJ float32 sums of c_t[j] V_t[p] over the unit's tokens.
+// s u_g, out [n_ad][P][r_max]), 2g + 1 = dA of projection g (V = x, P = K,
+// coefficients g_g = s dy_g B_g, out [n_ad][r_max][P]).
+//
+// Bound by the reads of V. D[j][p] += c^T V on v_mfma_f32_16x16x32_bf16 over 32
+// tokens: a lane loads 4 consecutive columns of its 8 tokens, and byte
+// permutes turn the 8 rows into the operands of 4 columns. V is bf16; a
+// float32 coefficient is cut by truncation into three bf16 parts that add up
+// to it exactly, one product each: 6 MFMAs of 16 cycles per column tile and 64
+// tokens, where v_mfma_f32_16x16x4_f32 takes 16 of 32 cycles (2048 tokens, q,
+// k and v at 4096 x 4096 and rank 16: 24.0 us against 34.7). Every product is
+// exact in float32 either way and the sums are float32; against float64 the
+// gradients are 1.6e-7 off (2.1e-7 with the float32 instruction).
+//
+// A workgroup owns one adapter's tokens for CT column tiles, UW waves a tile
+// (CT UW = 4): the waves of a tile take every UW-th unit of 64 tokens, and
+// after each round their tiles are added through LDS in unit order to sums
+// that stay in registers until the adapter's last unit, so no partial sum
+// goes through memory (with a workgroup per unit, the partial sums of 2048
+// tokens at 4096 x 4096 x 3 were 56 MB written and read back: 43 us and a
+// 10.8 us reduce launch). Units are added in order whatever UW is.
 struct OuterArgs {
   const uint16_t* V[kGrJobs];
-  const float* S[kGrJobs];  // shrink partial sums [ks][T][r_max]
-  int ks[kGrJobs];
-  float* part[kGrJobs];
-  int64_t P[kGrJobs];
-  const int32_t* ranks[kGrJobs];  // the projection's ranks, or NULL
-};
-
-template <int PT, int RJ>
-__global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(
-    OuterArgs args, int64_t T, int64_t ptiles, int r_max, const int32_t* __restrict__ perm,
-    const int32_t* __restrict__ useg, const i32x4* __restrict__ utab, int n_ad,
-    const float* __restrict__ scale) {
-  using RowT = typename std::conditional<PT == 2, uint32_t, uint16_t>::type;
-  __shared__ __attribute__((aligned(16))) float cl[kGrUnit][RJ];
-  __shared__ int tok[kGrUnit];
-  __shared__ float tsc[kGrUnit];
-  const int job = blockIdx.y;
-  const int64_t P = args.P[job];
-  const int slot = static_cast<int>(blockIdx.x / ptiles);
-  const int64_t p0 = ((blockIdx.x % ptiles) * kGrThreads + threadIdx.x) * PT;
-  if ((blockIdx.x % ptiles) * kGrThreads * PT >= P) return;  // the whole tile is past P
-  if (slot >= useg[n_ad]) return;                             // past the last unit
-  const i32x4 ut = utab[slot];
-  const int a = ut.x, first = ut.y, nt = ut.z;
-  const uint16_t* V = args.V[job];
-  const float* S = args.S[job];
-  const int ks = args.ks[job];
-  const int tid = threadIdx.x;
-  if (tid < nt) {
-    const int t = perm[first + tid];
-    tok[tid] = t;
-    tsc[tid] = scale[t];
-  }
-  const int32_t* ranks = args.ranks[job];
-  const int rk = ranks ? min(max(ranks[a], 0), r_max) : r_max;
-  __syncthreads();
-  // every row of the unit in flight at once (rows past nt read as zero)
-  const bool live = p0 < P;
-  RowT raw[kGrUnit];
-#pragma unroll
-  for (int i = 0; i < kGrUnit; ++i)
-    raw[i] = (live && i < nt)
-                 ? ld_global<RowT>(V + static_cast<int64_t>(tok[i]) * P + p0)
-                 : RowT(0);
-  stage_coefficients<RJ>(cl, tok, tsc, S, ks, T, r_max, nt, rk);
-  __syncthreads();
-  float acc[PT][RJ];
-#pragma unroll
-  for (int q = 0; q < PT; ++q)
-#pragma unroll
-    for (int j = 0; j < RJ; ++j) acc[q][j] = 0.f;
-#pragma unroll
-  for (int i = 0; i < kGrUnit; ++i) {
-    float v[PT];
-    if constexpr (PT == 2) {
-      v[0] = __uint_as_float(static_cast<uint32_t>(raw[i]) << 16);
-      v[1] = __uint_as_float(static_cast<uint32_t>(raw[i]) & 0xffff0000u);
-    } else {
-      v[0] = __uint_as_float(static_cast<uint32_t>(raw[i]) << 16);
-    }
-#pragma unroll
-    for (int j4 = 0; j4 < RJ; j4 += 4) {
-      const f32x4 cj = *reinterpret_cast<const f32x4*>(&cl[i][j4]);
-#pragma unroll
-      for (int q = 0; q < PT; ++q) {
-        acc[q][j4] += cj[0] * v[q];
-        acc[q][j4 + 1] += cj[1] * v[q];
-        acc[q][j4 + 2] += cj[2] * v[q];
-        acc[q][j4 + 3] += cj[3] * v[q];
-      }
-    }
-  }
-  if (!live) return;
-  float* out = args.part[job] + static_cast<int64_t>(slot) * P * r_max;
-  if (job & 1) {
-#pragma unroll
-    for (int q = 0; q < PT; ++q)
-#pragma unroll
-      for (int j = 0; j < RJ; ++j)
-        if (j < r_max) out[static_cast<int64_t>(j) * P + p0 + q] = acc[q][j];
-  } else {
-#pragma unroll
-    for (int q = 0; q < PT; ++q)
-#pragma unroll
-      for (int j = 0; j < RJ; j += 4)
-        if (j < r_max)
-          *reinterpret_cast<f32x4*>(out + (p0 + q) * r_max + j) =
-              f32x4{acc[q][j], acc[q][j + 1], acc[q][j + 2], acc[q][j + 3]};
-  }
-}
-
-// ---- the same products on the matrix cores (r_max <= 64), float32 MFMA
-// v_mfma_f32_16x16x4_f32: D[16 x 16] += A[16 x 4] B[4 x 16], lane l giving
-// A[l%16][l/16] and B[l/16][l%16] and holding D[4(l/16) + i][l%16]. With
-// the contraction over 4 tokens, A = the coefficients c[t][j] (j = row) and
-// B = the token rows V[t][col] (col = column): both are read along their
-// rows, so the token-major inputs need no transpose. A wave owns 128
-// columns: lane l loads 8 consecutive columns 8(l%16) .. +7 of token l/16
-// (16 bytes, 256 contiguous bytes per token), and MFMA e (e < 8) takes
-// element e, i.e. columns 8n + e for D column n. JT tiles of 16 cover
-// r_max. The unit's rows are all in flight before the first product.
-template <int JT>
-__global__ __launch_bounds__(kGrThreads) void grad_outer_mfma_kernel(
-    OuterArgs args, int64_t T, int64_t ptiles, int r_max, const int32_t* __restrict__ perm,
-    const int32_t* __restrict__ useg, const i32x4* __restrict__ utab, int n_ad,
-    const float* __restrict__ scale) {
-  constexpr int RJ = 16 * JT;
-  constexpr int kSteps = kGrUnit / 4;
-  __shared__ __attribute__((aligned(16))) float cl[kGrUnit][RJ];
-  __shared__ int tok[kGrUnit];
-  __shared__ float tsc[kGrUnit];
-  const int job = blockIdx.y;
-  const int64_t P = args.P[job];
-  const int slot = static_cast<int>(blockIdx.x / ptiles);
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  const int64_t wcol = ((blockIdx.x % ptiles) * (kGrThreads / kWave) + wave) * 128;
-  if ((blockIdx.x % ptiles) * 512 >= P) return;  // the whole tile is past P
-  if (slot >= useg[n_ad]) return;                // past the last unit
-  const i32x4 ut = utab[slot];
-  const int a = ut.x, first = ut.y, nt = ut.z;
-  const uint16_t* V = args.V[job];
-  const float* S = args.S[job];
-  const int ks = args.ks[job];
-  if (tid < nt) {
-    const int t = perm[first + tid];
-    tok[tid] = t;
-    tsc[tid] = scale[t];
-  }
-  const int32_t* ranks = args.ranks[job];
-  const int rk = ranks ? min(max(ranks[a], 0), r_max) : r_max;
-  __syncthreads();
-  const int n = lane % 16, k = lane / 16;
-  const int64_t col = wcol + 8 * n;  // this lane's 8 columns
-  const bool live = col < P;
-  u32x4 raw[kSteps];
-#pragma unroll
-  for (int st = 0; st < kSteps; ++st) {
-    const int i = 4 * st + k;
-    raw[st] = (live && i < nt) ? ld_global<u32x4>(V + static_cast<int64_t>(tok[i]) * P + col)
-                               : u32x4{0u, 0u, 0u, 0u};
-  }
-  stage_coefficients<RJ>(cl, tok, tsc, S, ks, T, r_max, nt, rk);
-  __syncthreads();
-  f32x4 acc[JT][8];
-#pragma unroll
-  for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[jt][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int st = 0; st < kSteps; ++st) {
-    float v[8];
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      v[2 * h] = __uint_as_float(raw[st][h] << 16);
-      v[2 * h + 1] = __uint_as_float(raw[st][h] & 0xffff0000u);
-    }
-#pragma unroll
-    for (int jt = 0; jt < JT; ++jt) {
-      const float c = cl[4 * st + k][16 * jt + n];
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        acc[jt][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(c, v[e], acc[jt][e], 0, 0, 0);
-    }
-  }
-  if (!live) return;
-  float* out = args.part[job] + static_cast<int64_t>(slot) * P * r_max;
-#pragma unroll
-  for (int jt = 0; jt < JT; ++jt) {
-    const int j0 = 16 * jt + 4 * k;  // this lane's rows j0 .. j0 + 3
-    if (j0 >= r_max) continue;
-    if (job & 1) {  // [r_max][P]: 8 consecutive columns per row
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float* o = out + static_cast<int64_t>(j0 + i) * P + col;
-        *reinterpret_cast<f32x4*>(o) =
-            f32x4{acc[jt][0][i], acc[jt][1][i], acc[jt][2][i], acc[jt][3][i]};
-        *reinterpret_cast<f32x4*>(o + 4) =
-            f32x4{acc[jt][4][i], acc[jt][5][i], acc[jt][6][i], acc[jt][7][i]};
-      }
-    } else {  // [P][r_max]: 4 consecutive rows per column
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        *reinterpret_cast<f32x4*>(out + (col + e) * r_max + j0) = acc[jt][e];
-    }
-  }
-}
-
-// ---- out[a][e .. e+4) = sum of the partial sums of a's units, in unit
-// order, for e < E = P * r_max; 0 for an adapter without tokens and at or
-// past its rank. blockIdx.z = job as for the outer products.
-struct ReduceArgs {
-  const float* part[kGrJobs];
+  const float* S[kGrJobs];  // low-rank products [T][r_max], unscaled
   float* out[kGrJobs];
   int64_t P[kGrJobs];
-  const int32_t* ranks[kGrJobs];
+  const int32_t* ranks[kGrJobs];  // the projection's ranks, or NULL
+  const int32_t *perm, *seg;
+  const float* pscale;  // scales in the order of perm
+  int64_t tiles;  // column-tile groups of the widest job
+  int r_max;
 };
 
-__global__ __launch_bounds__(kGrThreads) void grad_reduce_kernel(
-    ReduceArgs args, int r_max, const int32_t* __restrict__ useg) {
-  const int job = blockIdx.z;
-  const int a = blockIdx.y;
+constexpr int kGrWaves = kGrThreads / kWave;
+constexpr int kGrCols = 4;  // columns per lane (E below)
+
+template <int JT, int UW>
+__global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) {
+  constexpr int E = kGrCols;
+  static_assert(JT * E % UW == 0, "sums per thread");
+  constexpr int CT = kGrWaves / UW;
+  constexpr int RJ = 16 * JT, CW = 16 * E;  // rank rows and columns of a tile
+  constexpr int kLaneTok = kGrUnit / 4;  // tokens of a unit in a lane's group
+  constexpr int kSums = JT * E / UW;        // f32x4 of sums per thread
+  // a wave's tile in LDS: [RJ][CW + 4] for dA, [CW][RJ + 4] for dB
+  constexpr int TILE_A = RJ * (CW + 4), TILE_B = CW * (RJ + 4);
+  constexpr int TILE = TILE_A > TILE_B ? TILE_A : TILE_B;
+  __shared__ __attribute__((aligned(16))) float tl[kGrWaves][TILE];
+  __shared__ __attribute__((aligned(16))) int tok[kGrWaves][2][kGrUnit];
+  __shared__ __attribute__((aligned(16))) float tsc[kGrWaves][2][kGrUnit];
+  using RowT = u32x2;
+
+  const int job = blockIdx.y, jbase = 64 * blockIdx.z;  // ranks above 64: 64 rows at a time
   const int64_t P = args.P[job];
-  const int64_t E = P * r_max;
-  const int64_t e = (static_cast<int64_t>(blockIdx.x) * kGrThreads + threadIdx.x) * 4;
-  if (e >= E) return;
-  const int u0 = useg[a], nu = useg[a + 1] - u0;
+  const int r_max = args.r_max;
+  const int a = static_cast<int>(blockIdx.x / args.tiles);
+  const int64_t tg = blockIdx.x % args.tiles;
+  if (tg * CT * CW >= P) return;  // uniform: the whole group is past P
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int ct = wave / UW, uw = wave % UW;
+  const int n = lane % 16, k = lane / 16;
+  const int64_t wcol = (tg * CT + ct) * CW;  // the tile's first column
+  const int64_t col = wcol + E * n;          // this lane's columns
+  const bool live = col < P;
   const int32_t* ranks = args.ranks[job];
   const int rk = ranks ? min(max(ranks[a], 0), r_max) : r_max;
-  const float* part = args.part[job];
-  f32x4 sum{0.f, 0.f, 0.f, 0.f};
-  int u = 0;
-  for (; u + 4 <= nu; u += 4) {  // four loads in flight, added in unit order
-    f32x4 v[4];
+  const int s0 = args.seg[a], count = args.seg[a + 1] - s0;
+  const int units = (count + kGrUnit - 1) / kGrUnit;
+  const uint16_t* V = args.V[job];
+  const float* S = args.S[job];
+
+  f32x4 sum[kSums];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      v[q] = *reinterpret_cast<const f32x4*>(part + static_cast<int64_t>(u0 + u + q) * E + e);
+  for (int q = 0; q < kSums; ++q) sum[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // thread item q of the tile: 4 consecutive floats of the output order
+  const int it0 = uw * kWave + lane;
+  auto lds_at = [&](int w, int q) {
+    const int e = 4 * (it0 + q * UW * kWave);
+    if (job & 1) return &tl[w][(e / CW) * (CW + 4) + e % CW];
+    return &tl[w][(e / RJ) * (RJ + 4) + e % RJ];
+  };
+
+  // Token ids and scales of the wave's unit of round r, in slot r % 2. Past
+  // the unit's tokens the last one repeats (masked below).
+  auto unit_tokens = [&](int u0, int* tk, float* ts) {
+    const int left = count - kGrUnit * (u0 + uw);
+    if (left <= 0) return;
+    const int at = s0 + kGrUnit * (u0 + uw) + min(lane, left - 1);
+    *tk = args.perm[at];
+    *ts = args.pscale[at];
+  };
+  auto put_tokens = [&](int slot, int tk, float ts) {
+    tok[wave][slot][lane] = tk;
+    tsc[wave][slot][lane] = ts;
+  };
+  const uint16_t* Vc = V + (live ? col : P - E);  // columns past P: never stored
+  int jc[JT];
+  bool jok[JT];  // at or past the rank: A's padding rows may hold anything
 #pragma unroll
-    for (int q = 0; q < 4; ++q) sum += v[q];
+  for (int jt = 0; jt < JT; ++jt) {
+    jc[jt] = min(jbase + 16 * jt + n, r_max - 1);
+    jok[jt] = jbase + 16 * jt + n < rk;
   }
-  for (; u < nu; ++u)
-    sum += *reinterpret_cast<const f32x4*>(part + static_cast<int64_t>(u0 + u) * E + e);
+  // the lane's tokens of a unit: 32 h + 8 k + i (h < 2, i < 8) at 8 h + i
+  RowT raw[kLaneTok];
+  float c[JT][kLaneTok];
+  auto load_half = [&](int slot, int h) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int j = (job & 1) ? static_cast<int>((e + q) / P) : static_cast<int>((e + q) % r_max);
-    if (j >= rk) sum[q] = 0.f;
+    for (int i4 = 0; i4 < 8; i4 += 4) {
+      const i32x4 tv = *reinterpret_cast<const i32x4*>(&tok[wave][slot][32 * h + 8 * k + i4]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t t = tv[q];
+        raw[8 * h + i4 + q] = ld_global<RowT>(Vc + t * P);
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt) c[jt][8 * h + i4 + q] = S[t * r_max + jc[jt]];
+      }
+    }
+  };
+  int tk = 0;
+  float ts = 0.f;
+  if (uw < units) {
+    unit_tokens(0, &tk, &ts);
+    put_tokens(0, tk, ts);
+    unit_tokens(UW, &tk, &ts);
+    load_half(0, 0);
+    load_half(0, 1);
   }
-  *reinterpret_cast<f32x4*>(args.out[job] + static_cast<int64_t>(a) * E + e) = sum;
+  for (int u0 = 0; u0 < units; u0 += UW) {
+    const int unit = u0 + uw;
+    if (unit < units) {
+      const int nt = min(kGrUnit, count - kGrUnit * unit);
+      const int slot = (u0 / UW) & 1;
+      f32x4 acc[JT][E];
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[jt][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const bool more = unit + UW < units;  // uniform
+      if (more) {
+        put_tokens(slot ^ 1, tk, ts);
+        unit_tokens(u0 + 2 * UW, &tk, &ts);
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        // operands of the half's 32 tokens: element i of column e from the
+        // i-th row; the coefficients' three bf16 parts
+        if (nt < kGrUnit) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const bool in = 32 * h + 8 * k + i < nt;
+            raw[8 * h + i] = in ? raw[8 * h + i] : u32x2{0u, 0u};
+#pragma unroll
+            for (int jt = 0; jt < JT; ++jt) c[jt][8 * h + i] = in ? c[jt][8 * h + i] : 0.f;
+          }
+        }
+        u32x4 vf[E];
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+          for (int e = 0; e < E; ++e)
+            vf[e][d] = __builtin_amdgcn_perm(raw[8 * h + 2 * d + 1][e / 2], raw[8 * h + 2 * d][e / 2],
+                                             e & 1 ? 0x07060302u : 0x05040100u);
+        float sv[8];
+#pragma unroll
+        for (int i = 0; i < 8; i += 4) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(&tsc[wave][slot][32 * h + 8 * k + i]);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) sv[i + q] = v[q];
+        }
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt) {
+          u32x4 cf[3];
+#pragma unroll
+          for (int d = 0; d < 4; ++d) {
+            uint32_t part[2][3];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+              const float cs = jok[jt] ? c[jt][8 * h + 2 * d + q] * sv[2 * d + q] : 0.f;
+              part[q][0] = __float_as_uint(cs);
+              const float r1 = cs - __uint_as_float(part[q][0] & 0xffff0000u);
+              part[q][1] = __float_as_uint(r1);
+              part[q][2] =
+                  __float_as_uint(r1 - __uint_as_float(part[q][1] & 0xffff0000u));
+            }
+#pragma unroll
+            for (int m = 0; m < 3; ++m)
+              cf[m][d] = __builtin_amdgcn_perm(part[1][m], part[0][m], 0x07060302u);
+          }
+#pragma unroll
+          for (int m = 2; m >= 0; --m)
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+              acc[jt][e] = mfma16x16x32(as_bf16x8(cf[m]), as_bf16x8(vf[e]), acc[jt][e]);
+        }
+        if (more) load_half(slot ^ 1, h);
+      }
+      bool bad = false;
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) bad |= acc[jt][e][i] != acc[jt][e][i];
+      if (__any(bad)) {
+        // a value of the unit is not finite: the parts of a coefficient then
+        // mix infinities with zeros, so the unit runs again as float32
+        // products (16x16x4: lane l gives token l / 16)
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+          for (int e = 0; e < E; ++e) acc[jt][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int i = k; i < kGrUnit; i += 4) {
+          const bool in = i < nt;
+          const int64_t t = tok[wave][slot][i];
+          const RowT r = ld_global<RowT>(Vc + t * P);
+#pragma unroll
+          for (int jt = 0; jt < JT; ++jt) {
+            const float cs = in && jok[jt] ? S[t * r_max + jc[jt]] * tsc[wave][slot][i] : 0.f;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+              const uint32_t w = in ? r[e / 2] : 0u;
+              const float v = __uint_as_float(e & 1 ? w & 0xffff0000u : w << 16);
+              acc[jt][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(cs, v, acc[jt][e], 0, 0, 0);
+            }
+          }
+        }
+      }
+      float* w = tl[wave];
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) {
+        const int j0 = 16 * jt + 4 * k;  // this lane's rows j0 .. j0 + 3
+        if (job & 1) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < E; e += 4)
+              *reinterpret_cast<f32x4*>(w + (j0 + i) * (CW + 4) + E * n + e) =
+                  f32x4{acc[jt][e][i], acc[jt][e + 1][i], acc[jt][e + 2][i], acc[jt][e + 3][i]};
+        } else {
+#pragma unroll
+          for (int e = 0; e < E; ++e)
+            *reinterpret_cast<f32x4*>(w + (E * n + e) * (RJ + 4) + j0) = acc[jt][e];
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < UW; ++v)
+      if (u0 + v < units) {
+#pragma unroll
+        for (int q = 0; q < kSums; ++q)
+          sum[q] += *reinterpret_cast<const f32x4*>(lds_at(ct * UW + v, q));
+      }
+    if (u0 + UW < units) __syncthreads();  // the tiles are rewritten by the next round
+  }
+
+  // out: zero at or past the rank (and for an adapter without tokens)
+  float* out = args.out[job] + static_cast<int64_t>(a) * P * r_max;
+#pragma unroll
+  for (int q = 0; q < kSums; ++q) {
+    const int e = 4 * (it0 + q * UW * kWave);
+    if (job & 1) {
+      const int j = jbase + e / CW;
+      const int64_t p = wcol + e % CW;
+      if (j < r_max && p < P)
+        *reinterpret_cast<f32x4*>(out + static_cast<int64_t>(j) * P + p) =
+            j < rk ? sum[q] : f32x4{0.f, 0.f, 0.f, 0.f};
+    } else {
+      const int j = jbase + e % RJ;
+      const int64_t p = wcol + e / RJ;
+      if (j < r_max && p < P) {
+        f32x4 v = sum[q];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (j + i >= rk) v[i] = 0.f;
+        *reinterpret_cast<f32x4*>(out + p * r_max + j) = v;
+      }
+    }
+  }
 }
 
-local_status_t launch_outer(const OuterArgs& o, int n_jobs, int64_t T, int r_max,
-                            const int32_t* perm, const int32_t* useg, const i32x4* utab,
-                            int n_ad, int64_t units, const float* scale, hipStream_t s) {
+template <int JT, int UW>
+local_status_t launch_outer_uw(OuterArgs o, int n_jobs, int n_ad, hipStream_t s) {
   int64_t pmax = 0;
   for (int q = 0; q < n_jobs; ++q) pmax = std::max(pmax, o.P[q]);
-  auto go = [&](auto kernel, int64_t cols_per_wg) {
-    const int64_t ptiles = (pmax + cols_per_wg - 1) / cols_per_wg;
-    kernel<<<dim3(static_cast<unsigned>(units * ptiles), static_cast<unsigned>(n_jobs)),
-             kGrThreads, 0, s>>>(o, T, ptiles, r_max, perm, useg, utab, n_ad, scale);
-    return local_check_launch("lora_grad (outer)");
-  };
-  if (r_max <= 16) return go(grad_outer_mfma_kernel<1>, 512);
-  if (r_max <= 32) return go(grad_outer_mfma_kernel<2>, 512);
-  if (r_max <= 64) return go(grad_outer_mfma_kernel<4>, 512);
-  return go(grad_outer_kernel<1, 128>, kGrThreads);
+  constexpr int64_t cols = 16 * kGrCols * (kGrWaves / UW);
+  o.tiles = (pmax + cols - 1) / cols;
+  const unsigned jz = static_cast<unsigned>((o.r_max + 63) / 64);
+  grad_outer_kernel<JT, UW>
+      <<<dim3(static_cast<unsigned>(n_ad * o.tiles), static_cast<unsigned>(n_jobs), jz), kGrThreads,
+         0, s>>>(o);
+  return local_check_launch("lora_grad (outer)");
+}
+
+// Waves per column tile: enough for the mean number of 64-token units of an
+// adapter (a wave without a unit idles; a unit without a wave waits a round).
+template <int JT>
+local_status_t launch_outer_jt(const OuterArgs& o, int n_jobs, int64_t T, int n_ad,
+                               hipStream_t s) {
+  const int64_t units = (T + kGrUnit - 1) / kGrUnit;
+  if (units > n_ad) return launch_outer_uw<JT, 4>(o, n_jobs, n_ad, s);
+  if (2 * units > n_ad) return launch_outer_uw<JT, 2>(o, n_jobs, n_ad, s);
+  return launch_outer_uw<JT, 1>(o, n_jobs, n_ad, s);
+}
+
+local_status_t launch_outer(const OuterArgs& o, int n_jobs, int64_t T, int n_ad,
+                            hipStream_t s) {
+  if (o.r_max <= 16) return launch_outer_jt<1>(o, n_jobs, T, n_ad, s);
+  if (o.r_max <= 32) return launch_outer_jt<2>(o, n_jobs, T, n_ad, s);
+  return launch_outer_jt<4>(o, n_jobs, T, n_ad, s);
 }
 
 local_status_t grad_checks(const char* who, int64_t T, int64_t K, int64_t N, int32_t n_ad,
@@ -575,12 +592,8 @@ local_status_t grad_impl(const char* who, const uint16_t* x, int64_t T, int64_t 
   for (int g = 0; g < G; ++g)
     if ((st = grad_checks(who, T, K, N[g], n_adapters, r_max)) != LOCAL_OK) return st;
   const int64_t Tw = T > 0 ? T : 1;
-  const int64_t units = Tw / kGrUnit + n_adapters;  // >= sum over adapters of ceil(T_a / 64)
-  int ks_x = 0, ks_dy[kGrGroup] = {};
-  const size_t sh_x = token_shrink_bytes(Tw, K, r_max, G, &ks_x);
-  // workspace: token order, adapter offsets, unit offsets, unit table, B_g^T,
-  // the shrinks' partial sums (x against every A_g, dy_g against B_g^T), the
-  // partial products of every job
+  // workspace: token order, adapter offsets, B_g^T, the low-rank products u_g
+  // and dy_g B_g
   size_t o = 0;
   auto take = [&](size_t bytes) {
     const size_t at = o;
@@ -588,16 +601,13 @@ local_status_t grad_impl(const char* who, const uint16_t* x, int64_t T, int64_t 
     return at;
   };
   const size_t o_perm = take(static_cast<size_t>(Tw) * 4);
+  const size_t o_psc = take(static_cast<size_t>(Tw) * 4);
   const size_t o_seg = take(static_cast<size_t>(n_adapters + 1) * 4);
-  const size_t o_useg = take(static_cast<size_t>(n_adapters + 1) * 4);
-  const size_t o_utab = take(static_cast<size_t>(units) * 16);
-  size_t o_bt[kGrGroup], o_shy[kGrGroup], o_pb[kGrGroup], o_pa[kGrGroup];
-  for (int g = 0; g < G; ++g) o_bt[g] = take(static_cast<size_t>(n_adapters) * r_max * N[g] * 2);
-  const size_t o_shx = take(sh_x);
-  for (int g = 0; g < G; ++g) o_shy[g] = take(token_shrink_bytes(Tw, N[g], r_max, 1, &ks_dy[g]));
+  size_t o_bt[kGrGroup], o_u[kGrGroup], o_g[kGrGroup];
   for (int g = 0; g < G; ++g) {
-    o_pb[g] = take(static_cast<size_t>(units) * N[g] * r_max * 4);
-    o_pa[g] = take(static_cast<size_t>(units) * K * r_max * 4);
+    o_bt[g] = take(static_cast<size_t>(n_adapters) * r_max * N[g] * 2);
+    o_u[g] = take(static_cast<size_t>(Tw) * r_max * 4);
+    o_g[g] = take(static_cast<size_t>(Tw) * r_max * 4);
   }
   if (!ws) {
     *ws_bytes = o;
@@ -615,12 +625,10 @@ local_status_t grad_impl(const char* who, const uint16_t* x, int64_t T, int64_t 
   char* w = static_cast<char*>(ws);
   int32_t* perm = reinterpret_cast<int32_t*>(w + o_perm);
   int32_t* seg = reinterpret_cast<int32_t*>(w + o_seg);
-  int32_t* useg = reinterpret_cast<int32_t*>(w + o_useg);
-  i32x4* utab = reinterpret_cast<i32x4*>(w + o_utab);
   const uint16_t* Bt[kGrGroup];
   // tokens bucketed by adapter and every B_g transposed per adapter to
-  // [r_max][N_g], in one launch. T = 0: every adapter is empty and the
-  // reduce pass writes zero gradients (no memset: the call stays capturable)
+  // [r_max][N_g], in one launch. T = 0: every adapter is empty and the outer
+  // products write zero gradients (no memset: the call stays capturable)
   PrepArgs pr{};
   pr.n_jobs = T > 0 ? G : 0;
   for (int g = 0; g < G; ++g) {
@@ -631,62 +639,40 @@ local_status_t grad_impl(const char* who, const uint16_t* x, int64_t T, int64_t 
   pr.idx = adapter_idx ? adapter_idx : reinterpret_cast<const int32_t*>(w);  // not read if T = 0
   pr.T = T;
   pr.n_ad = n_adapters;
+  pr.scale = scale;
   pr.perm = perm;
+  pr.pscale = reinterpret_cast<float*>(w + o_psc);
   pr.seg = seg;
-  pr.useg = useg;
-  pr.utab = utab;
   if ((st = run_prep(s, pr)) != LOCAL_OK) return st;
-  if (T > 0) {
-    // u_g = x A_g^T for every g in one pass over x, then dy_g B_g for each g,
-    // as the shrink's K-slice partial sums
-    if ((st = token_shrink(x, T, K, G, A, n_adapters, r_max, adapter_idx, w + o_shx, s)) !=
-        LOCAL_OK)
-      return st;
-    for (int g = 0; g < G; ++g)
-      if ((st = token_shrink(dy[g], T, N[g], 1, &Bt[g], n_adapters, r_max, adapter_idx,
-                             w + o_shy[g], s)) != LOCAL_OK)
-        return st;
-    // dB_g partials from (dy_g, s u_g), dA_g partials from (x, s dy_g B_g)
-    OuterArgs oa{};
+  if (T > 0) {  // u_g = x A_g^T and dy_g B_g, one launch
+    ShrinkJob jobs[kGrJobs];
     for (int g = 0; g < G; ++g) {
-      const int32_t* rg = ranks ? ranks[g] : nullptr;
-      oa.V[2 * g] = dy[g];
-      oa.S[2 * g] = reinterpret_cast<const float*>(w + o_shx) +
-                    static_cast<int64_t>(g) * ks_x * T * r_max;
-      oa.ks[2 * g] = ks_x;
-      oa.part[2 * g] = reinterpret_cast<float*>(w + o_pb[g]);
-      oa.P[2 * g] = N[g];
-      oa.ranks[2 * g] = rg;
-      oa.V[2 * g + 1] = x;
-      oa.S[2 * g + 1] = reinterpret_cast<const float*>(w + o_shy[g]);
-      oa.ks[2 * g + 1] = ks_dy[g];
-      oa.part[2 * g + 1] = reinterpret_cast<float*>(w + o_pa[g]);
-      oa.P[2 * g + 1] = K;
-      oa.ranks[2 * g + 1] = rg;
+      jobs[g] = ShrinkJob{x, A[g], reinterpret_cast<float*>(w + o_u[g]), K};
+      jobs[G + g] = ShrinkJob{dy[g], Bt[g], reinterpret_cast<float*>(w + o_g[g]), N[g]};
     }
-    if ((st = launch_outer(oa, 2 * G, T, r_max, perm, useg, utab, n_adapters, units, scale, s)) !=
-        LOCAL_OK)
+    if ((st = token_shrink(jobs, 2 * G, T, n_adapters, r_max, adapter_idx, s)) != LOCAL_OK)
       return st;
   }
-  // dB_g [n_ad][N_g][r_max], dA_g [n_ad][r_max][K]
-  ReduceArgs ra{};
-  int64_t emax = 0;
+  // dB_g from (dy_g, s u_g), dA_g from (x, s dy_g B_g)
+  OuterArgs oa{};
   for (int g = 0; g < G; ++g) {
     const int32_t* rg = ranks ? ranks[g] : nullptr;
-    ra.part[2 * g] = reinterpret_cast<const float*>(w + o_pb[g]);
-    ra.out[2 * g] = dB[g];
-    ra.P[2 * g] = N[g];
-    ra.ranks[2 * g] = rg;
-    ra.part[2 * g + 1] = reinterpret_cast<const float*>(w + o_pa[g]);
-    ra.out[2 * g + 1] = dA[g];
-    ra.P[2 * g + 1] = K;
-    ra.ranks[2 * g + 1] = rg;
-    emax = std::max(emax, std::max(N[g], K) * r_max);
+    oa.V[2 * g] = dy[g];
+    oa.S[2 * g] = reinterpret_cast<const float*>(w + o_u[g]);
+    oa.out[2 * g] = dB[g];
+    oa.P[2 * g] = N[g];
+    oa.ranks[2 * g] = rg;
+    oa.V[2 * g + 1] = x;
+    oa.S[2 * g + 1] = reinterpret_cast<const float*>(w + o_g[g]);
+    oa.out[2 * g + 1] = dA[g];
+    oa.P[2 * g + 1] = K;
+    oa.ranks[2 * g + 1] = rg;
   }
-  grad_reduce_kernel<<<dim3(static_cast<unsigned>((emax / 4 + kGrThreads - 1) / kGrThreads),
-                            static_cast<unsigned>(n_adapters), static_cast<unsigned>(2 * G)),
-                       kGrThreads, 0, s>>>(ra, r_max, useg);
-  return local_check_launch("lora_grad (reduce)");
+  oa.perm = perm;
+  oa.seg = seg;
+  oa.pscale = pr.pscale;
+  oa.r_max = r_max;
+  return launch_outer(oa, 2 * G, T, n_adapters, s);
 }
 
 }  // namespace

@@ -7,14 +7,20 @@
 
 namespace localk {
 
-// The long-chunk shrink on its own, for G (1..4) projections of one x:
-// P[g][z][t][j] = the sum over K slice z of x[t][k] A[g][a_t][j][k] for token
-// t's own adapter a_t (tokens without one are not written), j < r_max,
-// z < *slices. token_shrink_bytes is the workspace it needs (the partial
-// sums first, then a bitmap area); K is a multiple of 64 and T >= 1.
-size_t token_shrink_bytes(int64_t T, int64_t K, int r_max, int G, int* slices);
-local_status_t token_shrink(const uint16_t* x, int64_t T, int64_t K, int G,
-                            const uint16_t* const* A, int n_ad, int r_max, const int32_t* idx,
-                            void* ws, hipStream_t s);
+// One low-rank product of token_shrink: u[t][j] = x[t] . A[a_t][j] (float32,
+// not scaled) for j < r_max and every token t with an adapter a_t; rows of
+// tokens without one are not written. x [T][K], A [n_ad][r_max][K] (rows past
+// an adapter's rank give values that the caller drops), K a multiple of 64.
+struct ShrinkJob {
+  const uint16_t* x;
+  const uint16_t* A;
+  float* u;  // [T][r_max]
+  int64_t K;
+};
+constexpr int kShrinkJobs = 8;
+
+// Up to kShrinkJobs of them in one launch; T >= 1.
+local_status_t token_shrink(const ShrinkJob* jobs, int n_jobs, int64_t T, int n_ad, int r_max,
+                            const int32_t* idx, hipStream_t s);
 
 }  // namespace localk
