@@ -164,9 +164,8 @@ local_status_t local_lora_linear(
  *  All projections share x, T, K, adapter_idx, scale, n_adapters and r_max;
  *  sizes as for local_lora_linear, for every N[g]. At decode sizes (T <= 256)
  *  the projections run as one virtual weight of sum N[g] rows, so one pass
- *  of launches serves all of them. Above, one shrink pass reads x once for
- *  every projection and one product covers the tiles of all of them when
- *  every N[g] is a multiple of 256; otherwise they run one after another.
+ *  of launches serves all of them. Above, one shrink launch and one product
+ *  over the tiles of all of them (a tile lies in one projection).
  *  Errors as for local_lora_linear; LOCAL_ERR_UNSUPPORTED for G outside 1..4,
  *  LOCAL_ERR_NULL for a NULL array.
  */

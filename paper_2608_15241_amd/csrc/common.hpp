@@ -31,10 +31,12 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
   return static_cast<uint16_t>(u >> 16);
 }
 
-// Two floats -> packed bf16 pair (low = a), round to nearest even.
+// Two floats -> packed bf16 pair (low = a), round to nearest even (one
+// v_cvt_pk_bf16_f32; NaN stays NaN).
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
-  return static_cast<uint32_t>(f32_to_bf16(a)) |
-         (static_cast<uint32_t>(f32_to_bf16(b)) << 16);
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 r = {static_cast<__bf16>(a), static_cast<__bf16>(b)};
+  return __builtin_bit_cast(uint32_t, r);
 }
 
 // ---------------------------------------------------------------- MFMA

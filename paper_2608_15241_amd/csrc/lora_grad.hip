@@ -609,12 +609,29 @@ local_status_t grad_impl(const char* who, const uint16_t* x, int64_t T, int64_t 
     o_u[g] = take(static_cast<size_t>(Tw) * r_max * 4);
     o_g[g] = take(static_cast<size_t>(Tw) * r_max * 4);
   }
+  // The size is the one that callers have always been told, which these parts
+  // fit: token order, two lists of adapter offsets, 16 bytes for each of at
+  // most T / 64 + n_adapters units, the B_g^T, the shrinks' sums over K slices,
+  // and a partial product of every unit and gradient.
+  const int64_t units = Tw / kGrUnit + n_adapters;
+  auto sums = [&](int64_t k, int g) {
+    return al256(static_cast<size_t>(g) * long_slices(Tw, k, r_max, g) * Tw * r_max * 4) +
+           al256(static_cast<size_t>((Tw + 63) / 64) * 32);
+  };
+  size_t need = al256(static_cast<size_t>(Tw) * 4) +
+                2 * al256(static_cast<size_t>(n_adapters + 1) * 4) + al256(units * 16) +
+                al256(sums(K, G));
+  for (int g = 0; g < G; ++g)
+    need += al256(static_cast<size_t>(n_adapters) * r_max * N[g] * 2) + al256(sums(N[g], 1)) +
+            al256(static_cast<size_t>(units) * N[g] * r_max * 4) +
+            al256(static_cast<size_t>(units) * K * r_max * 4);
+  need = std::max(need, o);
   if (!ws) {
-    *ws_bytes = o;
+    *ws_bytes = need;
     return LOCAL_OK;
   }
-  if (*ws_bytes < o)
-    return local_fail(LOCAL_ERR_WORKSPACE, "%s: workspace %zu < %zu", who, *ws_bytes, o);
+  if (*ws_bytes < need)
+    return local_fail(LOCAL_ERR_WORKSPACE, "%s: workspace %zu < %zu", who, *ws_bytes, need);
   for (int g = 0; g < G; ++g) {
     if (!dA[g] || !dB[g]) return local_fail(LOCAL_ERR_NULL, "%s: NULL output", who);
     if (T > 0 && (!dy[g] || !A[g] || !B[g]))
@@ -647,10 +664,11 @@ local_status_t grad_impl(const char* who, const uint16_t* x, int64_t T, int64_t 
   if (T > 0) {  // u_g = x A_g^T and dy_g B_g, one launch
     ShrinkJob jobs[kGrJobs];
     for (int g = 0; g < G; ++g) {
-      jobs[g] = ShrinkJob{x, A[g], reinterpret_cast<float*>(w + o_u[g]), K};
-      jobs[G + g] = ShrinkJob{dy[g], Bt[g], reinterpret_cast<float*>(w + o_g[g]), N[g]};
+      jobs[g] = ShrinkJob{x, A[g], reinterpret_cast<float*>(w + o_u[g]), K, nullptr, nullptr};
+      jobs[G + g] = ShrinkJob{dy[g], Bt[g], reinterpret_cast<float*>(w + o_g[g]), N[g], nullptr,
+                              nullptr};
     }
-    if ((st = token_shrink(jobs, 2 * G, T, n_adapters, r_max, adapter_idx, s)) != LOCAL_OK)
+    if ((st = token_shrink(jobs, 2 * G, T, n_adapters, r_max, adapter_idx, 1, s)) != LOCAL_OK)
       return st;
   }
   // dB_g from (dy_g, s u_g), dA_g from (x, s dy_g B_g)

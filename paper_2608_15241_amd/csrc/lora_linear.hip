@@ -24,22 +24,40 @@
 //      token's own adapter and rank, adds U_s B_a^T and the residual, and
 //      rounds once to bf16.
 //  * Long prefill chunks (T > 256), two kernels:
-//    - shrink: workgroups of 64 tokens x one K slice compute, for each
-//      adapter routed in the tile and every projection of the call,
-//      x_t . A[a,j,:] of its tokens on the matrix cores; fp32 partial sums
-//      per slice.
-//    - main product: 128 tokens x 256 features per workgroup, both operands
-//      brought to LDS by direct global-to-LDS loads in a three-stage ring;
-//      the delta U_s Btilde^T (U_s[t, a*r_max + j] = bf16(s_t * sum of the
-//      slices), zero unless a is t's adapter; Btilde[n, a*r_max + j] =
+//    - shrink (lora_shrink.hip): U_s[t] = bf16(s_t x_t . A[a_t]) of every
+//      token with an adapter, for every projection of the call.
+//    - main product: 256 x 192 down to 64 x 64 tokens x features per
+//      workgroup by the size of the call, both operands brought to LDS by
+//      direct global-to-LDS loads; the delta U_s Btilde^T over stacked columns
+//      c = a*r_max + j (U_s zero unless a is t's adapter; Btilde[n, c] =
 //      B[a, n, j]) runs as extra K-steps, only over adapters used in the tile
 //      and columns below their rank.
 //  Both paths sum the base K-steps in an order that does not depend on which
 //  adapters are present, so a zero up-projection leaves y bit-identical.
+#include <algorithm>
+#include <climits>
+
 #include "common.hpp"
 #include "lora_internal.hpp"
 
 namespace localk {
+
+// The most K slices of a long chunk's shrink that its workspace holds: the
+// fewest (a divisor of the 64-k steps) whose slices of 64 tokens and of every
+// projection's rank rows fit 144 KB and give 256 workgroups, at most 8 unless
+// more are needed to fit.
+int long_slices(int64_t T, int64_t K, int r_max, int G) {
+  const int steps = static_cast<int>(K / 64);
+  const int64_t rows = 64 + static_cast<int64_t>(G) * ((r_max + 15) / 16 * 16);
+  int best = steps;
+  for (int ks = 1; ks <= steps; ++ks) {
+    if (steps % ks || rows * (steps / ks) * 128 > 147456) continue;
+    best = ks;
+    if ((T + 63) / 64 * ks >= 256 || ks >= 8) break;
+  }
+  return best;
+}
+
 namespace {
 
 constexpr int kMaxGroup = 4;            // projections sharing x in one grouped call
@@ -74,9 +92,12 @@ struct GemmArgs {
   const uint16_t* res;   // optional residual [T][N] (main mode)
   uint16_t* y;           // bf16 output [T][N]
   int ksplit;            // K slices of the decode base product (grid.z)
-  int gm, gn;            // tile grid of the long-chunk main product
-  uint64_t* tile_present;  // long chunks: bitmap of the adapters routed in each
-                           // 64-token tile, [ceil(T/64)][4], written by the shrink
+  // long chunks: the tile grid of the main product, and what the shrink wrote:
+  // U_s of every projection [G][T][r_max] bf16 and 16 bytes of zeros, or (us
+  // null) sums over K slices, pout [G][up_ks][T][r_max]
+  int gm, gn;
+  const uint16_t* us;
+  const uint16_t* zero16;
 };
 
 // Rank of adapter ad, clamped to [0, r_max] so that no rank reads past the
@@ -606,46 +627,40 @@ local_status_t run_epilogue(const GemmArgs& a, hipStream_t s) {
 
 // ----------------------------------------------------------------- prefill
 // Long chunks (T > 256), the fused main product. Workgroup: tokens
-// [m0, m0 + 128) x features [n0, n0 + 256); wave w owns features
-// n0 + 64w .. +64 for all 128 tokens (4 x 8 MFMA tiles, 128 fp32 accumulators
-// per lane). Both operands reach LDS by direct global-to-LDS loads (no
-// staging registers, no LDS store instructions): a K-step of 64 is one 48 KB
-// stage (x: 128 rows, W: 256 rows, 128 bytes each), three stages in a ring,
-// so the loads of step s + 2 are in flight while step s computes. Each load
-// instruction moves 8 whole 128-byte rows (64 lanes x 16 bytes), so the
-// vector memory path sees fully used lines. Inside a row the eight 16-byte
-// chunks are stored XOR-swizzled by the row index (chunk c of row r at
-// position c ^ (r % 8)): the MFMA operand reads (16 rows, one chunk column)
-// then touch distinct banks. The loads name their own waits (the library
-// waits on the load counter itself before each barrier). The LoRA delta
-// follows as extra K-steps over the U_s columns of the adapters used in the
-// token tile.
-constexpr int kPfM = 128;
-constexpr int kPfN = 256;
-#ifndef LOCAL_PF_WM
-#define LOCAL_PF_WM 2      // waves along tokens (x 4 along features)
-#endif
-constexpr int kPfWM = LOCAL_PF_WM;
-constexpr int kPfWN = 4;
-constexpr int kPfWaves = kPfWM * kPfWN;
-constexpr int kPfThreads = kPfWaves * kWave;
-constexpr int kPfFT = kPfN / kPfWN / 16;   // 16-feature MFMA tiles per wave (4)
-constexpr int kPfTT = kPfM / kPfWM / 16;   // 16-token MFMA tiles per wave
-constexpr int kPfRow = 128;                       // bytes of one row of a stage
-constexpr int kPfXBytes = kPfM * kPfRow;          // 16 KB
-constexpr int kPfStageBytes = (kPfM + kPfN) * kPfRow;  // 48 KB
-constexpr int kPfStages = 3;
-constexpr int kPfURow = 80;                       // bytes of a U_s tile row: 32 bf16 + pad
-constexpr int kPfUBytes = kPfM * kPfURow;         // 10 KB
-constexpr int kPfLdsBytes = kPfStages * kPfStageBytes + kPfUBytes;  // 154 KB
-constexpr int kPfOutRow = kPfN * 4 + 16;          // bytes of a token row of the output tile
-static_assert(kPfM * kPfOutRow <= kPfLdsBytes, "output tile in LDS");
-constexpr int kPfXDma = kPfM / 8 / kPfWaves;      // 1 KB loads of x per wave and step
-constexpr int kPfWDma = kPfN / 8 / kPfWaves;      // ... of W
-constexpr int kPfDma = kPfXDma + kPfWDma;
-constexpr int kPfMfma = kPfFT * kPfTT;            // MFMAs per wave and half step
+// [m0, m0 + BM) x features [n0, n0 + BN), WM x WN waves. Both operands reach
+// LDS by direct global-to-LDS loads (no staging registers, no LDS store
+// instructions): a K-step of 64 is one stage (x: BM rows, W: BN rows, 128
+// bytes each) of a ring of STAGES, so the loads of later steps are in flight
+// while step s computes. Each load instruction moves 8 whole 128-byte rows
+// (64 lanes x 16 bytes), so the vector memory path sees fully used lines.
+// Inside a row the eight 16-byte chunks are stored XOR-swizzled by the row
+// index (chunk c of row r at position c ^ (r % 8)): the MFMA operand reads
+// (16 rows, one chunk column) then touch distinct banks. The loads name their
+// own waits (the library waits on the load counter itself before each
+// barrier). The LoRA delta runs first, as K-steps over 64 stacked columns of
+// the adapters used in the token tile.
+template <int BM, int BN, int WM_, int WN_, int STAGES>
+struct PfShape {
+  static constexpr int M = BM, N = BN, WM = WM_, WN = WN_;
+  static constexpr int S = STAGES;                // ring stages
+  static constexpr int WAVES = WM * WN, THREADS = WAVES * kWave;
+  static constexpr int FT = BN / WN / 16;         // 16-feature MFMA tiles per wave
+  static constexpr int TT = BM / WM / 16;         // 16-token MFMA tiles per wave
+  static constexpr int X_BYTES = BM * 128;        // x rows of a stage
+  static constexpr int STAGE = (BM + BN) * 128;   // bytes of a stage
+  static constexpr int OUT_ROW = BN * 4 + 16;     // bytes of a token row of the output tile
+  static constexpr int RING = S * STAGE;          // the U_s tile of the delta follows it
+  static constexpr int LDS = RING + X_BYTES > BM * OUT_ROW ? RING + X_BYTES : BM * OUT_ROW;
+  static constexpr int XD = BM / 8 / WAVES, WD = BN / 8 / WAVES;  // 1 KB loads per wave and step
+  static constexpr int DMA = XD + WD;
+  static constexpr int MFMAS = FT * TT;           // per wave and half step
+  static_assert(BM % (8 * WAVES) == 0 && BN % (8 * WAVES) == 0 && LDS <= 163840, "tile");
+  static_assert(DMA * (S - 1) < 64 && S >= 3, "ring");
+};
 
-__global__ __launch_bounds__(kPfThreads, 1) void lora_prefill_kernel(GemmArgs a) {
+template <class PF>
+__global__ __launch_bounds__(PF::THREADS, 1) void lora_prefill_kernel(GemmArgs a) {
+  constexpr int FT = PF::FT, TT = PF::TT, XD = PF::XD, WD = PF::WD, S = PF::S;
   extern __shared__ __attribute__((aligned(16))) uint8_t pf_lds[];
 
   const int tid = threadIdx.x, lane = tid % kWave;
@@ -668,80 +683,90 @@ __global__ __launch_bounds__(kPfThreads, 1) void lora_prefill_kernel(GemmArgs a)
     mt = first_m + r % gsize;
     nt = r / gsize;
   }
-  const int64_t m0 = static_cast<int64_t>(mt) * kPfM;
-  const int64_t n0 = static_cast<int64_t>(nt) * kPfN;
-  // projection of the tile (a 256-feature tile lies in one projection) and
-  // its operands; feature indices below are virtual rows n0 + ...
+  const int64_t m0 = static_cast<int64_t>(mt) * PF::M;
+  const int64_t n0 = static_cast<int64_t>(nt) * PF::N;
+  // projection of the tile (a tile lies in one projection) and its operands;
+  // feature indices below are virtual rows n0 + ...
   const int gq = group_of(a, n0);
   const int64_t gbase = gstart_of(a, gq), Ng = gstart_of(a, gq + 1) - gbase;
   const uint16_t* Wg = pick(a.gw, gq);
-  const uint16_t* Bg = pick(a.gb, gq);
-  const int32_t* ranksg = pick(a.granks, gq);
-  const float* Pg = a.pout ? a.pout + static_cast<int64_t>(gq) * a.up_ks * a.T * a.r_max : nullptr;
-  const int wm = wave / kPfWN, wn = wave % kPfWN;
-  const int64_t fw0 = n0 + 16 * kPfFT * wn;  // this wave's first feature
-  const int tw0 = 16 * kPfTT * wm;           // ... and first token of the tile
+  const int wm = wave / PF::WN, wn = wave % PF::WN;
+  const int tw0 = 16 * TT * wm;  // this wave's first token of the tile
+  const int fw0 = 16 * FT * wn;  // ... and first feature
 
-  const bool lora = a.n_ad > 0 && Pg != nullptr && a.tile_present != nullptr;  // uniform
+  const bool lora = a.n_ad > 0;  // uniform
 
-  // ---- direct loads. Wave w moves x rows 32w .. +32 and W rows 64w .. +64
-  // (its own features) of every stage; lane l writes 16 bytes at
-  // block + 16 l, i.e. row 8q + l/8, position l%8, which holds chunk
-  // (l%8) ^ (l/8) of that row. Rows past T (N) repeat row m0 (row 0): their
-  // accumulators are never stored.
+  // ---- direct loads. Wave w moves BM / waves x rows and BN / waves W rows of
+  // every stage; lane l writes 16 bytes at block + 16 l, i.e. row 8q + l/8,
+  // position l%8, which holds chunk (l%8) ^ (l/8) of that row. Rows past T (N)
+  // repeat row m0 (row 0): their accumulators are never stored.
   const int dchunk = (lane % 8) ^ (lane / 8);
-  const uint16_t* xg[kPfXDma];
-  const uint16_t* wg[kPfWDma];
+  const uint16_t* xg[XD];
+  const uint16_t* wg[WD];
+  int64_t xt[XD];          // the x rows
+  // the x rows' adapters and scales, and those of the whole tile (a token per
+  // lane): loaded before the stage loads, so that they wait for nothing else
+  int xad[XD], tad[PF::M / kWave];
+  float xsc[XD];
 #pragma unroll
-  for (int q = 0; q < kPfXDma; ++q) {
-    const int64_t t = m0 + (kPfM / kPfWaves) * wave + 8 * q + lane / 8;
-    xg[q] = a.x + (t < a.T ? t : m0) * a.K + 8 * dchunk;
+  for (int h = 0; h < PF::M / kWave; ++h) {
+    const int64_t t = m0 + kWave * h + lane;
+    tad[h] = lora && t < a.T ? a.idx[t] : -1;
   }
 #pragma unroll
-  for (int q = 0; q < kPfWDma; ++q) {
-    const int64_t nl = n0 - gbase + (kPfN / kPfWaves) * wave + 8 * q + lane / 8;
+  for (int q = 0; q < XD; ++q) {
+    const int64_t t = m0 + 8 * (XD * wave + q) + lane / 8;
+    xt[q] = t < a.T ? t : m0;
+    xad[q] = lora && t < a.T ? a.idx[t] : -1;
+    xsc[q] = lora && t < a.T ? a.scale[t] : 0.f;
+    xg[q] = a.x + xt[q] * a.K + 8 * dchunk;
+  }
+#pragma unroll
+  for (int q = 0; q < WD; ++q) {
+    const int64_t nl = n0 - gbase + 8 * (WD * wave + q) + lane / 8;
     wg[q] = Wg + (nl < Ng ? nl : 0) * a.K + 8 * dchunk;
   }
+  auto x_dst = [&](int stage, int q) {
+    return pf_lds + stage * PF::STAGE + 1024 * (XD * wave + q);
+  };
+  auto w_dst = [&](int stage, int q) {
+    return pf_lds + stage * PF::STAGE + PF::X_BYTES + 1024 * (WD * wave + q);
+  };
   // loads of K-step s into stage `stage`
   auto issue = [&](int stage, int s) {
-    uint8_t* st = pf_lds + stage * kPfStageBytes;
     const int64_t k = static_cast<int64_t>(s) * 64;
 #pragma unroll
-    for (int q = 0; q < kPfXDma; ++q)
-      __builtin_amdgcn_global_load_lds(xg[q] + k, st + ((kPfM / kPfWaves) * wave + 8 * q) * kPfRow,
-                                       16, 0, 0);
+    for (int q = 0; q < XD; ++q) lds_load16(xg[q] + k, x_dst(stage, q));
 #pragma unroll
-    for (int q = 0; q < kPfWDma; ++q)
-      __builtin_amdgcn_global_load_lds(
-          wg[q] + k, st + kPfXBytes + ((kPfN / kPfWaves) * wave + 8 * q) * kPfRow, 16, 0, 0);
+    for (int q = 0; q < WD; ++q) lds_load16(wg[q] + k, w_dst(stage, q));
   };
 
-  f32x4 acc[kPfFT][kPfTT];
+  f32x4 acc[FT][TT];
 #pragma unroll
-  for (int i = 0; i < kPfFT; ++i)
+  for (int i = 0; i < FT; ++i)
 #pragma unroll
-    for (int j = 0; j < kPfTT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < TT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // MFMA operand reads. K-group g of MFMA m holds k = 32m + 8g .. +8 of the
   // step (chunk 4m + g), the same for W and x; chunk c of row r sits at
   // position c ^ (r % 8), and r % 8 = col % 8 for every row a lane reads.
-  const int rd0 = col * kPfRow + 16 * (kgrp ^ (col % 8));  // chunk kgrp
-  const int rd1 = rd0 ^ 64;                                 // chunk 4 + kgrp
-  u32x4 xf[2][kPfTT], wf[2][kPfFT];
+  const int rd0 = col * 128 + 16 * (kgrp ^ (col % 8));  // chunk kgrp
+  const int rd1 = rd0 ^ 64;                              // chunk 4 + kgrp
+  u32x4 xf[2][TT], wf[2][FT];
   auto read_half = [&](int stage, int m) {
-    const uint8_t* st = pf_lds + stage * kPfStageBytes + (m ? rd1 : rd0);
+    const uint8_t* st = pf_lds + stage * PF::STAGE + (m ? rd1 : rd0);
 #pragma unroll
-    for (int i = 0; i < kPfFT; ++i)
-      wf[m][i] = *reinterpret_cast<const u32x4*>(st + kPfXBytes + (16 * kPfFT * wn + 16 * i) * kPfRow);
+    for (int i = 0; i < FT; ++i)
+      wf[m][i] = *reinterpret_cast<const u32x4*>(st + PF::X_BYTES + (fw0 + 16 * i) * 128);
 #pragma unroll
-    for (int j = 0; j < kPfTT; ++j)
-      xf[m][j] = *reinterpret_cast<const u32x4*>(st + (tw0 + 16 * j) * kPfRow);
+    for (int j = 0; j < TT; ++j)
+      xf[m][j] = *reinterpret_cast<const u32x4*>(st + (tw0 + 16 * j) * 128);
   };
   // MFMAs [b, e) of half m, in the order tile (i, j) = (idx / TT, idx % TT)
   auto mfma_range = [&](int m, int b, int e) {
 #pragma unroll
     for (int idx = b; idx < e; ++idx) {
-      const int i = idx / kPfTT, j = idx % kPfTT;
+      const int i = idx / TT, j = idx % TT;
       acc[i][j] = mfma16x16x32(as_bf16x8(wf[m][i]), as_bf16x8(xf[m][j]), acc[i][j]);
     }
   };
@@ -749,205 +774,184 @@ __global__ __launch_bounds__(kPfThreads, 1) void lora_prefill_kernel(GemmArgs a)
   // group sizes of a step: R operand reads per half, Q MFMAs of the second
   // half before the barrier, the loads paired with MFMAs after the reads
   constexpr int kSgMfma = 0x8, kSgVmem = 0x10, kSgDsRead = 0x100;
-  constexpr int kR = kPfFT + kPfTT, kQ = kPfMfma / 4;
-  constexpr int kVPair = kPfDma < kPfMfma - kQ - kR ? kPfDma : kPfMfma - kQ - kR;
-  static_assert(kPfMfma - kQ >= kR && kVPair >= 0, "step schedule");
+  constexpr int kR = FT + TT;
+  constexpr int kQ = PF::MFMAS / 4 < PF::MFMAS - kR ? PF::MFMAS / 4 : PF::MFMAS - kR;
+  constexpr int kVPair = PF::DMA < PF::MFMAS - kQ - kR ? PF::DMA : PF::MFMAS - kQ - kR;
+  static_assert(kQ >= 0 && kVPair >= 0, "step schedule");
 
-  // Step s (stage s % 3), first half: the m = 1 operands are read under the
+  // Step s (stage s % S), first half: the m = 1 operands are read under the
   // m = 0 MFMAs. Then each wave waits for its own loads of step s + 1 (those
-  // of step s + 2 may stay in flight) and for its reads of stage s % 3; after
-  // the barrier every wave's loads of step s + 1 are visible and stage s % 3
-  // is free, so the loads of step s + 3 refill it. Second half: the m = 0
+  // of later steps may stay in flight) and for its reads of stage s % S; after
+  // the barrier every wave's loads of step s + 1 are visible and stage s % S
+  // is free, so the loads of step s + S refill it. Second half: the m = 0
   // operands of step s + 1 are read under the m = 1 MFMAs of step s. The
   // body has no branch (a branch between the two halves makes the compiler
-  // copy the 128 accumulators around it): past the last step the loads
+  // copy the accumulators around it): past the last step the loads
   // repeat the last step into the free stage and the reads fetch operands
   // that are never used, so every wait count holds at every step.
   const int steps = static_cast<int>(a.K / 64);
   const int last = steps - 1;
-  // the first three stages' loads go out before anything else waits
-  issue(0, 0);
-  issue(1, min(1, last));
-  issue(2, min(2, last));
+  // the loads of every stage go out before anything else waits
+#pragma unroll
+  for (int p = 0; p < S; ++p) issue(p, min(p, last));
 
-  // ---- LoRA delta first, chunk by chunk (32 stacked columns
-  // c = a*r_max + j): U_s[t][c] = bf16(s_t * sum_z P[z][t][j]) (slices in
-  // order) when a is token t's adapter, else 0, formed by the whole
-  // workgroup into an LDS tile; Btilde is zero at or past the rank. Its
-  // chain of loads runs while the first stages load. Adding the delta first
-  // leaves a zero up-projection's result bit-identical (the MFMAs add +0).
-  // The adapters routed in the tile come from the bitmaps the shrink wrote
-  // for its two 64-token tiles, read by scalar loads, which do not wait for
-  // the stage loads.
-  uint64_t pm[4] = {0ull, 0ull, 0ull, 0ull};
+  // ---- LoRA delta: K-steps of 64 stacked columns c = a*r_max + j, a tile of
+  // U_s rows (laid out as x rows) against B rows loaded as operands, while the
+  // first stages load. U_s[t][c] = bf16(s_t u) when a is token t's adapter and
+  // j below its rank, else 0: as the shrink wrote it, by direct loads like
+  // those of x (pieces of other adapters from 16 bytes of zeros), or formed
+  // here from the sums of its K slices, in order. B's columns at or past the
+  // rank, and those of adapters that no token of the tile uses, are zeroed on
+  // their way into the product (they may hold anything). Adding the delta
+  // first leaves a zero up-projection's result bit-identical (the MFMAs add
+  // +0).
   if (lora) {
-    const int n64 = static_cast<int>((a.T + 63) / 64);
-    using const_u64 = const __attribute__((address_space(4))) uint64_t;  // scalar loads
-    const_u64* tp = (const_u64*)a.tile_present;
+    const uint16_t* Bg = pick(a.gb, gq);
+    const int32_t* ranksg = pick(a.granks, gq);
+    uint8_t* ut = pf_lds + PF::RING;
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-      if (2 * mt + h < n64)
+    for (int h = 0; h < PF::M / kWave; ++h)
+      if (tad[h] >= a.n_ad) tad[h] = -1;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) pm[w] |= tp[4 * (2 * mt + h) + w];
-  }
-  // the first chunk after chunk c that covers a routed adapter, or -1
-  auto next_chunk = [&](int c) {
-    const int amin = ((c + 1) * 32) / a.r_max;  // adapters with columns past chunk c
-    int found = -1;
+    for (int q = 0; q < XD; ++q)
+      if (xad[q] >= a.n_ad) xad[q] = -1;
+    // the first chunk after chunk c with columns of an adapter that a token of
+    // the tile uses, or -1
+    auto next_chunk = [&](int c) {
+      int first = INT_MAX;
 #pragma unroll
-    for (int w = 3; w >= 0; --w) {
-      uint64_t m = pm[w];
-      if (64 * w + 63 < amin)
-        m = 0ull;
-      else if (64 * w < amin)
-        m &= ~0ull << (amin - 64 * w);
-      if (m) found = 64 * w + __builtin_ctzll(m);
-    }
-    return found < 0 ? -1 : max(c + 1, found * a.r_max / 32);
-  };
-  auto routed = [&](int ad) {  // per lane: adapter ad is routed in the tile
-    const int w = ad >> 6;
-    const uint64_t m = w == 0 ? pm[0] : w == 1 ? pm[1] : w == 2 ? pm[2] : pm[3];
-    return ((m >> (ad & 63)) & 1ull) != 0ull;
-  };
-  if (lora) {
-    uint8_t* ut = pf_lds + kPfStages * kPfStageBytes;  // [128 tokens][kPfURow]
-    // forming: kFTpt threads per token, kFG groups of 8 columns each
-    constexpr int kFTpt = kPfThreads / kPfM, kFG = 4 / kFTpt;
-    const int ftl = tid / kFTpt, fh = tid % kFTpt;
-    const int64_t ft = m0 + ftl;
-    const int64_t ftc = ft < a.T ? ft : m0;
-    const int fidx = a.idx[ftc];
-    const float fscl = a.scale[ftc];
-    const int64_t slice = a.T * a.r_max;
-    // Every load of a chunk is issued unconditionally (clamped to valid
-    // addresses) and masked afterwards, so that all of them are in flight
-    // together.
-    for (int c = next_chunk(-1); c >= 0; c = next_chunk(c)) {
-      const int c0 = c * 32;
-      // Btilde operand: features fw0 + 16i + col, columns cb .. cb+8
-      const int cb = c0 + 8 * kgrp;
-      const int bad = min(cb / a.r_max, a.n_ad - 1), bj = cb % a.r_max;
-      const int brk = ranksg ? ranksg[bad] : a.r_max;
-      u32x4 bw[kPfFT];
+      for (int h = 0; h < PF::M / kWave; ++h)
+        if (tad[h] >= 0 && ((tad[h] + 1) * a.r_max - 1) / 64 > c)
+          first = min(first, max(tad[h] * a.r_max / 64, c + 1));
+      if (a.R <= 64) return __any(first == 0) ? 0 : -1;
 #pragma unroll
-      for (int i = 0; i < kPfFT; ++i) {
-        const int64_t nl = fw0 - gbase + 16 * i + col;
-        bw[i] = ld_global<u32x4>(Bg + (static_cast<int64_t>(bad) * Ng + (nl < Ng ? nl : 0)) *
-                                          a.r_max + bj);
+      for (int off = kWave / 2; off > 0; off >>= 1) first = min(first, __shfl_xor(first, off));
+      first = __builtin_amdgcn_readfirstlane(first);
+      return first == INT_MAX ? -1 : first;
+    };
+    for (int c = next_chunk(-1); c >= 0;) {
+      const int cl = c * 64 + 8 * dchunk;  // the stacked columns of this lane's pieces
+      const int ca = cl / a.r_max, cj = cl % a.r_max;
+      // B operands: features fw0 + 16 i + col, columns 64 c + 32 m + 8 kgrp ..
+      // +8, and how many of those columns are used
+      const int a_lo = c * 64 / a.r_max;
+      uint32_t routed = 0u;  // bit i: a token of the tile uses adapter a_lo + i
+      for (int i = 0; i <= (c * 64 + 63) / a.r_max - a_lo; ++i) {
+        bool any = false;
+#pragma unroll
+        for (int h = 0; h < PF::M / kWave; ++h) any |= tad[h] == a_lo + i;
+        routed |= __any(any) ? 1u << i : 0u;
       }
-      // forming: columns c0 + 8 (kFG fh + g), g < kFG (8 columns of one adapter)
-      int frk[kFG];
-      int64_t off[kFG];
+      u32x4 bw[2][FT];
+      int keep[2];
 #pragma unroll
-      for (int g = 0; g < kFG; ++g) {
-        const int c = c0 + 8 * (kFG * fh + g);
-        frk[g] = ranksg ? ranksg[min(c / a.r_max, a.n_ad - 1)] : a.r_max;
-        off[g] = (ft < a.T ? ft : m0) * a.r_max + c % a.r_max;
-      }
-      f32x4 sum[kFG][2] = {};
-      constexpr int kZB = 8;  // slices loaded together
-      for (int z0 = 0; z0 < a.up_ks; z0 += kZB) {
-        f32x4 v[kZB][kFG][2];
+      for (int m = 0; m < 2; ++m) {
+        const int k0 = c * 64 + 32 * m + 8 * kgrp;
+        const int ad = min(k0 / a.r_max, a.n_ad - 1), j = k0 % a.r_max;
+        const int rk = ranksg ? min(max(ranksg[ad], 0), a.r_max) : a.r_max;
+        keep[m] = k0 < a.R && (routed >> (ad - a_lo) & 1u) ? rk - j : 0;
 #pragma unroll
-        for (int dz = 0; dz < kZB; ++dz)
-#pragma unroll
-          for (int g = 0; g < kFG; ++g) {
-            const int64_t o = static_cast<int64_t>(min(z0 + dz, a.up_ks - 1)) * slice + off[g];
-            v[dz][g][0] = ld_global<f32x4>(Pg + o);
-            v[dz][g][1] = ld_global<f32x4>(Pg + o + 4);
-          }
-        // every slice's loads are issued before the first sum (the compiler
-        // would otherwise move some into the conditional sums below, one
-        // memory round trip after the others)
-#pragma unroll
-        for (int dz = 0; dz < kZB; ++dz)
-#pragma unroll
-          for (int g = 0; g < kFG; ++g) asm volatile("" : "+v"(v[dz][g][0]), "+v"(v[dz][g][1]));
-#pragma unroll
-        for (int dz = 0; dz < kZB; ++dz)
-          if (z0 + dz < a.up_ks)
-#pragma unroll
-            for (int g = 0; g < kFG; ++g) {
-              sum[g][0] += v[dz][g][0];
-              sum[g][1] += v[dz][g][1];
-            }
-      }
-      // U_s: zero unless the columns' adapter is the token's, and at or past
-      // its rank (padding rows of A may hold anything). The token's adapter
-      // and scale are passed through an empty asm here so that the compiler
-      // cannot test them (and wait for their loads, which the stage loads
-      // precede) before the chunk's loads are issued.
-      int fidx_c = fidx;
-      float fscl_c = fscl;
-      asm volatile("" : "+v"(fidx_c), "+v"(fscl_c));
-      const int fad = (ft < a.T && fidx_c >= 0 && fidx_c < a.n_ad) ? fidx_c : -1;
-#pragma unroll
-      for (int g = 0; g < kFG; ++g) {
-        const int c = c0 + 8 * (kFG * fh + g);
-        const bool own = c < a.R && fad == c / a.r_max;
-        const int keep = own ? min(max(frk[g], 0), a.r_max) - c % a.r_max : 0;
-        float u[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float sv = e < 4 ? sum[g][0][e] : sum[g][1][e - 4];
-          u[e] = e < keep ? fscl_c * sv : 0.f;
+        for (int i = 0; i < FT; ++i) {
+          const int64_t nl = n0 - gbase + fw0 + 16 * i + col;
+          bw[m][i] = ld_global<u32x4>(
+              Bg + (static_cast<int64_t>(ad) * Ng + (nl < Ng ? nl : 0)) * a.r_max + j);
         }
-        *reinterpret_cast<u32x4*>(ut + ftl * kPfURow + 16 * (kFG * fh + g)) =
-            u32x4{pack_bf16x2(u[0], u[1]), pack_bf16x2(u[2], u[3]), pack_bf16x2(u[4], u[5]),
-                  pack_bf16x2(u[6], u[7])};
       }
-      // Btilde: zero for an adapter not routed in the tile, and at or past
-      // the rank
-      const int bkeep = (cb < a.R && routed(bad))
-                            ? min(max(brk, 0), a.r_max) - bj : 0;
-      bf16x8 bv[kPfFT];
+      if (a.us) {
+        const uint16_t* Ug = a.us + gq * a.T * a.r_max;
 #pragma unroll
-      for (int i = 0; i < kPfFT; ++i) bv[i] = as_bf16x8(keep_first8(bw[i], bkeep));
+        for (int q = 0; q < XD; ++q)
+          lds_load16(xad[q] == ca ? Ug + xt[q] * a.r_max + cj : a.zero16,
+                     ut + 1024 * (XD * wave + q));
+      } else {
+        // All loads go out before the first sum: clamped to valid addresses
+        // instead of left out, four slices at a time.
+        const float* Pg = a.pout + static_cast<int64_t>(gq) * a.up_ks * a.T * a.r_max;
+        const int rk = ranksg ? min(max(ranksg[min(ca, a.n_ad - 1)], 0), a.r_max) : a.r_max;
+        const int64_t slice = a.T * a.r_max;
+        f32x4 sum[XD][2] = {};
+        for (int z0 = 0; z0 < a.up_ks; z0 += 4) {
+          f32x4 v[4][XD][2];
+#pragma unroll
+          for (int dz = 0; dz < 4; ++dz)
+#pragma unroll
+            for (int q = 0; q < XD; ++q) {
+              const float* p = Pg + min(z0 + dz, a.up_ks - 1) * slice +
+                               (xad[q] == ca ? xt[q] * a.r_max + cj : 0);
+              v[dz][q][0] = ld_global<f32x4>(p);
+              v[dz][q][1] = ld_global<f32x4>(p + 4);
+            }
+#pragma unroll
+          for (int dz = 0; dz < 4; ++dz)
+            if (z0 + dz < a.up_ks)
+#pragma unroll
+              for (int q = 0; q < XD; ++q) {
+                sum[q][0] += v[dz][q][0];
+                sum[q][1] += v[dz][q][1];
+              }
+        }
+#pragma unroll
+        for (int q = 0; q < XD; ++q) {
+          const int keep = xad[q] == ca ? rk - cj : 0;
+          float u[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            u[i] = i < keep ? xsc[q] * (i < 4 ? sum[q][0][i] : sum[q][1][i - 4]) : 0.f;
+          *reinterpret_cast<u32x4*>(ut + 1024 * (XD * wave + q) + 16 * lane) =
+              u32x4{pack_bf16x2(u[0], u[1]), pack_bf16x2(u[2], u[3]), pack_bf16x2(u[4], u[5]),
+                    pack_bf16x2(u[6], u[7])};
+        }
+      }
+      wait_vmcnt<0>();
       wait_lgkm0_barrier();
-      bf16x8 uv[kPfTT];
 #pragma unroll
-      for (int j = 0; j < kPfTT; ++j)
-        uv[j] = as_bf16x8(
-            *reinterpret_cast<const u32x4*>(ut + (tw0 + 16 * j + col) * kPfURow + 16 * kgrp));
+      for (int m = 0; m < 2; ++m) {
+        u32x4 uv[TT];
 #pragma unroll
-      for (int i = 0; i < kPfFT; ++i)
+        for (int j = 0; j < TT; ++j)
+          uv[j] = *reinterpret_cast<const u32x4*>(ut + (tw0 + 16 * j) * 128 + (m ? rd1 : rd0));
 #pragma unroll
-        for (int j = 0; j < kPfTT; ++j) acc[i][j] = mfma16x16x32(bv[i], uv[j], acc[i][j]);
-      wait_lgkm0_barrier();  // the tile is rewritten by the next chunk
+        for (int i = 0; i < FT; ++i) {
+          const bf16x8 b = as_bf16x8(keep_first8(bw[m][i], keep[m]));
+#pragma unroll
+          for (int j = 0; j < TT; ++j) acc[i][j] = mfma16x16x32(b, as_bf16x8(uv[j]), acc[i][j]);
+        }
+      }
+      c = next_chunk(c);
+      if (c >= 0) wait_lgkm0_barrier();  // the tile is rewritten
     }
   }
-  wait_vmcnt<0>();
+  wait_vmcnt<PF::DMA * (S - 1)>();
   wait_lgkm0_barrier();
   read_half(0, 0);
   // unrolled over the stage ring so that stage offsets are constants; the
   // tail leaves the loop (a branch out of the loop, not around work in it)
-  for (int s0 = 0; s0 < steps; s0 += kPfStages) {
+  for (int s0 = 0; s0 < steps; s0 += S) {
 #pragma unroll
-    for (int u = 0; u < kPfStages; ++u) {
+    for (int u = 0; u < S; ++u) {
       const int s = s0 + u;
       if (s >= steps) break;
       // first half: one operand read (m = 1) beside each of the first kR
       // MFMAs (m = 0)
       read_half(u, 1);
-      mfma_range(0, 0, kPfMfma);
+      mfma_range(0, 0, PF::MFMAS);
 #pragma unroll
       for (int g = 0; g < kR; ++g) {
         __builtin_amdgcn_sched_group_barrier(kSgMfma, 1, 0);
         __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 0);
       }
-      __builtin_amdgcn_sched_group_barrier(kSgMfma, kPfMfma - kR, 0);
+      if (PF::MFMAS > kR) __builtin_amdgcn_sched_group_barrier(kSgMfma, PF::MFMAS - kR, 0);
       __builtin_amdgcn_sched_barrier(0);
       // second half: kQ MFMAs (m = 1) before the barrier, then the operand
-      // reads of the next step and the loads of step s + 3 beside the rest
+      // reads of the next step and the loads of step s + S beside the rest
       mfma_range(1, 0, kQ);
       __builtin_amdgcn_sched_barrier(0);
-      wait_vmcnt<kPfDma>();
+      wait_vmcnt<PF::DMA * (S - 2)>();
       wait_lgkm0_barrier();
       __builtin_amdgcn_sched_barrier(0);
-      read_half((u + 1) % kPfStages, 0);
-      issue(u, min(s + 3, last));
-      mfma_range(1, kQ, kPfMfma);
+      read_half((u + 1) % S, 0);
+      issue(u, min(s + S, last));
+      mfma_range(1, kQ, PF::MFMAS);
 #pragma unroll
       for (int g = 0; g < kR; ++g) {
         __builtin_amdgcn_sched_group_barrier(kSgMfma, 1, 1);
@@ -958,9 +962,9 @@ __global__ __launch_bounds__(kPfThreads, 1) void lora_prefill_kernel(GemmArgs a)
         __builtin_amdgcn_sched_group_barrier(kSgMfma, 1, 1);
         __builtin_amdgcn_sched_group_barrier(kSgVmem, 1, 1);
       }
-      if (kPfDma > kVPair) __builtin_amdgcn_sched_group_barrier(kSgVmem, kPfDma - kVPair, 1);
-      if (kPfMfma - kQ - kR > kVPair)
-        __builtin_amdgcn_sched_group_barrier(kSgMfma, kPfMfma - kQ - kR - kVPair, 1);
+      if (PF::DMA > kVPair) __builtin_amdgcn_sched_group_barrier(kSgVmem, PF::DMA - kVPair, 1);
+      if (PF::MFMAS - kQ - kR > kVPair)
+        __builtin_amdgcn_sched_group_barrier(kSgMfma, PF::MFMAS - kQ - kR - kVPair, 1);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -970,32 +974,33 @@ __global__ __launch_bounds__(kPfThreads, 1) void lora_prefill_kernel(GemmArgs a)
   // every wave's loads have landed and its reads are done), so that each
   // thread then finishes 8 consecutive features of one token: the residual
   // and the output move as coalesced 16-byte pieces. Token rows are
-  // kPfOutRow bytes (1 KB + 16), so the 16 tokens of one MFMA tile written
+  // padded by 16 bytes, so the 16 tokens of one MFMA tile written
   // together fall in distinct banks.
-  wait_lgkm0_barrier();
-#pragma unroll
-  for (int j = 0; j < kPfTT; ++j)
-#pragma unroll
-    for (int i = 0; i < kPfFT; ++i)
-      *reinterpret_cast<f32x4*>(pf_lds + (tw0 + 16 * j + col) * kPfOutRow +
-                                (16 * kPfFT * wn + 16 * i + 4 * kgrp) * 4) = acc[i][j];
-  wait_lgkm0_barrier();
   const uint16_t* res = pick(a.gres, gq);
   uint16_t* y = pick(a.gy, gq);
-  constexpr int kGroups = kPfN / 8;                       // 8-feature groups per token
-  constexpr int kItems = kPfM * kGroups / kPfThreads;     // per thread
+  wait_lgkm0_barrier();
+#pragma unroll
+  for (int j = 0; j < TT; ++j)
+#pragma unroll
+    for (int i = 0; i < FT; ++i)
+      *reinterpret_cast<f32x4*>(pf_lds + (tw0 + 16 * j + col) * PF::OUT_ROW +
+                                (fw0 + 16 * i + 4 * kgrp) * 4) = acc[i][j];
+  wait_lgkm0_barrier();
+  constexpr int kGroups = PF::N / 8;                     // 8-feature groups per token
+  constexpr int kItems = PF::M * kGroups / PF::THREADS;  // per thread
+  static_assert(PF::M * kGroups % PF::THREADS == 0, "output items");
   u32x4 rv[kItems];
 #pragma unroll
   for (int e = 0; e < kItems; ++e) {
-    const int item = tid + e * kPfThreads, tl = item / kGroups, f = 8 * (item % kGroups);
+    const int item = tid + e * PF::THREADS, tl = item / kGroups, f = 8 * (item % kGroups);
     const int64_t t = m0 + tl, n = n0 - gbase + f;
     rv[e] = (res && t < a.T && n < Ng) ? ld_global<u32x4>(res + t * Ng + n) : u32x4{0u, 0u, 0u, 0u};
   }
 #pragma unroll
   for (int e = 0; e < kItems; ++e) {
-    const int item = tid + e * kPfThreads, tl = item / kGroups, f = 8 * (item % kGroups);
+    const int item = tid + e * PF::THREADS, tl = item / kGroups, f = 8 * (item % kGroups);
     const int64_t t = m0 + tl, n = n0 - gbase + f;
-    const uint8_t* src = pf_lds + tl * kPfOutRow + f * 4;
+    const uint8_t* src = pf_lds + tl * PF::OUT_ROW + f * 4;
     const f32x4 lo = *reinterpret_cast<const f32x4*>(src);
     const f32x4 hi = *reinterpret_cast<const f32x4*>(src + 16);
     float o[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
@@ -1014,164 +1019,16 @@ __global__ __launch_bounds__(kPfThreads, 1) void lora_prefill_kernel(GemmArgs a)
   }
 }
 
-// ------------------------------------------------------------ long shrink
-// Long chunks (T > 256): the shrink as SGMV partial sums over K slices,
-//   P[g][z][t][j] = sum over slice z of x[t][k] A_g[a_t][j][k],   j < r_max,
-// for the token's own adapter a_t only and every projection g of the call.
-// Workgroup: 64 tokens x one K slice of sps 64-k steps; wave w owns tokens
-// 16w .. 16w + 15 over the whole slice, so nothing is reduced across waves.
-// The x slice is brought to LDS by direct loads while wave 0 lists the
-// adapters routed in the tile; then, adapter by adapter, the A slices of
-// every projection (r_max rows padded to 16) follow, in the 128-byte rows and
-// chunk swizzle of the main product. x is read once for all projections.
-constexpr int kShTok = 64;
-constexpr int kShThreads = 256;
-constexpr int kShWaves = kShThreads / kWave;
-constexpr size_t kShLdsMax = 147456;
-
-struct ShrinkShape {
-  int ks;      // K slices (grid.y)
-  int sps;     // 64-k steps per slice
-  int rpad;    // r_max rounded up to 16
-  size_t lds;  // dynamic LDS bytes
+// One projection of a (grouped) call.
+struct Proj {
+  const uint16_t* W;
+  int64_t N;
+  const uint16_t* A;
+  const uint16_t* B;
+  const int32_t* ranks;
+  const uint16_t* res;
+  uint16_t* y;
 };
-
-size_t shrink_lds(int sps, int rpad, int G) {
-  return static_cast<size_t>(kShTok + G * rpad) * sps * 128;
-}
-
-// Fewest K slices (a divisor of the step count) that fit LDS and give at
-// least one workgroup per compute unit, at most kShMaxSlices of them unless
-// LDS needs more (the main product sums the slices for every U_s value it
-// uses). One slice step always fits: (64 + 4 * 128) rows of 128 bytes.
-constexpr int kShMaxSlices = 8;
-ShrinkShape shrink_shape(int64_t T, int64_t K, int r_max, int G) {
-  const int steps = static_cast<int>(K / 64);
-  const int rpad = (r_max + 15) / 16 * 16;
-  const int64_t tiles = (T + kShTok - 1) / kShTok;
-  ShrinkShape best{steps, 1, rpad, shrink_lds(1, rpad, G)};
-  for (int ks = 1; ks <= steps; ++ks) {
-    if (steps % ks) continue;
-    const int sps = steps / ks;
-    const size_t lds = shrink_lds(sps, rpad, G);
-    if (lds > kShLdsMax) continue;
-    best = ShrinkShape{ks, sps, rpad, lds};
-    if (tiles * ks >= 256 || ks >= kShMaxSlices) break;
-  }
-  return best;
-}
-
-template <int RT>
-__global__ __launch_bounds__(kShThreads) void lora_shrink_long_kernel(GemmArgs a, int sps) {
-  constexpr int rpad = 16 * RT;
-  extern __shared__ __attribute__((aligned(16))) uint8_t sh_lds[];
-  __shared__ int ad_list[kShTok];
-  __shared__ int tok_ad[kShTok];
-  __shared__ int n_list;
-
-  const int tid = threadIdx.x, lane = tid % kWave;
-  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int col = lane % 16, kgrp = lane / 16;
-  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kShTok;
-  const int z = blockIdx.y;
-  const int G = a.G;
-  static_assert(kShTok == kWave, "wave 0 reads one token per lane");
-  const int64_t k0 = static_cast<int64_t>(z) * sps * 64;
-  uint8_t* xl = sh_lds;                                            // [sps][64][128 B]
-  uint8_t* al = sh_lds + static_cast<size_t>(sps) * kShTok * 128;  // [G][sps][rpad][128 B]
-
-  // wave 0 reads the tile's adapters before it issues any x load, so that
-  // listing them waits for that load alone; the other waves read theirs from
-  // LDS after the list is made
-  const int my = wave == 0 ? token_adapter(a, t0 + lane) : -1;
-  const int64_t t = t0 + 16 * wave + col;  // this lane's token (MFMA column)
-
-  // direct loads as in the main product: lane l writes 16 bytes at
-  // block + 16 l = row 8b + l/8, position l%8, holding chunk (l%8) ^ (l/8);
-  // wave w moves rows 8w .. +8 and 32 + 8w .. +8 of every step
-  const int dchunk = (lane % 8) ^ (lane / 8);
-  auto load_x = [&]() {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int r0 = 8 * (wave + kShWaves * i);
-      const int64_t tr = t0 + r0 + lane / 8;
-      const uint16_t* src = a.x + (tr < a.T ? tr : t0) * a.K + k0 + 8 * dchunk;
-      for (int st = 0; st < sps; ++st)
-        lds_load16(src + 64 * st, xl + (static_cast<size_t>(st) * kShTok + r0) * 128);
-    }
-  };
-  if (wave == 0) {  // adapters routed in the tile, in order of first appearance
-    uint64_t pending = __ballot(my >= 0);
-    int n = 0;
-    uint64_t bits = 0ull;  // lane w < 4: word w of the tile's adapter bitmap
-    while (pending) {
-      const int ad = __shfl(my, __ffsll(static_cast<long long>(pending)) - 1);
-      if (lane == 0) ad_list[n] = ad;
-      ++n;
-      if (lane == (ad >> 6)) bits |= 1ull << (ad & 63);
-      pending &= ~__ballot(my == ad);
-    }
-    if (lane == 0) n_list = n;
-    tok_ad[lane] = my;
-    if (z == 0 && lane < 4) a.tile_present[4 * blockIdx.x + lane] = bits;
-  }
-  load_x();
-  wait_lgkm0_barrier();  // the list; the x loads stay in flight
-  const int n_ad_tile = n_list;
-  const int t_ad = tok_ad[16 * wave + col];
-
-  const int rd0 = col * 128 + 16 * (kgrp ^ (col % 8));
-  const int rd1 = rd0 ^ 64;
-  const int64_t slice = a.T * a.r_max;
-  const int a_blocks = sps * (rpad / 8);  // 8-row load blocks per projection
-  for (int q = 0; q < n_ad_tile; ++q) {
-    const int ad = ad_list[q];
-    if (q > 0) wait_lgkm0_barrier();  // every wave is done with the previous A
-    // A rows of the adapter, every projection (rows past r_max repeat its
-    // last row: never stored)
-    for (int b = wave; b < G * a_blocks; b += kShWaves) {
-      const int g = b / a_blocks, st = (b % a_blocks) / (rpad / 8), rb = b % (rpad / 8);
-      const int j = min(8 * rb + lane / 8, a.r_max - 1);
-      lds_load16(pick(a.ga, g) + (static_cast<int64_t>(ad) * a.r_max + j) * a.K + k0 + 64 * st +
-                     8 * dchunk,
-                 al + ((static_cast<size_t>(g) * sps + st) * rpad + 8 * rb) * 128);
-    }
-    wait_vmcnt<0>();
-    wait_lgkm0_barrier();
-
-    for (int g = 0; g < G; ++g) {
-      f32x4 acc[RT];
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      const uint8_t* ag = al + static_cast<size_t>(g) * sps * rpad * 128;
-      for (int st = 0; st < sps; ++st) {
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-          const int rd = m ? rd1 : rd0;
-          const u32x4 xf =
-              *reinterpret_cast<const u32x4*>(xl + (st * kShTok + 16 * wave) * 128 + rd);
-          u32x4 af[RT];
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt)
-            af[rt] = *reinterpret_cast<const u32x4*>(ag + (st * rpad + 16 * rt) * 128 + rd);
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt)
-            acc[rt] = mfma16x16x32(as_bf16x8(af[rt]), as_bf16x8(xf), acc[rt]);
-        }
-      }
-      // lane l of tile rt holds rank rows 16 rt + 4 (l/16) .. +4 of token t
-      if (t_ad == ad) {
-        float* Pz = a.pout + (static_cast<int64_t>(g) * a.up_ks + z) * slice + t * a.r_max;
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          const int j = 16 * rt + 4 * kgrp;
-          if (j < a.r_max) *reinterpret_cast<f32x4*>(Pz + j) = acc[rt];
-        }
-      }
-    }
-  }
-  wait_vmcnt<0>();  // no direct load may still be writing LDS when the workgroup ends
-}
 
 template <typename Kernel>
 void raise_lds_limit(Kernel k, size_t bytes, bool& done) {
@@ -1183,34 +1040,75 @@ void raise_lds_limit(Kernel k, size_t bytes, bool& done) {
   }
 }
 
+template <class PF>
 local_status_t launch_prefill(GemmArgs a, hipStream_t s) {
-  a.gm = static_cast<int>((a.T + kPfM - 1) / kPfM);
-  a.gn = static_cast<int>((a.N + kPfN - 1) / kPfN);
+  a.gm = static_cast<int>((a.T + PF::M - 1) / PF::M);
+  a.gn = static_cast<int>((a.N + PF::N - 1) / PF::N);
   static bool done = false;
-  raise_lds_limit(lora_prefill_kernel, kPfLdsBytes, done);
-  lora_prefill_kernel<<<a.gm * a.gn, kPfThreads, kPfLdsBytes, s>>>(a);
+  raise_lds_limit(lora_prefill_kernel<PF>, PF::LDS, done);
+  lora_prefill_kernel<PF><<<a.gm * a.gn, PF::THREADS, PF::LDS, s>>>(a);
   return local_check_launch("lora_linear (prefill)");
 }
 
-template <int RT>
-local_status_t launch_shrink_rt(GemmArgs a, const ShrinkShape& sh, hipStream_t s) {
-  static bool done = false;
-  raise_lds_limit(lora_shrink_long_kernel<RT>, kShLdsMax, done);
-  const dim3 grid(static_cast<unsigned>((a.T + kShTok - 1) / kShTok), static_cast<unsigned>(sh.ks));
-  lora_shrink_long_kernel<RT><<<grid, kShThreads, sh.lds, s>>>(a, sh.sps);
-  return local_check_launch("lora_linear (shrink)");
+using Pf128x256 = PfShape<128, 256, 2, 4, 3>;
+using Pf128x128 = PfShape<128, 128, 2, 4, 4>;
+using Pf64x128 = PfShape<64, 128, 2, 2, 3>;
+using Pf64x64 = PfShape<64, 64, 2, 2, 4>;
+
+// Tile shape of a long chunk's product over projections of N_g features, by
+// the time its tiles take: whole rounds of `slots` workgroups (two per compute
+// unit where the ring is at most half its LDS), then a last round of what is
+// left. A workgroup takes `fixed` us and, per 64-k step, `few` us while a
+// third of the chip or less is busy and `full` us when all of it is (the
+// clock falls and the caches are shared). Measured at K = 4096 (tile: us of a
+// round that is nearly empty / full): 128x256: 44 / 58, 128x128: 28 / 36,
+// 64x128: 24 / 41, 64x64: 23 / 26. So, at 4096 features, 2048 tokens take
+// 128x256 (58 us; 128x128: 70), 1000 tokens 128x128 (37 us; 128x256: 49) and
+// 300 tokens 64x64 (24 us; 128x256: 44). (Larger tiles are no faster where
+// they would fill the chip: a full round of 256x256 takes twice that of
+// 128x256, the clock being what gives.)
+struct PfCost {
+  int m, n, slots;
+  double fixed, few, full, knee;  // knee: the load from which a step takes `full`
+};
+constexpr PfCost kPfCosts[] = {{128, 256, 256, 5.0, 0.62, 0.83, 1.0},
+                               {128, 128, 256, 4.0, 0.37, 0.51, 1.0},
+                               {64, 128, 512, 3.2, 0.32, 0.57, 0.75},
+                               {64, 64, 512, 3.0, 0.31, 0.35, 1.0}};
+
+int prefill_tile(int64_t T, int64_t K, int G, const Proj* p) {
+  int64_t n_total = 0;
+  for (int g = 0; g < G; ++g) n_total += p[g].N;
+  int best = 3;  // every N_g is a multiple of 64
+  double best_us = 0.0;
+  for (int c = best; c >= 0; --c) {
+    const PfCost& f = kPfCosts[c];
+    bool ok = true;  // no tile straddles two projections
+    for (int g = 0; g < G && G > 1; ++g) ok = ok && p[g].N % f.n == 0;
+    if (!ok) continue;
+    const int64_t tiles = ((T + f.m - 1) / f.m) * ((n_total + f.n - 1) / f.n);
+    const int64_t rest = tiles % f.slots;
+    const double steps = static_cast<double>(K / 64);
+    double us = static_cast<double>(tiles / f.slots) * (f.fixed + steps * f.full);
+    if (rest) {
+      const double busy = static_cast<double>(rest) / f.slots;
+      const double load = std::max(0.0, (busy - 0.35) / (f.knee - 0.35));
+      us += f.fixed + steps * (f.few + (f.full - f.few) * std::min(load, 1.0));
+    }
+    if (c == 3 || us < best_us) {
+      best = c;
+      best_us = us;
+    }
+  }
+  return best;
 }
 
-local_status_t launch_shrink_long(const GemmArgs& a, const ShrinkShape& sh, hipStream_t s) {
-  switch (sh.rpad / 16) {
-    case 1: return launch_shrink_rt<1>(a, sh, s);
-    case 2: return launch_shrink_rt<2>(a, sh, s);
-    case 3: return launch_shrink_rt<3>(a, sh, s);
-    case 4: return launch_shrink_rt<4>(a, sh, s);
-    case 5: return launch_shrink_rt<5>(a, sh, s);
-    case 6: return launch_shrink_rt<6>(a, sh, s);
-    case 7: return launch_shrink_rt<7>(a, sh, s);
-    default: return launch_shrink_rt<8>(a, sh, s);
+local_status_t run_prefill(const GemmArgs& a, int tile, hipStream_t s) {
+  switch (tile) {
+    case 0: return launch_prefill<Pf128x256>(a, s);
+    case 1: return launch_prefill<Pf128x128>(a, s);
+    case 2: return launch_prefill<Pf64x128>(a, s);
+    default: return launch_prefill<Pf64x64>(a, s);
   }
 }
 
@@ -1311,17 +1209,6 @@ local_status_t run_partial(const GemmArgs& a, int fn, hipStream_t s) {
 
 size_t align256(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }
 
-// One projection of a (grouped) call.
-struct Proj {
-  const uint16_t* W;
-  int64_t N;
-  const uint16_t* A;
-  const uint16_t* B;
-  const int32_t* ranks;
-  const uint16_t* res;
-  uint16_t* y;
-};
-
 // Sets the group fields of `a` for projections p[0..G).
 void set_groups(GemmArgs& a, int G, const Proj* p) {
   a.G = G;
@@ -1416,11 +1303,6 @@ local_status_t lora_impl(const uint16_t* x, int64_t T, int64_t K, int G, const P
                          const float* scale, void* ws, size_t* ws_bytes, hipStream_t s) {
   const int R = n_adapters > 0 ? n_adapters * r_max : 0;
   const bool decode = T <= kSgMaxTokens;
-  if (G > 1 && !decode) {  // one launch over all projections when no tile straddles two
-    for (int q = 0; q < G; ++q)
-      if (p[q].N % kPfN != 0)
-        return one_by_one(x, T, K, G, p, n_adapters, r_max, adapter_idx, scale, ws, ws_bytes, s);
-  }
   DecodePlan d{};
   if (decode) {
     d = plan_decode(T, K, G, p, n_adapters, r_max);
@@ -1430,15 +1312,17 @@ local_status_t lora_impl(const uint16_t* x, int64_t T, int64_t K, int G, const P
   // Workspace. Decode sizes (T <= kSgMaxTokens): the base partial sums
   // [ksb][T][N] fp32 (N over all projections), then the shrink's partial
   // sums: [ksb][T][G*R] fp32 when the shrink runs inside the base product,
-  // [slices][T][r_max] after the SGMV shrink. Above: the long shrink's
-  // partial sums [G][ks][T][r_max] fp32, then its adapter bitmaps
-  // [ceil(T/64)][4] uint64.
-  const ShrinkShape shs = decode ? ShrinkShape{} : shrink_shape(T, K, r_max, G);
-  const size_t long_p =
-      align256(static_cast<size_t>(G) * shs.ks * T * r_max * sizeof(float));
-  const size_t long_bits = align256(static_cast<size_t>((T + 63) / 64) * 4 * sizeof(uint64_t));
-  const size_t need = decode ? d.part_bytes + d.shrink_bytes
-                             : (n_adapters > 0 ? long_p + long_bits : 0);
+  // [slices][T][r_max] after the SGMV shrink. Above: the shrink's sums
+  // [G][ks][T][r_max] fp32 (at most long_slices K slices), or its U_s and 16
+  // zero bytes; the size (with 32 bytes per 64 tokens, once bitmaps) is the
+  // one that callers have always been told.
+  const int slices = decode ? 0 : long_slices(T, K, r_max, G);
+  const size_t need =
+      decode ? d.part_bytes + d.shrink_bytes
+      : n_adapters > 0
+          ? align256(static_cast<size_t>(G) * slices * T * r_max * sizeof(float)) +
+                align256(static_cast<size_t>((T + 63) / 64) * 32)
+          : 0;
   if (!ws) {
     *ws_bytes = need;
     return LOCAL_OK;
@@ -1484,17 +1368,38 @@ local_status_t lora_impl(const uint16_t* x, int64_t T, int64_t K, int G, const P
     return run_epilogue(m, s);
   }
 
-  // long chunks: the shrink's partial sums [G][ks][T][r_max], then the main
-  // product over the projections' tiles
-  float* P = n_adapters > 0 ? static_cast<float*>(ws) : nullptr;
+  // long chunks: the shrink of every projection, then the main product over
+  // the projections' tiles
   GemmArgs m = g;
   set_groups(m, G, p);
-  m.pout = P;
-  m.tile_present =
-      n_adapters > 0 ? reinterpret_cast<uint64_t*>(static_cast<char*>(ws) + long_p) : nullptr;
-  m.up_ks = shs.ks;
-  if (n_adapters > 0 && (st = launch_shrink_long(m, shs, s)) != LOCAL_OK) return st;
-  return launch_prefill(m, s);
+  if (n_adapters > 0) {
+    // Few 16-token tiles leave compute units idle, and one unit reads no
+    // faster than about 50 GB/s: below 128 of them K is cut into up to 4
+    // slices (300 tokens, K = 4096: shrink 8.6 us in one slice, 4.3 in four;
+    // with the product, which then forms U_s itself, 33.2 and 30.5 us). From
+    // 128 on the slices save less than their sums cost the product (3 x 4096
+    // features, 2048 tokens: 199 us with them, 194 without).
+    const int64_t tiles = (T + 15) / 16 * G;
+    int ks = 1;
+    if (tiles < 128)
+      while (2 * ks <= std::min(slices, 4) && tiles * ks < 256) ks *= 2;
+    m.up_ks = ks;
+    uint16_t* us = ks == 1 ? static_cast<uint16_t*>(ws) : nullptr;
+    uint16_t* zero16 = us ? us + static_cast<int64_t>(G) * T * r_max : nullptr;
+    m.us = us;
+    m.zero16 = zero16;
+    m.pout = static_cast<float*>(ws);
+    ShrinkJob jobs[kMaxGroup];
+    for (int q = 0; q < G; ++q)
+      jobs[q] = us ? ShrinkJob{x, p[q].A, nullptr, K, us + static_cast<int64_t>(q) * T * r_max,
+                               p[q].ranks}
+                   : ShrinkJob{x, p[q].A, m.pout + static_cast<int64_t>(q) * ks * T * r_max, K,
+                               nullptr, nullptr};
+    if ((st = token_shrink(jobs, G, T, n_adapters, r_max, adapter_idx, ks, s, scale, zero16)) !=
+        LOCAL_OK)
+      return st;
+  }
+  return run_prefill(m, prefill_tile(T, K, G, p), s);
 }
 
 // Argument checks shared by the entry points (before any launch).

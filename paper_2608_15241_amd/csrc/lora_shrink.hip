@@ -1,11 +1,11 @@
 // The low-rank product of long token runs, u[t][j] = x[t] . A[a_t][j] with
-// token t's own adapter a_t, over the whole of K in one launch: the shrink of
-// the backward (u = x A^T and dy B, float32), for several (x, A) pairs at
-// once.
+// token t's own adapter a_t: the shrink of long chunks and of the backward
+// (u = x A^T and dy B), for several (x, A) pairs in one launch.
 //
 // Bound by the reads of x and A (2 r flop per byte). A workgroup takes 16
 // tokens and one pair; its waves cut K between them, so that no partial sum
-// leaves the compute unit. Each wave streams its K slice of the 16 token rows
+// leaves the compute unit (with few tiles K is also cut into slices, each its
+// own workgroups and output, which the reader adds in order). Each wave streams its K slice of the 16 token rows
 // and of 16 RT adapter rows through a ring of its own in LDS (64 k a stage,
 // no barrier in the loop) and runs S^T = A X^T on the matrix cores; the
 // waves' tiles are added through LDS in wave order. Direct global-to-LDS
@@ -22,8 +22,6 @@
 namespace localk {
 namespace {
 
-constexpr int kSkWaves = 4;
-constexpr int kSkThreads = kSkWaves * kWave;
 constexpr int kSkTokens = 16;
 
 struct SkArgs {
@@ -31,15 +29,18 @@ struct SkArgs {
   int64_t T;
   int n_ad, r_max;
   const int32_t* idx;
+  int ks;  // K slices (each its own workgroups and output)
+  const float* scale;  // for bf16 outputs
+  uint16_t* zero16;    // 16 bytes or null
 };
 
-template <int RT>
+template <int RT_, int W_, int S_>
 struct SkShape {
-  static constexpr int DMA = 2 + 2 * RT;       // 1 KB loads per stage
-  static constexpr int STAGE = 1024 * DMA;     // x rows, then A rows, 128 bytes each
-  static constexpr int S = RT == 1 ? 4 : 3;    // stages: two workgroups per unit up to RT = 2
-  static constexpr int RED = RT * kSkWaves * kWave * 16;
-  static constexpr int LDS = kSkWaves * S * STAGE + RED;
+  static constexpr int RT = RT_, W = W_, S = S_;  // 16-row tiles of A, waves, stages
+  static constexpr int DMA = 2 + 2 * RT;          // 1 KB loads per stage
+  static constexpr int STAGE = 1024 * DMA;        // x rows, then A rows, 128 bytes each
+  static constexpr int LDS = W * S * STAGE;
+  static_assert(LDS <= 163840 && S >= 2, "ring");
 };
 
 __device__ __forceinline__ void sk_load16(const void* g, void* lds) {
@@ -50,17 +51,20 @@ __device__ __forceinline__ void sk_wait_loads() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory");
 }
 
-template <int RT>
-__global__ __launch_bounds__(kSkThreads) void token_shrink_kernel(SkArgs a) {
-  using SK = SkShape<RT>;
-  constexpr int S = SK::S, D = SK::DMA;
+template <class SK>
+__global__ __launch_bounds__(SK::W * kWave) void token_shrink_kernel(SkArgs a) {
+  constexpr int S = SK::S, D = SK::DMA, RT = SK::RT, W = SK::W;
   extern __shared__ __attribute__((aligned(16))) uint8_t sk_lds[];
   const int tid = threadIdx.x, lane = tid % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int col = lane % 16, kgrp = lane / 16;
   uint8_t* ring = sk_lds + wave * S * SK::STAGE;
-  f32x4* red = reinterpret_cast<f32x4*>(sk_lds + kSkWaves * S * SK::STAGE);  // [RT][waves][64]
-  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kSkTokens;
+  // after the loop a wave's tiles take the start of its ring: [RT][64] f32x4
+  auto red = [&](int w, int rt) {
+    return reinterpret_cast<f32x4*>(sk_lds + w * S * SK::STAGE) + rt * kWave + lane;
+  };
+  const int z = static_cast<int>(blockIdx.x) % a.ks;
+  const int64_t t0 = static_cast<int64_t>(blockIdx.x / a.ks) * kSkTokens;
   const int64_t t = t0 + col;
   const ShrinkJob& jb = a.job[blockIdx.y];
 
@@ -69,7 +73,8 @@ __global__ __launch_bounds__(kSkThreads) void token_shrink_kernel(SkArgs a) {
   // the wave's 64-k steps [s_lo, s_lo + n)
   const int64_t K = jb.K;
   const int steps = static_cast<int>(K / 64);
-  const int s_lo = wave * steps / kSkWaves, n = (wave + 1) * steps / kSkWaves - s_lo;
+  const int zw = z * W + wave, all = a.ks * W;
+  const int s_lo = zw * steps / all, n = (zw + 1) * steps / all - s_lo;
   // lane l of a load writes 16 bytes at block + 16 l: row 8 q + l / 8,
   // position l % 8, which holds chunk (l % 8) ^ (l / 8) of that row
   const int lrow = lane / 8;
@@ -83,97 +88,119 @@ __global__ __launch_bounds__(kSkThreads) void token_shrink_kernel(SkArgs a) {
   const int rd0 = col * 128 + 16 * (kgrp ^ (col % 8));
 
   uint64_t pending = __ballot(my >= 0) & 0xffffull;
+  if (a.zero16 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && tid < 8)
+    a.zero16[tid] = 0;
+  const int j0 = 16 * RT * blockIdx.z;
   bool again = false;
   while (pending) {
     const int ad = __builtin_amdgcn_readlane(my, __ffsll(static_cast<long long>(pending)) - 1);
     pending &= ~__ballot(my == ad);
-    for (int j0 = 0; j0 < a.r_max; j0 += 16 * RT) {
-      const uint16_t* as[2 * RT];
+    if (again) __syncthreads();  // the previous adapter's tiles have been read
+    again = true;
+    const uint16_t* as[2 * RT];
 #pragma unroll
-      for (int q = 0; q < 2 * RT; ++q) {  // rows past r_max repeat its last, never stored
-        const int j = min(j0 + 8 * q + lrow, a.r_max - 1);
-        as[q] = jb.A + (static_cast<int64_t>(ad) * a.r_max + j) * K + loff;
+    for (int q = 0; q < 2 * RT; ++q) {  // rows past r_max repeat its last, never stored
+      const int j = min(j0 + 8 * q + lrow, a.r_max - 1);
+      as[q] = jb.A + (static_cast<int64_t>(ad) * a.r_max + j) * K + loff;
+    }
+    auto issue = [&](int s) {
+      uint8_t* st = ring + (s % S) * SK::STAGE;
+      const int64_t k = 64 * static_cast<int64_t>(s);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) sk_load16(xs[q] + k, st + 1024 * q);
+#pragma unroll
+      for (int q = 0; q < 2 * RT; ++q) sk_load16(as[q] + k, st + 2048 + 1024 * q);
+    };
+    f32x4 acc[2][RT];  // the two halves of the steps apart: shorter sums
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) acc[0][rt] = acc[1][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < min(S - 1, n); ++s) issue(s);
+    for (int s = 0; s < n; ++s) {
+      // stage s % S has landed; stage (s - 1) % S was read before the last
+      // step's products, so the loads of step s + S - 1 may refill it
+      if (s + S - 1 < n) {
+        sk_wait_loads<D * (S - 2)>();
+        issue(s + S - 1);
+      } else {
+        sk_wait_loads<0>();
       }
-      auto issue = [&](int s) {
-        uint8_t* st = ring + (s % S) * SK::STAGE;
-        const int64_t k = 64 * static_cast<int64_t>(s);
+      const uint8_t* st = ring + (s % S) * SK::STAGE;
+      u32x4 xf[2], af[2][RT];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) sk_load16(xs[q] + k, st + 1024 * q);
+      for (int m = 0; m < 2; ++m) {
+        xf[m] = *reinterpret_cast<const u32x4*>(st + (rd0 ^ (64 * m)));
 #pragma unroll
-        for (int q = 0; q < 2 * RT; ++q) sk_load16(as[q] + k, st + 2048 + 1024 * q);
-      };
-      f32x4 acc[2][RT];  // the two halves of the steps apart: shorter sums
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) acc[0][rt] = acc[1][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int s = 0; s < min(S - 1, n); ++s) issue(s);
-      for (int s = 0; s < n; ++s) {
-        // stage s % S has landed; stage (s - 1) % S was read before the last
-        // step's products, so the loads of step s + S - 1 may refill it
-        if (s + S - 1 < n) {
-          sk_wait_loads<D * (S - 2)>();
-          issue(s + S - 1);
-        } else {
-          sk_wait_loads<0>();
-        }
-        const uint8_t* st = ring + (s % S) * SK::STAGE;
-        u32x4 xf[2], af[2][RT];
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-          xf[m] = *reinterpret_cast<const u32x4*>(st + (rd0 ^ (64 * m)));
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt)
-            af[m][rt] = *reinterpret_cast<const u32x4*>(st + 2048 * (1 + rt) + (rd0 ^ (64 * m)));
-        }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt)
-            acc[m][rt] = mfma16x16x32(as_bf16x8(af[m][rt]), as_bf16x8(xf[m]), acc[m][rt]);
+        for (int rt = 0; rt < RT; ++rt)
+          af[m][rt] = *reinterpret_cast<const u32x4*>(st + 2048 * (1 + rt) + (rd0 ^ (64 * m)));
       }
-      if (again) __syncthreads();  // the previous sums have been read
-      again = true;
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) red[(rt * kSkWaves + wave) * kWave + lane] = acc[0][rt] + acc[1][rt];
-      __syncthreads();
-      for (int rt = wave; rt < RT; rt += kSkWaves) {
-        f32x4 v = red[rt * kSkWaves * kWave + lane];
+      for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int w = 1; w < kSkWaves; ++w) v += red[(rt * kSkWaves + w) * kWave + lane];
-        const int j = j0 + 16 * rt + 4 * kgrp;
-        if (my == ad && j < a.r_max) *reinterpret_cast<f32x4*>(jb.u + t * a.r_max + j) = v;
+        for (int rt = 0; rt < RT; ++rt)
+          acc[m][rt] = mfma16x16x32(as_bf16x8(af[m][rt]), as_bf16x8(xf[m]), acc[m][rt]);
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) *red(wave, rt) = acc[0][rt] + acc[1][rt];
+    __syncthreads();
+    for (int rt = wave; rt < RT; rt += W) {
+      f32x4 v = *red(0, rt);
+#pragma unroll
+      for (int w = 1; w < W; ++w) v += *red(w, rt);
+      const int j = j0 + 16 * rt + 4 * kgrp;
+      if (my != ad || j >= a.r_max) continue;
+      if (jb.u) {
+        *reinterpret_cast<f32x4*>(jb.u + (z * a.T + t) * a.r_max + j) = v;
+      } else {
+        const int rk = jb.ranks ? jb.ranks[ad] : a.r_max;
+        const float sc = a.scale[t];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = j + q < rk ? sc * v[q] : 0.f;
+        *reinterpret_cast<u32x2*>(jb.us + t * a.r_max + j) =
+            u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
       }
     }
   }
 }
 
-template <int RT>
+template <class SK>
 local_status_t launch_sk(const SkArgs& a, int n_jobs, hipStream_t s) {
   static bool done = false;
   if (!done) {  // benign race: every caller sets the same value
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(token_shrink_kernel<RT>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, SkShape<RT>::LDS);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(token_shrink_kernel<SK>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, SK::LDS);
     done = true;
   }
-  const dim3 grid(static_cast<unsigned>((a.T + kSkTokens - 1) / kSkTokens),
-                  static_cast<unsigned>(n_jobs));
-  token_shrink_kernel<RT><<<grid, kSkThreads, SkShape<RT>::LDS, s>>>(a);
+  const dim3 grid(static_cast<unsigned>((a.T + kSkTokens - 1) / kSkTokens * a.ks),
+                  static_cast<unsigned>(n_jobs),
+                  static_cast<unsigned>((a.r_max + 16 * SK::RT - 1) / (16 * SK::RT)));
+  token_shrink_kernel<SK><<<grid, SK::W * kWave, SK::LDS, s>>>(a);
   return local_check_launch("lora (token shrink)");
 }
 
 }  // namespace
 
 local_status_t token_shrink(const ShrinkJob* jobs, int n_jobs, int64_t T, int n_ad, int r_max,
-                            const int32_t* idx, hipStream_t s) {
+                            const int32_t* idx, int ks, hipStream_t s, const float* scale,
+                            uint16_t* zero16) {
   SkArgs a{};
   for (int q = 0; q < n_jobs; ++q) a.job[q] = jobs[q];
   a.T = T;
   a.n_ad = n_ad;
   a.r_max = r_max;
   a.idx = idx;
-  if (r_max <= 16) return launch_sk<1>(a, n_jobs, s);
-  if (r_max <= 32) return launch_sk<2>(a, n_jobs, s);
-  return launch_sk<4>(a, n_jobs, s);
+  a.ks = ks;
+  a.scale = scale;
+  a.zero16 = zero16;
+  // Rank rows per workgroup: all of them (token rows read once) when the
+  // tiles alone fill the chip, else half, side by side. Measured (K = 4096):
+  // rank 32, 63 tiles: 10.1 us with 16 rows, 11.7 with 32; rank 64, 94 tiles:
+  // 18.5, 15.4 and 17.4 with 16, 32 and 64; rank 64, 768 tiles: 72.9, 60.1
+  // and 55.7.
+  const bool full = (T + kSkTokens - 1) / kSkTokens * n_jobs * ks >= 256;
+  if (r_max <= 16 || (r_max <= 32 && !full)) return launch_sk<SkShape<1, 8, 2>>(a, n_jobs, s);
+  if (r_max <= 32 || !full) return launch_sk<SkShape<2, 8, 3>>(a, n_jobs, s);
+  return launch_sk<SkShape<4, 8, 2>>(a, n_jobs, s);
 }
 
 }  // namespace localk
