@@ -364,8 +364,9 @@ local_status_t local_paged_attn_decode_checked(
  *  no allocating routine.
  *
  *  Limit: the partials need B * Hq * ceil(max_blocks / P) * (D + 2) * 4
- *  bytes (the size local_paged_attn_decode asks for), P the partition length
- *  in blocks: 32 for tables up to 256 blocks wide, 48 up to 512, 64 beyond.
+ *  bytes, P the partition length in blocks: 32 for tables up to 256 blocks
+ *  wide, 48 up to 512, 64 beyond (calls of few requests take shorter
+ *  partitions, which never need more than 2304 * Hq / Hkv partials).
  *  A call needing more than LOCAL_DECODE_NOALLOC_SCRATCH_BYTES returns
  *  LOCAL_ERR_UNSUPPORTED and launches nothing. (131072 partials at D = 128:
  *  for instance 512 requests x 32 heads with a 256-block table, or 256

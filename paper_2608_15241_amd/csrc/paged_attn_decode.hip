@@ -4,13 +4,15 @@
 //
 // Design (HBM-bound: every valid KV byte is read once, stale blocks are never
 // read):
-//  * Split-KV. A workgroup is one wave and owns a partition of 32 logical
-//    blocks (512 tokens) of one request and one KV head. Partitions are
+//  * Split-KV. A workgroup owns a partition of 16 to 64 logical blocks of one
+//    request and one KV head; it is one wave, or two or four where there are
+//    few partitions (its valid blocks are dealt to the waves, whose results
+//    meet in LDS). Partitions are
 //    counted from the end of the context and their index is the slowest grid
 //    dimension, so full partitions are dispatched first and each request's
 //    partial one (its oldest blocks) last, which shortens the tail when
-//    context lengths vary. A wave reads its 32 table entries and tags first,
-//    keeps the non-stale blocks and walks them
+//    context lengths vary. A wave reads the partition's table entries and tags
+//    first, keeps the non-stale blocks and walks them
 //    in order through a ring of DEPTH register sets, so that DEPTH-1 blocks'
 //    K/V loads are in flight while one block is computed. Block loads are
 //    buffer loads issued unconditionally (a block past the end gets a
@@ -32,6 +34,7 @@
 //  * The new token's K/V are written at position L-1 by the wave that owns
 //    that block, which also substitutes them for the cache slot it reads, so
 //    no other workgroup and no second launch is involved.
+#include <algorithm>
 #include <mutex>
 
 #include "common.hpp"
@@ -39,14 +42,41 @@
 namespace localk {
 namespace {
 
-// Blocks per partition (one wave each), by the width of the block table:
-// 32 up to 256 blocks, 48 up to 512, 64 beyond (at most 64: one bit per lane
-// in the stale masks). Measured: the 32-layer decode with contexts up to 16K
-// tokens (1024-block tables) is 3.2% faster a step with 64 than with 32, the
-// GQA decode with 512-block tables 2% faster with 48, and the MHA decode with
-// 256-block tables fastest with 32 (fewer, longer partitions: less merge
-// traffic and fewer waves; shorter ones: more parallelism per request).
-int part_blocks(int max_blocks) { return max_blocks <= 256 ? 32 : max_blocks <= 512 ? 48 : 64; }
+// Blocks per partition, by the width of the block table: 32 up to 256 blocks,
+// 48 up to 512, 64 beyond (at most 64: one bit per lane in the stale masks).
+// Measured: the 32-layer decode with contexts up to 16K tokens (1024-block
+// tables) is 3.2% faster a step with 64 than with 32, the GQA decode with
+// 512-block tables 2% faster with 48, and the MHA decode with 256-block tables
+// fastest with 32 (fewer, longer partitions: less merge traffic and fewer
+// waves; shorter ones: more parallelism per request).
+//
+// A call with fewer than kFewUnits (KV head, request, partition) units leaves
+// compute units idle or unevenly loaded, and halves the partitions until it
+// has that many, down to 16 blocks and up to kMaxFine partitions a request
+// (whose merge is a serial pass). Measured, 8 KV heads of 4 query heads:
+// 5 requests of up to 15K tokens 55 us with 64 blocks and 36 with 32 (600 and
+// 1200 units); 8 of up to 4000 tokens 31 us with 32 and 21 with 16; one of
+// 16000 tokens (4 waves each) 22 us with 64, 17 with 32, 20 with 16 (62
+// partitions).
+constexpr int kFewUnits = 768;
+constexpr int kMaxFine = 32;
+
+int parts_of_table(int max_blocks, int pb) { return (max_blocks + pb - 1) / pb; }
+
+int part_blocks(int max_blocks, int64_t heads) {  // heads: B * Hkv
+  int pb = max_blocks <= 256 ? 32 : max_blocks <= 512 ? 48 : 64;
+  while (pb > 16 && heads * parts_of_table(max_blocks, pb) < kFewUnits) {
+    const int half = pb == 64 ? 32 : 16;
+    if (parts_of_table(max_blocks, half) > kMaxFine) break;
+    pb = half;
+  }
+  return pb;
+}
+
+// Units that the partials are always sized for, so that a call with fewer
+// requests never needs a larger workspace than one with more: halving (or a
+// step from 48 to 16) starts below kFewUnits, so no fine call has more.
+constexpr int64_t kFineUnits = 3 * kFewUnits;
 constexpr float kNegBig = -1.0e30f;
 
 struct DecodeArgs {
@@ -84,10 +114,16 @@ __device__ __forceinline__ int owned_blocks(int L, int max_blocks) {
   return L <= 0 ? 0 : min((L + kBlockSize - 1) / kBlockSize, max_blocks);
 }
 
-// Position of the k-th (0-based) set bit of m (k < popcount(m)).
-__device__ __forceinline__ int nth_set_bit(uint64_t m, int k) {
-  for (int i = 0; i < k; ++i) m &= m - 1ull;
-  return __ffsll(static_cast<long long>(m)) - 1;
+// Set bits of m below this lane.
+__device__ __forceinline__ int bits_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                   __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+}
+
+// Full partitions of nb blocks (part_blocks is 16, 32, 48 or 64).
+__device__ __forceinline__ int full_parts(int nb, int pb) {
+  const unsigned u = static_cast<unsigned>(nb);
+  return static_cast<int>(pb == 48 ? u / 48u : u >> (pb == 16 ? 4 : pb == 32 ? 5 : 6));
 }
 
 // Requests a wavefront ranks at once: 64 per register, up to this many
@@ -95,67 +131,93 @@ __device__ __forceinline__ int nth_set_bit(uint64_t m, int k) {
 constexpr int kRankChunks = 8;
 
 // The unit of work of dispatch slot k, longest first: every full partition,
-// row by row (partition z of each request that has it, ascending b), then
-// each request's partial partition, longest first (ties: smaller b); an
-// empty context is a partial partition of no block. Returns the request (-1
-// past the last unit) and, in *part, its partition index (a partial one is
-// numbered n_full, as in the merge). Every lane returns the same.
+// request by request (they are equally long), then each request's partial
+// partition, longest first (ties: smaller b); an empty context is a partial
+// partition of no block. Returns the request (-1 past the last unit) and, in
+// *part, its partition index (a partial one is numbered n_full, as in the
+// merge). Every lane returns the same.
+//
+// Every wave of every slot runs this before it knows what to load, so its
+// instructions count (with 128 requests and 1000 units, 30 us of issue slots over
+// the chip when the partial partitions were searched length by length and
+// the k-th set bit by clearing k of them): the full partitions are found by
+// prefix sums over the bits of n_full, the partial ones by a radix selection
+// over the 6 bits of their length, all with ballots.
 __device__ int decode_unit(const DecodeArgs& a, int B, int k, int* part) {
   const int lane = threadIdx.x % kWave;
   const int nc = (B + kWave - 1) / kWave;
-  int nf[kRankChunks], rem[kRankChunks];
-  bool has_partial[kRankChunks];
+  int nf[kRankChunks], rem[kRankChunks], pre[kRankChunks];
+  uint64_t cand[kRankChunks];  // requests with a partial partition
 #pragma unroll
   for (int c = 0; c < kRankChunks; ++c) {
+    if (c >= nc) break;
     const int b = c * kWave + lane;
-    const int nb = b < B ? owned_blocks(a.ctx_lens[b], a.max_blocks) : -1;
-    nf[c] = nb > 0 ? nb / a.pb : 0;
-    rem[c] = nb > 0 ? nb % a.pb : 0;
-    has_partial[c] = nb == 0 || rem[c] > 0;  // nb = -1: no request
+    rem[c] = b < B ? a.ctx_lens[b] : -1;
   }
-  // slots past the last unit leave before any ranking
-  int units = 0;
+  int n_partial = 0;
 #pragma unroll
-  for (int c = 0; c < kRankChunks; ++c) units += nf[c] + (has_partial[c] ? 1 : 0);
+  for (int c = 0; c < kRankChunks; ++c) {
+    if (c >= nc) break;
+    const bool in = c * kWave + lane < B;
+    const int nb = in ? owned_blocks(rem[c], a.max_blocks) : 0;
+    nf[c] = full_parts(nb, a.pb);
+    rem[c] = nb - nf[c] * a.pb;
+    cand[c] = __ballot(in && (nb == 0 || rem[c] > 0));
+    n_partial += __popcll(cand[c]);
+  }
+  // exclusive prefix sums of n_full over the requests, bit by bit
+  int full = 0;
 #pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) units += __shfl_xor(units, off);
-  if (k >= units) return -1;
-  for (int z = 0; z < a.n_parts; ++z) {
-    int cnt = 0;
+  for (int c = 0; c < kRankChunks; ++c) {
+    if (c >= nc) break;
+    pre[c] = full;
+    for (int bit = 0; (1 << bit) <= a.n_parts; ++bit) {
+      const uint64_t m = __ballot((nf[c] >> bit) & 1);
+      pre[c] += bits_below(m) << bit;
+      full += __popcll(m) << bit;
+    }
+  }
+  if (k >= full + n_partial) return -1;
+  if (k < full) {
 #pragma unroll
     for (int c = 0; c < kRankChunks; ++c) {
       if (c >= nc) break;
-      cnt += __popcll(__ballot(nf[c] > z));
-    }
-    if (cnt == 0) break;
-    if (k < cnt) {
-#pragma unroll
-      for (int c = 0; c < kRankChunks; ++c) {
-        if (c >= nc) break;
-        const uint64_t m = __ballot(nf[c] > z);
-        const int n = __popcll(m);
-        if (k < n) {
-          *part = z;
-          return c * kWave + nth_set_bit(m, k);
-        }
-        k -= n;
-      }
-    }
-    k -= cnt;
-  }
-  for (int v = a.pb - 1; v >= 0; --v) {
-#pragma unroll
-    for (int c = 0; c < kRankChunks; ++c) {
-      if (c >= nc) break;
-      const uint64_t m = __ballot(has_partial[c] && rem[c] == v);
-      const int n = __popcll(m);
-      if (k < n) {
-        const int l = nth_set_bit(m, k);
-        *part = __shfl(nf[c], l);
+      const uint64_t m = __ballot(k >= pre[c] && k < pre[c] + nf[c]);
+      if (m) {
+        const int l = __builtin_ctzll(m);
+        *part = k - __builtin_amdgcn_readlane(pre[c], l);
         return c * kWave + l;
       }
-      k -= n;
     }
+  }
+  k -= full;
+  for (int bit = 5; bit >= 0; --bit) {  // (a partial partition has at most 63 blocks)
+    int longer = 0;
+#pragma unroll
+    for (int c = 0; c < kRankChunks; ++c) {
+      if (c >= nc) break;
+      longer += __popcll(cand[c] & __ballot((rem[c] >> bit) & 1));
+    }
+    const bool take = k < longer;
+    if (!take) k -= longer;
+#pragma unroll
+    for (int c = 0; c < kRankChunks; ++c) {
+      if (c >= nc) break;
+      const uint64_t m = __ballot((rem[c] >> bit) & 1);
+      cand[c] &= take ? m : ~m;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < kRankChunks; ++c) {
+    if (c >= nc) break;
+    const int n = __popcll(cand[c]);
+    if (k < n) {
+      const bool mine = (cand[c] >> lane & 1ull) && bits_below(cand[c]) == k;
+      const int l = __builtin_ctzll(__ballot(mine));
+      *part = __builtin_amdgcn_readlane(nf[c], l);
+      return c * kWave + l;
+    }
+    k -= n;
   }
   return -1;
 }
@@ -199,12 +261,21 @@ struct BlockRegs {
   u32x2 v[D / 16];
 };
 
-template <int D, int DEPTH, bool RANKED>
-__global__ __launch_bounds__(kWave) void decode_attn_kernel(DecodeArgs a, int B) {
+// Bytes of LDS a workgroup of W > 1 waves merges its waves' results in: per
+// (wave, column) an unnormalised O row (padded by 16 bytes, so that the columns
+// a wave writes together fall in distinct banks), its maximum and its sum.
+template <int D>
+constexpr int merge_lds_bytes(int W, int group) {
+  return W * group * (D + 4 + 2) * static_cast<int>(sizeof(float));
+}
+
+template <int D, int DEPTH, bool RANKED, int W>
+__global__ __launch_bounds__(kWave* W) void decode_attn_kernel(DecodeArgs a, int B) {
   constexpr int KC = D / 32;  // 32-dim chunks of the QK product
   constexpr int VT = D / 16;  // 16-dim tiles of the PV product
 
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x % kWave;
+  const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int col = lane % 16, kgrp = lane / 16;
   // Partition p covers blocks [nb - P(p+1), nb - Pp) of b (P = a.pb): the full ones
   // counted from the end of the context, then at most one partial one at the
@@ -227,7 +298,7 @@ __global__ __launch_bounds__(kWave) void decode_attn_kernel(DecodeArgs a, int B)
   }
   const int L = a.ctx_lens[b];
   const int nb = owned_blocks(L, a.max_blocks);
-  const int n_full = nb / a.pb, rem = nb % a.pb;
+  const int n_full = full_parts(nb, a.pb), rem = nb - n_full * a.pb;
   if (!RANKED) {
     if (part < a.n_parts) {
       if (part >= n_full && !(nb == 0 && part == 0)) return;
@@ -238,7 +309,7 @@ __global__ __launch_bounds__(kWave) void decode_attn_kernel(DecodeArgs a, int B)
   }
   const int j_end_part = nb - part * a.pb;
   const int j0 = max(0, j_end_part - a.pb);
-  const int n_parts_b = max(1, (nb + a.pb - 1) / a.pb);
+  const int n_parts_b = max(1, n_full + (rem > 0 ? 1 : 0));
   const int rv = a.req_version[b];
   const int32_t* table = a.block_table + static_cast<int64_t>(b) * a.max_blocks;
   const int G = a.group;
@@ -252,8 +323,12 @@ __global__ __launch_bounds__(kWave) void decode_attn_kernel(DecodeArgs a, int B)
     ok = my_phys >= 0 && my_phys < a.num_blocks && a.block_version[my_phys] == rv;
     if (!ok) my_phys = 0;  // an id outside the pool is never dereferenced
   }
-  uint64_t valid_mask = __ballot(ok);
-  if (a.vc_mask && g == 0) {  // the version check of this partition's blocks
+  // The valid blocks are dealt to the waves in turn: the i-th to wave i % W.
+  const uint64_t part_valid = __ballot(ok);
+  uint64_t valid_mask = part_valid;
+  if (W > 1)
+    valid_mask = __ballot(ok && __popcll(part_valid & ((1ull << lane) - 1ull)) % W == wave);
+  if (a.vc_mask && g == 0 && wave == 0) {  // the version check of this partition's blocks
     const bool owned = lane < a.pb && j0 + lane < jend;
     const uint64_t stale = __ballot(owned && !ok);
     int live = ok ? min(kBlockSize, L - kBlockSize * (j0 + lane)) : 0;
@@ -286,7 +361,10 @@ __global__ __launch_bounds__(kWave) void decode_attn_kernel(DecodeArgs a, int B)
   const int j_new = (L - 1) / kBlockSize, s_last = (L - 1) % kBlockSize;
   const bool has_new = a.k_new != nullptr;
   const int64_t kvrow = (static_cast<int64_t>(b) * a.Hkv + g) * D;
-  const bool append = has_new && j_new >= j0 && j_new < jend;
+  bool append = has_new && j_new >= j0 && j_new < jend;
+  if (W > 1 && append)  // by the wave that reads the block (a stale one: wave 0)
+    append = (part_valid >> (j_new - j0) & 1ull) ? (valid_mask >> (j_new - j0) & 1ull) != 0ull
+                                                 : wave == 0;
   const int p_new = append ? table[j_new] : -1;
 
   f32x4 acc[VT];
@@ -301,7 +379,7 @@ __global__ __launch_bounds__(kWave) void decode_attn_kernel(DecodeArgs a, int B)
   for (int c = 0; c < KC; ++c) kn[c] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
   for (int t = 0; t < VT; ++t) vn[t] = 0u;
-  if (has_new && j_new >= j0 && j_new < jend) {
+  if (append) {
 #pragma unroll
     for (int c = 0; c < KC; ++c) kn[c] = ld_global<u32x4>(a.k_new + kvrow + 32 * c + 8 * kgrp);
 #pragma unroll
@@ -415,7 +493,52 @@ __global__ __launch_bounds__(kWave) void decode_attn_kernel(DecodeArgs a, int B)
   // ---- finish: the column's sum over the 4 lane groups, then write
   l_run += __shfl_xor(l_run, 16);
   l_run += __shfl_xor(l_run, 32);
-  if (col < G) {
+  if constexpr (W > 1) {
+    // the waves' results meet in LDS; each thread then finishes 4 dims of a head
+    extern __shared__ __attribute__((aligned(16))) float mg[];
+    constexpr int kRow = D + 4;
+    float* mg_ml = mg + W * G * kRow;
+    if (col < G) {
+      const int row = wave * G + col;
+#pragma unroll
+      for (int t = 0; t < VT; ++t)
+        *reinterpret_cast<f32x4*>(mg + row * kRow + 16 * t + 4 * kgrp) = acc[t];
+      if (kgrp == 0) {
+        mg_ml[2 * row] = m_run;
+        mg_ml[2 * row + 1] = l_run;
+      }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < G * (D / 4); e += kWave * W) {
+      const int hc = e / (D / 4), d = 4 * (e % (D / 4));
+      float M = kNegBig;
+#pragma unroll
+      for (int w = 0; w < W; ++w) M = fmaxf(M, mg_ml[2 * (w * G + hc)]);
+      float den = 0.f;
+      f32x4 num = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < W; ++w) {  // a wave without a block: weight x 0
+        const int row = w * G + hc;
+        const float f = fast_exp2(mg_ml[2 * row] - M);
+        den += mg_ml[2 * row + 1] * f;
+        num += *reinterpret_cast<const f32x4*>(mg + row * kRow + d) * f;
+      }
+      const int64_t bh = static_cast<int64_t>(b) * a.Hq + g * G + hc;
+      if (n_parts_b == 1) {
+        num *= den > 0.f ? 1.f / den : 0.f;
+        *reinterpret_cast<u32x2*>(a.out + bh * D + d) =
+            u32x2{pack_bf16x2(num[0], num[1]), pack_bf16x2(num[2], num[3])};
+        if (d == 0 && a.lse) a.lse[bh] = den > 0.f ? (M + __log2f(den)) * kLn2 : -INFINITY;
+      } else {
+        const int64_t pi = bh * a.n_parts + part;
+        *reinterpret_cast<f32x4*>(a.part_o + pi * D + d) = num;
+        if (d == 0) {
+          a.part_ml[pi * 2] = M;
+          a.part_ml[pi * 2 + 1] = den;
+        }
+      }
+    }
+  } else if (col < G) {
     const int h = g * G + col;
     const int64_t bh = static_cast<int64_t>(b) * a.Hq + h;
     if (n_parts_b == 1) {
@@ -450,7 +573,7 @@ __device__ void decode_version_check(const DecodeArgs& a, int b, int B, int* sh)
   const int tid = threadIdx.x, nt = blockDim.x;
   auto parts_of = [&](int bb) {
     const int nbb = owned_blocks(a.ctx_lens[bb], a.max_blocks);
-    return max(1, (nbb + a.pb - 1) / a.pb);
+    return max(1, full_parts(nbb + a.pb - 1, a.pb));
   };
   int before = 0;
   for (int e = tid; e < b * a.n_parts; e += nt) {
@@ -514,7 +637,7 @@ __global__ __launch_bounds__(D) void decode_merge_kernel(DecodeArgs a, int B) {
   }
   const int L = a.ctx_lens[b];
   const int nb = owned_blocks(L, a.max_blocks);
-  const int np = max(1, (nb + a.pb - 1) / a.pb);
+  const int np = max(1, full_parts(nb + a.pb - 1, a.pb));
   if (np == 1) return;  // written by the main kernel
   // one pass over the partitions, 8 at a time with all their loads in flight;
   // the running sums are rescaled when a batch raises the maximum
@@ -559,6 +682,45 @@ __global__ __launch_bounds__(D) void decode_merge_kernel(DecodeArgs a, int B) {
 #define LOCAL_DECODE_DEPTH 3
 #endif
 
+template <int D, int DEPTH, bool RANKED>
+void launch_attn(const DecodeArgs& a, int B, unsigned grid, int W, hipStream_t s) {
+  const int lds = merge_lds_bytes<D>(W, a.group);
+  if (W == 4)
+    decode_attn_kernel<D, DEPTH, RANKED, 4><<<grid, 4 * kWave, lds, s>>>(a, B);
+  else if (W == 2)
+    decode_attn_kernel<D, DEPTH, RANKED, 2><<<grid, 2 * kWave, lds, s>>>(a, B);
+  else
+    decode_attn_kernel<D, DEPTH, RANKED, 1><<<grid, kWave, 0, s>>>(a, B);
+}
+
+template <int D, int DEPTH>
+void launch_ranked(const DecodeArgs& a, int B, unsigned grid, int W, hipStream_t s) {
+  if (B <= kRankChunks * kWave)
+    launch_attn<D, DEPTH, true>(a, B, grid, W, s);
+  else
+    launch_attn<D, DEPTH, false>(a, B, grid, W, s);
+}
+
+// Waves that share a partition. What a wave does before its first block (three
+// dependent loads) and its in-flight blocks bound a partition, so few units
+// want more waves each, and many units want one (three waves of one unit hold
+// the registers of three units). Measured in us with 1 / 2 / 4 waves, units as
+// counted here (half of them or less run; the table is as wide as the longest
+// context): grouped heads 248 units 31 / 21 / 17; 512 (16-block table rows of
+// 44) 22 / 16 / 13; 1024 38 / 37 / 36, but 26 / 25 / 27 with tables of 19 blocks;
+// 2048 62 / 59 / 58; 4096 112 / 107 / 108; 16384 719 / 715 / 725; with 64-block
+// partitions (2560 units) 148 / 152 / 142. One query head
+// per KV head: 96 units 30 / 19 / 15; 512 31 / 22 / 27; 2816 111 / 107 / 114; 4096
+// 109 / 106 / 124, but 76 / 99 / 156 with tables of 19 blocks; 8192 199 / 202 / 238.
+int waves_of(const DecodeArgs& a, int B) {
+  const int64_t units = static_cast<int64_t>(a.Hkv) * B * a.n_parts;
+  const bool mha = a.group == 1;
+  if (units < (mha ? 257 : kFewUnits)) return 4;
+  if (units < kFewUnits) return 2;
+  const bool pair = units >= 1536 && units <= (mha ? 3072 : 4096);
+  return pair && a.max_blocks >= 64 && a.pb < 64 ? 2 : 1;
+}
+
 template <int D>
 local_status_t launch_decode(const DecodeArgs& a, int B, hipStream_t s) {
   const int64_t wgs = static_cast<int64_t>(a.Hkv) * B * (a.n_parts + 1);
@@ -566,18 +728,11 @@ local_status_t launch_decode(const DecodeArgs& a, int B, hipStream_t s) {
     return local_fail(LOCAL_ERR_UNSUPPORTED, "paged_attn_decode: grid of %lld workgroups",
                       (long long)wgs);
   const unsigned grid = static_cast<unsigned>(wgs);
-  const bool ranked = B <= kRankChunks * kWave;
-  if (a.group == 1) {
-    if (ranked)
-      decode_attn_kernel<D, LOCAL_DECODE_DEPTH_MHA, true><<<grid, kWave, 0, s>>>(a, B);
-    else
-      decode_attn_kernel<D, LOCAL_DECODE_DEPTH_MHA, false><<<grid, kWave, 0, s>>>(a, B);
-  } else {
-    if (ranked)
-      decode_attn_kernel<D, LOCAL_DECODE_DEPTH, true><<<grid, kWave, 0, s>>>(a, B);
-    else
-      decode_attn_kernel<D, LOCAL_DECODE_DEPTH, false><<<grid, kWave, 0, s>>>(a, B);
-  }
+  const int W = waves_of(a, B);
+  if (a.group == 1)
+    launch_ranked<D, LOCAL_DECODE_DEPTH_MHA>(a, B, grid, W, s);
+  else
+    launch_ranked<D, LOCAL_DECODE_DEPTH>(a, B, grid, W, s);
   if (a.n_parts > 1 || a.vc_mask) decode_merge_kernel<D><<<B * a.Hq, D, 0, s>>>(a, B);
   return local_check_launch("paged_attn_decode");
 }
@@ -606,9 +761,10 @@ static local_status_t decode_setup(const uint16_t* q, int32_t B, int32_t Hq, int
                       block_size, D, Hq / Hkv);
   if ((k_new == nullptr) != (v_new == nullptr))
     return local_fail(LOCAL_ERR_NULL, "%s: k_new and v_new must both be set", who);
-  const int pb = part_blocks(max_blocks);
-  const int n_parts = (max_blocks + pb - 1) / pb;
-  *part_elems = static_cast<size_t>(B > 0 ? B : 1) * Hq * n_parts;
+  const int pb = part_blocks(max_blocks, static_cast<int64_t>(B) * Hkv);
+  const int n_parts = parts_of_table(max_blocks, pb);
+  *part_elems = std::max(static_cast<size_t>(B > 0 ? B : 1) * Hq * n_parts,
+                         static_cast<size_t>(kFineUnits) * (Hq / Hkv));
   *need = *part_elems * (D + 2) * sizeof(float);
   a->q = q;
   a->k_new = k_new;
@@ -709,7 +865,8 @@ extern "C" local_status_t local_paged_attn_decode_checked(
   if (a.n_parts > D)
     return local_fail(LOCAL_ERR_UNSUPPORTED, "%s: max_blocks=%d over %d blocks", who,
                       max_blocks, D * a.pb);
-  const size_t masks = static_cast<size_t>(B > 0 ? B : 1) * a.n_parts;
+  const size_t masks = std::max(static_cast<size_t>(B > 0 ? B : 1) * a.n_parts,
+                                static_cast<size_t>(kFineUnits));
   const size_t total =
       align256(need) + align256(masks * sizeof(uint64_t)) + align256(masks * sizeof(int32_t));
   if (!ws) {
