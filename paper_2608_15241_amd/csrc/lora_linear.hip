@@ -187,8 +187,7 @@ __device__ __forceinline__ void lds_load16(const void* g, void* lds) {
 // (128-byte rows, chunk-swizzled as in the long-chunk product), brought in
 // by direct global-to-LDS loads: every load instruction moves 8 whole rows,
 // and a ring of S stages keeps S - 2 steps in flight while one is computed.
-// Each wave owns every fourth output tile, so there is no reduction across
-// waves. Rows past N or T and stacked-A rows past the adapter's rank read
+// Each wave owns whole output tiles, so there is no reduction across waves. Rows past N or T and stacked-A rows past the adapter's rank read
 // clamped rows; their outputs are never stored (rows past the rank are
 // masked by the epilogue). Workgroups start their slice at different steps
 // (by feature tile), so that those running together read different parts
@@ -204,14 +203,21 @@ struct StreamShape {
   static constexpr int DMA = (ROWS / 8 + kStWaves - 1) / kStWaves;  // loads per wave and stage
   static constexpr int STAGE = 8 * DMA * kStWaves * 128;            // bytes, padded
   static constexpr int S = kStLdsMax / STAGE < 8 ? kStLdsMax / STAGE : 8;
-  static constexpr int NT = (FT * FM + kStWaves - 1) / kStWaves;    // tiles per wave
+  // Output tiles of a wave: token tiles j = wave % FM (with 8 of them wave and
+  // wave + 4) x every feature tile, or every second or fourth one where there
+  // are fewer token tiles than waves, so that a step reads each of the wave's
+  // operands from LDS once.
+  static constexpr int NX = FM > kStWaves ? FM / kStWaves : 1;
+  static constexpr int IS = FM > kStWaves ? 1 : kStWaves / FM;      // stride of the feature tiles
+  static constexpr int NI = (FT + IS - 1) / IS;
+  static_assert(FM <= kStWaves ? kStWaves % FM == 0 : FM % kStWaves == 0, "tiles of a wave");
   static_assert(S >= 3 && DMA * (S - 2) < 64, "stream ring");
 };
 
 template <int FN, int FM, int XT>
 __global__ __launch_bounds__(kStThreads) void lora_stream_kernel(GemmArgs a) {
   using SS = StreamShape<FN, FM, XT>;
-  constexpr int FT = SS::FT, S = SS::S, D = SS::DMA, NT = SS::NT;
+  constexpr int FT = SS::FT, S = SS::S, D = SS::DMA, NX = SS::NX, NI = SS::NI, IS = SS::IS;
   extern __shared__ __attribute__((aligned(16))) uint8_t st_lds[];
 
   const int tid = threadIdx.x, lane = tid % kWave;
@@ -255,81 +261,82 @@ __global__ __launch_bounds__(kStThreads) void lora_stream_kernel(GemmArgs a) {
     return static_cast<int64_t>(as) * 64;
   };
 
-  // this wave's tiles (past the last tile: the last tile again, not stored)
-  int woff[NT], xoff[NT];
+  // this wave's tiles (past the last feature tile: the last again, not stored)
+  const int i0 = FM >= kStWaves ? 0 : wave / FM, j0 = FM >= kStWaves ? wave : wave % FM;
+  int woff[NI], xoff[NX];
 #pragma unroll
-  for (int k = 0; k < NT; ++k) {
-    const int tl = min(wave + kStWaves * k, FT * FM - 1);
-    woff[k] = 16 * (tl / FM) * 128;
-    xoff[k] = 16 * (FT + tl % FM) * 128;
-  }
+  for (int i = 0; i < NI; ++i) woff[i] = 16 * min(i0 + IS * i, FT - 1) * 128;
+#pragma unroll
+  for (int j = 0; j < NX; ++j) xoff[j] = 16 * (FT + j0 + kStWaves * j) * 128;
   const int rd0 = col * 128 + 16 * (kgrp ^ (col % 8));  // chunk kgrp of row col
   const int rd1 = rd0 ^ 64;                              // chunk 4 + kgrp
-  f32x4 acc[NT];
+  f32x4 acc[NI][NX];
 #pragma unroll
-  for (int k = 0; k < NT; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NX; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // Step rs: each wave waits for its own loads of stage rs % S (those of the
   // S - 2 later steps may stay in flight); after the barrier every wave's
   // loads of the step are visible and stage (rs - 1) % S is free for the
   // loads of step rs + S - 1.
-#pragma unroll
-  for (int p = 0; p < S - 1; ++p) {
-    const int64_t k = step_k(p);
+  auto issue = [&](int rs, uint8_t* st) {
+    const int64_t k = step_k(rs);
 #pragma unroll
     for (int q = 0; q < D; ++q)
-      lds_load16(src[q] + k, st_lds + p * SS::STAGE + 8 * (wave + kStWaves * q) * 128);
-  }
+      lds_load16(src[q] + k, st + 8 * (wave + kStWaves * q) * 128);
+  };
+#pragma unroll
+  for (int p = 0; p < S - 1; ++p) issue(p, st_lds + p * SS::STAGE);
   for (int rs = 0; rs < nsteps; ++rs) {
     const int cur = rs % S;
     wait_vmcnt<D * (S - 2)>();
     wait_lgkm0_barrier();
-    {
-      const int64_t k = step_k(rs + S - 1);
-      uint8_t* st = st_lds + (cur == 0 ? S - 1 : cur - 1) * SS::STAGE;
-#pragma unroll
-      for (int q = 0; q < D; ++q)
-        lds_load16(src[q] + k, st + 8 * (wave + kStWaves * q) * 128);
-    }
+    issue(rs + S - 1, st_lds + (cur == 0 ? S - 1 : cur - 1) * SS::STAGE);
     const uint8_t* st = st_lds + cur * SS::STAGE;
-    u32x4 wv[2][NT], xv[2][NT];
+    u32x4 wv[2][NI], xv[2][NX];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+#pragma unroll
+      for (int j = 0; j < NX; ++j)
+        xv[m][j] = *reinterpret_cast<const u32x4*>(st + xoff[j] + (m ? rd1 : rd0));
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        wv[m][i] = *reinterpret_cast<const u32x4*>(st + woff[i] + (m ? rd1 : rd0));
+    }
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int k = 0; k < NT; ++k) {
-        wv[m][k] = *reinterpret_cast<const u32x4*>(st + woff[k] + (m ? rd1 : rd0));
-        xv[m][k] = *reinterpret_cast<const u32x4*>(st + xoff[k] + (m ? rd1 : rd0));
-      }
+      for (int i = 0; i < NI; ++i)
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-      for (int k = 0; k < NT; ++k)
-        acc[k] = mfma16x16x32(as_bf16x8(wv[m][k]), as_bf16x8(xv[m][k]), acc[k]);
+        for (int j = 0; j < NX; ++j)
+          acc[i][j] = mfma16x16x32(as_bf16x8(wv[m][i]), as_bf16x8(xv[m][j]), acc[i][j]);
   }
   wait_vmcnt<0>();
 
   // partial sums of the slice: lane holds rows 4 (l/16) .. +4 of tile row i,
   // token column l % 16 of tile j
 #pragma unroll
-  for (int k = 0; k < NT; ++k) {
-    const int tl = wave + kStWaves * k;
-    if (tl >= FT * FM) continue;
-    const int i = tl / FM, j = tl % FM;
-    const int64_t t = t0 + 16 * j + col;
-    if (t >= a.T) continue;
-    if (i >= FN) {  // stacked-A rows: the shrink's partial sums of this slice
-      const int rr = 16 * (i - FN) + 4 * kgrp;
-      const int64_t rows = static_cast<int64_t>(a.G) * a.R;
-      float* dst = a.pout + (static_cast<int64_t>(z) * a.T + t) * rows + x0 + rr;
+  for (int ii = 0; ii < NI; ++ii)
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (rr + q < a.xrows && x0 + rr + q < rows) dst[q] = acc[k][q];
-      continue;
+    for (int jj = 0; jj < NX; ++jj) {
+      const int i = i0 + IS * ii, j = j0 + kStWaves * jj;
+      const int64_t t = t0 + 16 * j + col;
+      if (i >= FT || t >= a.T) continue;
+      if (i >= FN) {  // stacked-A rows: the shrink's partial sums of this slice
+        const int rr = 16 * (i - FN) + 4 * kgrp;
+        const int64_t rows = static_cast<int64_t>(a.G) * a.R;
+        float* dst = a.pout + (static_cast<int64_t>(z) * a.T + t) * rows + x0 + rr;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (rr + q < a.xrows && x0 + rr + q < rows) dst[q] = acc[ii][jj][q];
+        continue;
+      }
+      const int64_t n = n0 + 16 * i + 4 * kgrp;
+      if (n < a.N)
+        *reinterpret_cast<f32x4*>(a.part + (static_cast<int64_t>(z) * a.T + t) * a.N + n) =
+            acc[ii][jj];
     }
-    const int64_t n = n0 + 16 * i + 4 * kgrp;
-    if (n < a.N)
-      *reinterpret_cast<f32x4*>(a.part + (static_cast<int64_t>(z) * a.T + t) * a.N + n) = acc[k];
-  }
 }
 
 // ------------------------------------------------------------- SGMV shrink
@@ -485,16 +492,31 @@ local_status_t run_sgmv_shrink(const GemmArgs& a, hipStream_t s) {
 //   y[t, n] = bf16( sum_z part[z][t][n] + sum_j U_s[t][j] B[a_t][n][j] + res[t][n] )
 // with U_s[t][j] = bf16(s_t * sum_z P[z][t][c]) for j < rank(a_t), both sums
 // in slice order; c = a_t*r_max + j when the shrink ran fused with the base
-// product (sums for every stacked row), c = j after the SGMV shrink. Workgroup: 16 tokens x 64 features; U_s of its tokens is
-// built once in LDS, then each thread finishes 4 consecutive features of one
-// token (16-byte partial loads, an 8-byte store).
+// product (sums for every stacked row), c = j after the SGMV shrink. Workgroup:
+// 16 tokens x 64 features; each thread finishes 4 consecutive features of one
+// token (16-byte partial loads, an 8-byte store), and with few rank columns its
+// share of the delta too, from its own loads of B. With more columns those are
+// the bound (every load instruction touches 64 rows of B, and each token reads
+// its adapter's rows again), and a wave takes 16 features on the matrix cores
+// instead, reading the B rows of each adapter of the tile once, 16 rows by 64
+// bytes an instruction. The tokens of other adapters select their own product,
+// so a value that is not finite stays with its adapter. Measured (whole calls,
+// a thread's own loads / matrix cores): rank 64, 64 tokens x 6144 features over
+// 16 adapters 35.1 / 32.3 us (this kernel 14.8 / 11.8), 256 tokens x 12288 144 /
+// 130; rank 32, 256 tokens x 4096 45.5 / 41.6; rank 16, 32 tokens x 6144 19.7 /
+// 20.5 (the list of adapters comes first).
 constexpr int kEpThreads = 256;
 constexpr int kEpTokens = 16;
 constexpr int kEpFeatures = 64;
 
+constexpr int kEpFewColumns = 16;
+constexpr int kEpBatch = 16;      // B operands in flight per wave
+constexpr int kEpUsRow = 128 + 8;  // bf16 values of an LDS row of U_s (padded: bank spread)
+
+// r_max <= kEpFewColumns, or no adapters.
 template <int KSB>
 __global__ __launch_bounds__(kEpThreads) void lora_epilogue_kernel(GemmArgs a) {
-  __shared__ float us[kEpTokens][128 + 1];
+  __shared__ float us[kEpTokens][kEpFewColumns + 1];
   const int tid = threadIdx.x;
   const int tt = tid / (kEpFeatures / 4), ng = tid % (kEpFeatures / 4);
   const int64_t t0 = static_cast<int64_t>(blockIdx.y) * kEpTokens;
@@ -510,7 +532,7 @@ __global__ __launch_bounds__(kEpThreads) void lora_epilogue_kernel(GemmArgs a) {
 
   // Every load that needs no other load's result is issued first: the base
   // slices, the residual, this token's adapter; then, needing only the
-  // adapter, the first 32 rank columns of its B rows and the shrink slices.
+  // adapter, its B rows and the shrink slices.
   f32x4 pv[KSB];
 #pragma unroll
   for (int z = 0; z < KSB; ++z)
@@ -522,10 +544,11 @@ __global__ __launch_bounds__(kEpThreads) void lora_epilogue_kernel(GemmArgs a) {
   const int my_ad = (lora && live) ? token_adapter(a, t) : -1;
   const uint16_t* brow =
       pick(a.gb, g) + (static_cast<int64_t>(my_ad >= 0 ? my_ad : 0) * Ng + n) * a.r_max;
-  u32x4 bv[4][4];  // [8-column step][feature]
+  constexpr int kSteps = kEpFewColumns / 8;
+  u32x4 bv[kSteps][4];  // [8-column step][feature]
   if (my_ad >= 0) {
 #pragma unroll
-    for (int js = 0; js < 4; ++js)
+    for (int js = 0; js < kSteps; ++js)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         bv[js][i] = 8 * js < a.r_max ? ld_global<u32x4>(brow + i * a.r_max + 8 * js) : zero4;
@@ -568,35 +591,162 @@ __global__ __launch_bounds__(kEpThreads) void lora_epilogue_kernel(GemmArgs a) {
     }
     __syncthreads();
     if (my_ad >= 0) {
-      // delta of 4 features over the rank columns, 32 at a time
+      // delta of 4 features over the rank columns
       const int rk = rank_g(a, g, my_ad);
-      for (int j0 = 0; j0 < rk; j0 += 32) {
-        if (j0 > 0) {
 #pragma unroll
-          for (int js = 0; js < 4; ++js)
+      for (int js = 0; js < kSteps; ++js)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              bv[js][i] = j0 + 8 * js < rk ? ld_global<u32x4>(brow + i * a.r_max + j0 + 8 * js)
-                                           : zero4;
-        }
+        for (int e = 0; e < 8; ++e) {
+          const int j = 8 * js + e;
+          if (j < rk) {  // columns at or past the rank are never used
+            const float u = us[tt][j];
 #pragma unroll
-        for (int js = 0; js < 4; ++js)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int j = j0 + 8 * js + e;
-            if (j < rk) {  // columns at or past the rank are never used
-              const float u = us[tt][j];
-#pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const uint32_t w = bv[js][i][e / 2];
-                acc[i] += u * __uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16));
-              }
+            for (int i = 0; i < 4; ++i) {
+              const uint32_t w = bv[js][i][e / 2];
+              acc[i] += u * __uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16));
             }
           }
-      }
+        }
     }
   }
   if (!live) return;
+  if (res) {
+    acc[0] += __uint_as_float(rv.x << 16);
+    acc[1] += __uint_as_float(rv.x & 0xffff0000u);
+    acc[2] += __uint_as_float(rv.y << 16);
+    acc[3] += __uint_as_float(rv.y & 0xffff0000u);
+  }
+  *reinterpret_cast<u32x2*>(pick(a.gy, g) + t * Ng + n) =
+      u32x2{pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3])};
+}
+
+// r_max > kEpFewColumns.
+template <int KSB>
+__global__ __launch_bounds__(kEpThreads) void lora_epilogue_wide_kernel(GemmArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t us[kEpTokens * kEpUsRow];
+  __shared__ __attribute__((aligned(16))) float delta[kEpTokens * (kEpFeatures + 4)];
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int col = lane % 16, kgrp = lane / 16;
+  const int tt = tid / (kEpFeatures / 4), ng = tid % (kEpFeatures / 4);
+  const int64_t t0 = static_cast<int64_t>(blockIdx.y) * kEpTokens;
+  const int64_t nv0 = static_cast<int64_t>(blockIdx.x) * kEpFeatures;  // virtual row
+  const int64_t t = t0 + tt, nv = nv0 + 4 * ng;
+  const bool live = t < a.T && nv < a.N;
+  const bool lora = a.n_ad > 0;  // uniform
+  const u32x4 zero4 = {0u, 0u, 0u, 0u};
+  // the tile's projection (a 64-row tile lies in one) and its own row index
+  const int g = group_of(a, nv0);
+  const int64_t Ng = gstart_of(a, g + 1) - gstart_of(a, g);
+  const int64_t n = nv - gstart_of(a, g);
+
+  // Every load that needs no other load's result is issued first: the
+  // adapter of token col of the tile, the base slices, the residual.
+  const int my_ad = lora ? token_adapter(a, t0 + col) : -1;
+  f32x4 pv[KSB];
+#pragma unroll
+  for (int z = 0; z < KSB; ++z)
+    pv[z] = live ? ld_global<f32x4>(a.part + (static_cast<int64_t>(z) * a.T + t) * a.N + nv)
+                 : f32x4{0.f, 0.f, 0.f, 0.f};
+  const uint16_t* res = pick(a.gres, g);
+  u32x2 rv = {0u, 0u};
+  if (live && res) rv = ld_global<u32x2>(res + t * Ng + n);
+
+  // ---- delta: for each adapter of the tile's tokens the product of its B
+  // rows (16 of this wave's features) and every token's U_s, of which the
+  // tokens of that adapter keep theirs. Items: (adapter, 32 rank columns).
+  uint64_t pending = __ballot(my_ad >= 0) & 0xffffull;
+  if (pending) {  // uniform over the workgroup (every wave holds the same 16 tokens)
+    const int my_rk = my_ad >= 0 ? rank_g(a, g, my_ad) : 0;
+    // lane i holds item i (at most 16 adapters x 4 steps of rank columns): its
+    // first column and a token of its adapter. One step holds r_max <= 32
+    // columns, whatever the rank: then the B rows need not wait for the ranks.
+    int it_t = 0, it_j = 0, n_items = 0;
+    while (pending) {
+      const int l = __builtin_ctzll(pending);
+      pending &= ~__ballot(my_ad == __builtin_amdgcn_readlane(my_ad, l));
+      if (lane >= n_items) {
+        it_t = l;
+        it_j = 32 * (lane - n_items);
+      }
+      n_items += a.r_max <= 32 ? 1 : (__builtin_amdgcn_readlane(my_rk, l) + 31) / 32;
+    }
+    const uint16_t* brow = pick(a.gb, g) +  // (N_g is a multiple of 64)
+                           (nv0 - gstart_of(a, g) + 16 * wave + col) * a.r_max;
+    const int64_t ad_stride = Ng * a.r_max;
+    u32x4 bv[kEpBatch];
+    auto load_batch = [&](int base) {
+#pragma unroll
+      for (int i = 0; i < kEpBatch; ++i)
+        if (base + i < n_items) {
+          const int j = __builtin_amdgcn_readlane(it_j, base + i) + 8 * kgrp;
+          const int ad =
+              __builtin_amdgcn_readlane(my_ad, __builtin_amdgcn_readlane(it_t, base + i));
+          bv[i] = ld_global<u32x4>(brow + ad * ad_stride + (j < a.r_max ? j : 0));
+        }
+    };
+    load_batch(0);
+
+    // U_s of the tile's tokens, 4 rank rows per item: bf16(s_t * u), u the
+    // sum of the shrink slices in slice order (batches of 8 loads)
+    const int quads = (a.r_max + 31) / 32 * 8;
+    const int64_t slice = a.T * a.p_stride;
+    for (int e = tid; e < kEpTokens * quads; e += kEpThreads) {
+      const int et = e / quads, j = 4 * (e % quads);
+      const int ead = token_adapter(a, t0 + et);
+      f32x4 u = {0.f, 0.f, 0.f, 0.f};
+      if (ead >= 0 && j < a.r_max) {
+        const float sc = a.scale[t0 + et];
+        const int erk = rank_g(a, g, ead);
+        const float* p = a.pout + (t0 + et) * a.p_stride +
+                         (a.p_stacked ? static_cast<int64_t>(g) * a.R + ead * a.r_max
+                                      : static_cast<int64_t>(g) * a.r_max) + j;
+        for (int z0 = 0; z0 < a.up_ks; z0 += 8) {
+          f32x4 sv[8];
+#pragma unroll
+          for (int zz = 0; zz < 8; ++zz)
+            sv[zz] = z0 + zz < a.up_ks ? ld_global<f32x4>(p + (z0 + zz) * slice)
+                                       : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int zz = 0; zz < 8; ++zz) u += sv[zz];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)  // rows at or past the rank are never written
+          u[q] = j + q < erk ? sc * u[q] : 0.f;
+      }
+      *reinterpret_cast<u32x2*>(us + et * kEpUsRow + j) =
+          u32x2{pack_bf16x2(u[0], u[1]), pack_bf16x2(u[2], u[3])};
+    }
+    __syncthreads();
+
+    f32x4 mine = {0.f, 0.f, 0.f, 0.f}, prod = {0.f, 0.f, 0.f, 0.f};
+    for (int base = 0; base < n_items; base += kEpBatch) {
+      if (base) load_batch(base);
+#pragma unroll
+      for (int i = 0; i < kEpBatch; ++i)
+        if (base + i < n_items) {
+          const int at = __builtin_amdgcn_readlane(it_t, base + i);
+          const int j0 = __builtin_amdgcn_readlane(it_j, base + i);
+          const int ad = __builtin_amdgcn_readlane(my_ad, at);
+          const int rk = __builtin_amdgcn_readlane(my_rk, at);
+          const u32x4 b = keep_first8(bv[i], rk - j0 - 8 * kgrp);
+          const u32x4 u = *reinterpret_cast<const u32x4*>(us + col * kEpUsRow + j0 + 8 * kgrp);
+          if (j0 == 0) prod = f32x4{0.f, 0.f, 0.f, 0.f};
+          prod = mfma16x16x32(as_bf16x8(b), as_bf16x8(u), prod);
+          // the tokens of the adapter (after its last columns: the whole sum)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) mine[q] = my_ad == ad ? prod[q] : mine[q];
+        }
+    }
+    *reinterpret_cast<f32x4*>(delta + col * (kEpFeatures + 4) + 16 * wave + 4 * kgrp) = mine;
+  }
+  const bool any = lora && __ballot(my_ad >= 0) != 0ull;
+  if (any) __syncthreads();
+  if (!live) return;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int z = 0; z < KSB; ++z) acc += pv[z];
+  if (any) acc += *reinterpret_cast<const f32x4*>(delta + tt * (kEpFeatures + 4) + 4 * ng);
   if (res) {
     acc[0] += __uint_as_float(rv.x << 16);
     acc[1] += __uint_as_float(rv.x & 0xffff0000u);
@@ -611,7 +761,10 @@ template <int KSB>
 local_status_t launch_epilogue(const GemmArgs& a, hipStream_t s) {
   dim3 grid(static_cast<unsigned>((a.N + kEpFeatures - 1) / kEpFeatures),
             static_cast<unsigned>((a.T + kEpTokens - 1) / kEpTokens));
-  lora_epilogue_kernel<KSB><<<grid, kEpThreads, 0, s>>>(a);
+  if (a.n_ad > 0 && a.r_max > kEpFewColumns)
+    lora_epilogue_wide_kernel<KSB><<<grid, kEpThreads, 0, s>>>(a);
+  else
+    lora_epilogue_kernel<KSB><<<grid, kEpThreads, 0, s>>>(a);
   return local_check_launch("lora_linear (epilogue)");
 }
 
