@@ -63,6 +63,7 @@ __device__ __forceinline__ float max3f(float a, float b, float c) {
 #endif
 constexpr int kPaSplitBlocks = LOCAL_PA_SPLIT_BLOCKS;
 constexpr int kPaMaxSplit = LOCAL_PA_MAX_SPLIT;
+constexpr int kPaSlots = 512;  // workgroups that run at once: two per compute unit
 
 struct PrefillArgs {
   const uint16_t* q;
@@ -283,9 +284,23 @@ __device__ __forceinline__ int tile_blocks(int P, int n_b, int t, int max_blocks
   return lim < 0 ? 0 : min(lim / kBlockSize + 1, max_blocks);
 }
 
-// Key ranges a tile of nbl blocks is split into.
-__device__ __forceinline__ int tile_splits(int nbl) {
-  return nbl <= kPaSplitBlocks ? 1 : min(kPaMaxSplit, (nbl + kPaSplitBlocks - 1) / kPaSplitBlocks);
+// Key ranges a tile of nbl blocks is split into, `limit` blocks each at most
+// (kPaMaxSplit ranges at most): without a division, one thread counts many tiles.
+__device__ __forceinline__ int tile_splits(int nbl, int limit) {
+  int ns = 1;
+#pragma unroll
+  for (int i = 1; i < kPaMaxSplit; ++i) ns += nbl > i * limit ? 1 : 0;
+  return ns;
+}
+
+// The limit of a call whose tiles see `blocks` blocks in all, over its heads.
+// From 24 blocks for each workgroup that the chip holds (two per compute unit)
+// kPaSplitBlocks: the longest units start first, and partial results cost
+// traffic. Below, the chip is not full and the longest unit sets the end, so the
+// ranges go down to that mean load, at least 16 blocks.
+__device__ __forceinline__ int split_limit(unsigned long long blocks) {
+  const unsigned long long mean = blocks / kPaSlots;
+  return mean >= 24 ? kPaSplitBlocks : max(static_cast<int>(mean), 16);
 }
 
 // Partial-result slot of (tile t of request b with rows from r0, head h,
@@ -300,7 +315,9 @@ __device__ __forceinline__ int64_t part_slot(int r0, int b, int t, int h, int Hq
 // takes the classes longest first.
 constexpr int kPaClasses = 8;
 __device__ __forceinline__ int tile_class(int nbl, int ns) {
-  return min((nbl / ns) >> 3, kPaClasses - 1);
+  static_assert(kPaMaxSplit == 4, "divisions by constants");
+  const int mean = ns == 1 ? nbl : ns == 2 ? nbl / 2 : ns == 3 ? nbl / 3 : nbl / 4;
+  return min(mean >> 3, kPaClasses - 1);
 }
 
 // The unit schedule, written once per call by one workgroup of
@@ -316,6 +333,7 @@ __device__ void plan_units(const PrefillArgs& a) {
   __shared__ int scan[kPaClasses][kPlanThreads];
   __shared__ int totals[kPaClasses];
   __shared__ int n_split_tiles;
+  __shared__ unsigned long long all_blocks;
   const int tid = threadIdx.x;
   // request bb's first row, rows and prefix (false: no rows, or a bad range)
   auto rows = [&](int bb, int* r0, int* n, int* P) {
@@ -326,17 +344,32 @@ __device__ void plan_units(const PrefillArgs& a) {
     *P = a.ctx_lens[bb] - *n;
     return true;
   };
+  int limit = 0;
   auto count = [&](int P, int n, int (&cnt)[kPaClasses]) {
     for (int t = 0; t * kPaRows < n; ++t) {
-      const int nbl = tile_blocks(P, n, t, a.max_blocks), ns = tile_splits(nbl);
+      const int nbl = tile_blocks(P, n, t, a.max_blocks), ns = tile_splits(nbl, limit);
       const int c = tile_class(nbl, ns);
 #pragma unroll
       for (int cc = 0; cc < kPaClasses; ++cc) cnt[cc] += c == cc ? ns : 0;
     }
   };
   if (tid < kPaClasses) totals[tid] = 0;
-  if (tid == 0) n_split_tiles = 0;
+  if (tid == 0) {
+    n_split_tiles = 0;
+    all_blocks = 0ull;
+  }
   __syncthreads();
+  for (int bb = tid; bb < a.B; bb += kPlanThreads) {
+    int r0, n, P;
+    if (!rows(bb, &r0, &n, &P)) continue;
+    // the mean of the first and the last tile for each of them
+    const int last = (n - 1) / kPaRows;
+    const unsigned long long ends =
+        tile_blocks(P, n, 0, a.max_blocks) + tile_blocks(P, n, last, a.max_blocks);
+    atomicAdd(&all_blocks, ends * (last + 1) / 2);
+  }
+  __syncthreads();
+  limit = split_limit(all_blocks * a.Hq);
   for (int bb = tid; bb < a.B; bb += kPlanThreads) {
     int r0, n, P, cnt[kPaClasses];
 #pragma unroll
@@ -384,7 +417,7 @@ __device__ void plan_units(const PrefillArgs& a) {
     for (int c = 0; c < kPaClasses; ++c) pos[c] = first[c] + scan[c][tid] - cnt[c];
     if (ok) {
       for (int t = (n - 1) / kPaRows; t >= 0; --t) {
-        const int nbl = tile_blocks(P, n, t, a.max_blocks), ns = tile_splits(nbl);
+        const int nbl = tile_blocks(P, n, t, a.max_blocks), ns = tile_splits(nbl, limit);
         const int c = tile_class(nbl, ns);
         int e = 0;
 #pragma unroll
