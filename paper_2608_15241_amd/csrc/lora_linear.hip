@@ -1279,14 +1279,19 @@ local_status_t launch_stream(GemmArgs a, hipStream_t s) {
 
 // Decode sizes (T <= 256): base partial sums over K slices. Wider feature
 // tiles cut the re-reads of x (every workgroup of a slice reads the slice of
-// x for all its tokens); the shape is the widest tile (of 4, 3 or 2 MFMA
-// tiles; 2 above 64 tokens) and K split that bring the grid closest to
-// LOCAL_P_TARGET_WG workgroups from below.
+// x for all its tokens); the shape is the widest tile (of 6, 4, 3 or 2 MFMA
+// tiles; 6 up to 32 tokens and above 128) and K split that bring the grid closest
+// to LOCAL_P_TARGET_WG workgroups from below. Above 64 tokens the re-reads of x
+// bound the product (2 tiles: 16 KB of x a step for 4 KB of W) and the partial sums
+// of more than 2 slices cost more than they bring, except with the smallest tile.
+// Measured, whole calls with 2 / 3 / 4 / 6 tiles: 128 tokens x 6144 x 4096 35.4 / 28.9
+// / 29.1 / 28.8 us, x 12288 (rank 64) 86 / 65 / 66 / 68; 256 tokens x 6144 67 / 48 / 49
+// / 44, x 12288 132 / 132 / 126 / 103; 128 tokens x 1536 x 1024 with 4 slices 14.7 / 15.9.
 #ifndef LOCAL_P_TARGET_WG
 #define LOCAL_P_TARGET_WG 256  // aim: about one workgroup per compute unit
 #endif
 #ifndef LOCAL_P_WIDE
-#define LOCAL_P_WIDE 6  // widest feature tile (MFMA tiles) up to 32 tokens; 0 = none
+#define LOCAL_P_WIDE 6  // widest feature tile (MFMA tiles); 0 = none
 #endif
 
 struct PartialShape {
@@ -1299,13 +1304,14 @@ int token_tiles(int64_t T) { return T <= 16 ? 1 : T <= 32 ? 2 : T <= 64 ? 4 : 8;
 PartialShape partial_shape(int64_t T, int64_t N, int64_t K, bool allow_wide) {
   const int64_t fm = token_tiles(T);
   const int64_t ttiles = (T + 16 * fm - 1) / (16 * fm);
-  PartialShape best{T <= 64 ? 4 : 2, 1};
+  PartialShape best{4, 1};
   int64_t best_wg = -1;
   const int fns[4] = {LOCAL_P_WIDE, 4, 3, 2};
   for (int fn : fns) {
-    if (fn == 0 || (T > 64 && fn != 2) || (fn > 4 && (T > 32 || !allow_wide))) continue;
+    if (fn == 0 || (fn > 4 && ((T > 32 && T <= 128) || !allow_wide))) continue;
     const int64_t tiles = (N + 16 * fn - 1) / (16 * fn) * ttiles;
-    for (int ks = 1; ks <= 8 && ks <= K / 64; ks *= 2) {
+    const int most = T > 64 && fn > 2 ? 2 : 8;
+    for (int ks = 1; ks <= most && ks <= K / 64; ks *= 2) {
       const int64_t wg = tiles * ks;
       if (wg <= LOCAL_P_TARGET_WG && wg > best_wg) {
         best = {fn, ks};
@@ -1324,9 +1330,10 @@ local_status_t run_partial_fn(const GemmArgs& a, hipStream_t s) {
   if constexpr (FN <= 4) {
     if (a.T <= 32) return launch_stream<FN, 2, XT>(a, s);
     if (a.T <= 64) return launch_stream<FN, 4, XT>(a, s);
-    if constexpr (FN == 2 && XT <= 2) return launch_stream<2, 8, XT>(a, s);
+    return launch_stream<FN, 8, XT>(a, s);
   } else if constexpr (XT <= 2) {
     if (a.T <= 32) return launch_stream<FN, 2, XT>(a, s);
+    if (a.T > 64) return launch_stream<FN, 8, XT>(a, s);
   }
   return local_fail(LOCAL_ERR_UNSUPPORTED, "lora_linear: tile of %d features, %d extra row tiles, "
                     "%lld tokens", 16 * FN, XT, static_cast<long long>(a.T));
@@ -1344,19 +1351,18 @@ local_status_t run_partial_xt(const GemmArgs& a, int fn, hipStream_t s) {
 
 // Stacked-A rows each feature-tile workgroup takes with the base product
 // (the shrink fused into it), or 0 when that would take more than 4 extra
-// row tiles (2 above 64 tokens, where the accumulators of more would not fit
-// in registers); then the SGMV shrink runs as its own kernel.
-int partial_xrows(int64_t T, int64_t ftiles, int64_t rows) {
+// row tiles; then the SGMV shrink runs as its own kernel.
+int partial_xrows(int64_t ftiles, int64_t rows) {
   if (rows == 0) return 0;
   const int64_t per = (rows + ftiles - 1) / ftiles;
-  return per <= (T <= 64 ? 64 : 32) ? static_cast<int>(per) : 0;
+  return per <= 64 ? static_cast<int>(per) : 0;
 }
 
 local_status_t run_partial(const GemmArgs& a, int fn, hipStream_t s) {
   if (a.xrows == 0) return run_partial_xt<0>(a, fn, s);
   if (a.xrows <= 16) return run_partial_xt<1>(a, fn, s);
   if (a.xrows <= 32) return run_partial_xt<2>(a, fn, s);
-  if (a.T <= 64) return run_partial_xt<4>(a, fn, s);
+  if (a.xrows <= 64) return run_partial_xt<4>(a, fn, s);
   return local_fail(LOCAL_ERR_UNSUPPORTED, "lora_linear: %d stacked rows per tile", a.xrows);
 }
 
@@ -1398,11 +1404,12 @@ DecodePlan plan_decode(int64_t T, int64_t K, int G, const Proj* p, int n_ad, int
   const int64_t R = n_ad > 0 ? static_cast<int64_t>(n_ad) * r_max : 0;
   d.shape = partial_shape(T, n_total, K, true);
   int64_t ftiles = (n_total + 16 * d.shape.fn - 1) / (16 * d.shape.fn);
-  d.xrows = partial_xrows(T, ftiles, G * R);
-  if (d.shape.fn > 4 && d.xrows > 32) {  // the wide tile takes at most 2 extra row tiles
+  d.xrows = partial_xrows(ftiles, G * R);
+  // the wide tile takes at most 2 extra row tiles
+  if (d.shape.fn > 4 && (d.xrows > 32 || (T > 64 && R > 0 && d.xrows == 0))) {
     d.shape = partial_shape(T, n_total, K, false);
     ftiles = (n_total + 16 * d.shape.fn - 1) / (16 * d.shape.fn);
-    d.xrows = partial_xrows(T, ftiles, G * R);
+    d.xrows = partial_xrows(ftiles, G * R);
   }
   // (Measured at 64 tokens over 16 adapters padded from ranks 8..64 to 64:
   // taking the shrink out of the base product saves 6.8 us of streaming
@@ -1470,8 +1477,13 @@ local_status_t lora_impl(const uint16_t* x, int64_t T, int64_t K, int G, const P
   // zero bytes; the size (with 32 bytes per 64 tokens, once bitmaps) is the
   // one that callers have always been told.
   const int slices = decode ? 0 : long_slices(T, K, r_max, G);
+  size_t decode_need = d.part_bytes + d.shrink_bytes;
+  if (decode && T > 128) {  // never less than 128 tokens, whose plan differs, take
+    const DecodePlan h = plan_decode(128, K, G, p, n_adapters, r_max);
+    decode_need = std::max(decode_need, h.part_bytes + h.shrink_bytes);
+  }
   const size_t need =
-      decode ? d.part_bytes + d.shrink_bytes
+      decode ? decode_need
       : n_adapters > 0
           ? align256(static_cast<size_t>(G) * slices * T * r_max * sizeof(float)) +
                 align256(static_cast<size_t>((T + 63) / 64) * 32)

@@ -27,6 +27,12 @@ CASES = [
     (65, 64, 576, 70, 128, [128] * 70),                     # 64 steps in a tile
     (129, 128, 64, 12, 16, None),
     (256, 512, 256, 256, 8, None),
+    # more than 64 tokens: tiles of 3, 6, 6 and 4 x 16 features, 1 to 4 extra row tiles
+    (100, 128, 6144, 5, 16, None),
+    (129, 128, 12288, 3, 16, None),
+    (200, 192, 6144, 2, 8, [8, 5]),
+    (256, 64, 8192, 40, 64, None),
+    (70, 128, 6144, 64, 96, None),
 ]
 
 
