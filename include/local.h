@@ -304,6 +304,14 @@ local_status_t local_lora_grad_input(
  *  block_size == 16. The appended slots of different requests must be
  *  distinct physical slots, and no other request of the same call may read
  *  them (a request's newest slot belongs to that request alone).
+ *
+ *  Workspace: split-KV partials, (D + 2) floats for each (request, query head,
+ *  partition). The size asked for has room for the short partitions that calls
+ *  of few requests run fastest with. Any workspace of at least
+ *  max(B, 1) * Hq * ceil(max_blocks / P) * (D + 2) * 4 bytes is accepted, P the
+ *  longest partition in blocks: 32 for tables up to 256 blocks wide, 48 up to
+ *  512, 64 beyond. With less than the size asked for the call takes
+ *  partitions of P blocks (results may then differ in the last bits).
  */
 local_status_t local_paged_attn_decode(
     const uint16_t* q, int32_t B, int32_t Hq, int32_t Hkv, int32_t D,
@@ -335,7 +343,11 @@ local_status_t local_paged_attn_decode(
  *  Sizes and errors as local_paged_attn_decode, and LOCAL_ERR_SHAPE for
  *  cap < 0, LOCAL_ERR_NULL for a NULL n_stale (or valid_tokens with B > 0,
  *  or stale_pairs with cap > 0), LOCAL_ERR_UNSUPPORTED for a table wider
- *  than 32 * D blocks. B = 0 writes *n_stale = 0 and nothing else.
+ *  than 64 * D blocks. B = 0 writes *n_stale = 0 and nothing else.
+ *
+ *  Workspace: as local_paged_attn_decode (also the smallest one accepted),
+ *  then 8 and then 4 bytes for each (request, partition), max(B, 1) requests;
+ *  each of the three parts is rounded up to 256 bytes.
  */
 local_status_t local_paged_attn_decode_checked(
     const uint16_t* q, int32_t B, int32_t Hq, int32_t Hkv, int32_t D,
@@ -356,17 +368,17 @@ local_status_t local_paged_attn_decode_checked(
  * capture that must not call hipMalloc, tight serving loops, harnesses that
  * forbid allocation. The caller still passes every input and output.
  *
- *  Same arguments, computation, results (bit for bit) and errors as
- *  local_paged_attn_decode, without ws / ws_bytes. The split-KV partials go
+ *  Same arguments, computation, results (bit for bit, given the workspace that
+ *  it asks for) and errors as local_paged_attn_decode, without ws / ws_bytes.
+ *  The split-KV partials go
  *  to a scratch array of LOCAL_DECODE_NOALLOC_SCRATCH_BYTES that the library
  *  holds in device memory, one copy per GPU it runs on, from the first call
  *  on that GPU until the process ends. The call allocates nothing and calls
  *  no allocating routine.
  *
  *  Limit: the partials need B * Hq * ceil(max_blocks / P) * (D + 2) * 4
- *  bytes, P the partition length in blocks: 32 for tables up to 256 blocks
- *  wide, 48 up to 512, 64 beyond (calls of few requests take shorter
- *  partitions, which never need more than 2304 * Hq / Hkv partials).
+ *  bytes, P the longest partition as above (the shorter ones of calls of few
+ *  requests never need more than 2304 * Hq / Hkv partials, within the scratch).
  *  A call needing more than LOCAL_DECODE_NOALLOC_SCRATCH_BYTES returns
  *  LOCAL_ERR_UNSUPPORTED and launches nothing. (131072 partials at D = 128:
  *  for instance 512 requests x 32 heads with a 256-block table, or 256

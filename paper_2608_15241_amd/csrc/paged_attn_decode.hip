@@ -63,8 +63,12 @@ constexpr int kMaxFine = 32;
 
 int parts_of_table(int max_blocks, int pb) { return (max_blocks + pb - 1) / pb; }
 
+int longest_part_blocks(int max_blocks) {
+  return max_blocks <= 256 ? 32 : max_blocks <= 512 ? 48 : 64;
+}
+
 int part_blocks(int max_blocks, int64_t heads) {  // heads: B * Hkv
-  int pb = max_blocks <= 256 ? 32 : max_blocks <= 512 ? 48 : 64;
+  int pb = longest_part_blocks(max_blocks);
   while (pb > 16 && heads * parts_of_table(max_blocks, pb) < kFewUnits) {
     const int half = pb == 64 ? 32 : 16;
     if (parts_of_table(max_blocks, half) > kMaxFine) break;
@@ -73,8 +77,8 @@ int part_blocks(int max_blocks, int64_t heads) {  // heads: B * Hkv
   return pb;
 }
 
-// Units that the partials are always sized for, so that a call with fewer
-// requests never needs a larger workspace than one with more: halving (or a
+// Units that the partials are sized for at least, so that a call with fewer
+// requests never asks for a larger workspace than one with more: halving (or a
 // step from 48 to 16) starts below kFewUnits, so no fine call has more.
 constexpr int64_t kFineUnits = 3 * kFewUnits;
 constexpr float kNegBig = -1.0e30f;
@@ -742,8 +746,33 @@ local_status_t launch_decode(const DecodeArgs& a, int B, hipStream_t s) {
 
 using namespace localk;
 
-// Host-side validation shared by both entry points: fills *a (without the
-// partials' pointers) and *need, the bytes of split-KV partials of the call.
+// Split-KV partials of a call: the partition length (a->pb, a->n_parts) and what
+// the partials take.
+struct DecodeParts {
+  size_t elems, bytes;  // (request, query head, partition) triples; their bytes
+  size_t units;         // (request, partition) pairs of the version masks
+};
+
+// fine: the partitions that the call's size asks for, with room for any call of
+// fewer requests; else the longest ones of its table and exactly their partials,
+// for a workspace that has no room for more.
+static DecodeParts decode_parts(DecodeArgs& a, int B, int D, bool fine) {
+  a.pb = fine ? part_blocks(a.max_blocks, static_cast<int64_t>(B) * a.Hkv)
+              : longest_part_blocks(a.max_blocks);
+  a.n_parts = parts_of_table(a.max_blocks, a.pb);
+  DecodeParts p;
+  p.units = static_cast<size_t>(B > 0 ? B : 1) * a.n_parts;
+  p.elems = p.units * a.Hq;
+  if (fine) {
+    p.units = std::max(p.units, static_cast<size_t>(kFineUnits));
+    p.elems = std::max(p.elems, static_cast<size_t>(kFineUnits) * a.group);
+  }
+  p.bytes = p.elems * (D + 2) * sizeof(float);
+  return p;
+}
+
+// Host-side validation shared by the entry points: fills *a (without the
+// partials' pointers) and *part, the split-KV partials of the call.
 static local_status_t decode_setup(const uint16_t* q, int32_t B, int32_t Hq, int32_t Hkv,
                                    int32_t D, const uint16_t* k_new, const uint16_t* v_new,
                                    uint16_t* k_cache, uint16_t* v_cache, int64_t num_blocks,
@@ -751,7 +780,7 @@ static local_status_t decode_setup(const uint16_t* q, int32_t B, int32_t Hq, int
                                    int32_t max_blocks, const int32_t* ctx_lens,
                                    const int32_t* block_version, const int32_t* req_version,
                                    float sm_scale, uint16_t* out, float* lse, const char* who,
-                                   DecodeArgs* a, size_t* part_elems, size_t* need) {
+                                   DecodeArgs* a, DecodeParts* part) {
   if (B < 0 || Hq <= 0 || Hkv <= 0 || max_blocks < 1 || num_blocks < 1 || Hq % Hkv != 0)
     return local_fail(LOCAL_ERR_SHAPE, "%s: B=%d Hq=%d Hkv=%d max_blocks=%d num_blocks=%lld",
                       who, B, Hq, Hkv, max_blocks, (long long)num_blocks);
@@ -761,11 +790,6 @@ static local_status_t decode_setup(const uint16_t* q, int32_t B, int32_t Hq, int
                       block_size, D, Hq / Hkv);
   if ((k_new == nullptr) != (v_new == nullptr))
     return local_fail(LOCAL_ERR_NULL, "%s: k_new and v_new must both be set", who);
-  const int pb = part_blocks(max_blocks, static_cast<int64_t>(B) * Hkv);
-  const int n_parts = parts_of_table(max_blocks, pb);
-  *part_elems = std::max(static_cast<size_t>(B > 0 ? B : 1) * Hq * n_parts,
-                         static_cast<size_t>(kFineUnits) * (Hq / Hkv));
-  *need = *part_elems * (D + 2) * sizeof(float);
   a->q = q;
   a->k_new = k_new;
   a->v_new = v_new;
@@ -790,9 +814,8 @@ static local_status_t decode_setup(const uint16_t* q, int32_t B, int32_t Hq, int
   a->group = Hq / Hkv;
   a->num_blocks = num_blocks;
   a->max_blocks = max_blocks;
-  a->n_parts = n_parts;
-  a->pb = pb;
   a->scale_log2 = sm_scale * kLog2e;
+  *part = decode_parts(*a, B, D, true);
   return LOCAL_OK;
 }
 
@@ -821,21 +844,22 @@ extern "C" local_status_t local_paged_attn_decode(
   const char* who = "paged_attn_decode";
   if (!ws_bytes) return local_fail(LOCAL_ERR_WORKSPACE, "%s: ws_bytes is NULL", who);
   DecodeArgs a;
-  size_t part_elems = 0, need = 0;
+  DecodeParts part;
   local_status_t st = decode_setup(q, B, Hq, Hkv, D, k_new, v_new, k_cache, v_cache,
                                    num_blocks, block_size, block_table, max_blocks, ctx_lens,
                                    block_version, req_version, sm_scale, out, lse, who, &a,
-                                   &part_elems, &need);
+                                   &part);
   if (st != LOCAL_OK) return st;
   if (!ws) {
-    *ws_bytes = need;
+    *ws_bytes = part.bytes;
     return LOCAL_OK;
   }
-  if (*ws_bytes < need)
-    return local_fail(LOCAL_ERR_WORKSPACE, "%s: workspace %zu < %zu", who, *ws_bytes, need);
+  if (*ws_bytes < part.bytes) part = decode_parts(a, B, D, false);
+  if (*ws_bytes < part.bytes)
+    return local_fail(LOCAL_ERR_WORKSPACE, "%s: workspace %zu < %zu", who, *ws_bytes, part.bytes);
   if (B == 0) return LOCAL_OK;
   if ((st = decode_pointers_ok(a, who)) != LOCAL_OK) return st;
-  return decode_launch(a, B, D, ws, part_elems, stream);
+  return decode_launch(a, B, D, ws, part.elems, stream);
 }
 
 // ---------------------------------------------------------------- checked
@@ -855,26 +879,27 @@ extern "C" local_status_t local_paged_attn_decode_checked(
   const char* who = "paged_attn_decode_checked";
   if (!ws_bytes) return local_fail(LOCAL_ERR_WORKSPACE, "%s: ws_bytes is NULL", who);
   DecodeArgs a;
-  size_t part_elems = 0, need = 0;
+  DecodeParts part;
   local_status_t st = decode_setup(q, B, Hq, Hkv, D, k_new, v_new, k_cache, v_cache,
                                    num_blocks, block_size, block_table, max_blocks, ctx_lens,
                                    block_version, req_version, sm_scale, out, lse, who, &a,
-                                   &part_elems, &need);
+                                   &part);
   if (st != LOCAL_OK) return st;
   if (cap < 0) return local_fail(LOCAL_ERR_SHAPE, "%s: cap=%lld", who, (long long)cap);
   if (a.n_parts > D)
     return local_fail(LOCAL_ERR_UNSUPPORTED, "%s: max_blocks=%d over %d blocks", who,
                       max_blocks, D * a.pb);
-  const size_t masks = std::max(static_cast<size_t>(B > 0 ? B : 1) * a.n_parts,
-                                static_cast<size_t>(kFineUnits));
-  const size_t total =
-      align256(need) + align256(masks * sizeof(uint64_t)) + align256(masks * sizeof(int32_t));
+  auto total = [](const DecodeParts& p) {
+    return align256(p.bytes) + align256(p.units * sizeof(uint64_t)) +
+           align256(p.units * sizeof(int32_t));
+  };
   if (!ws) {
-    *ws_bytes = total;
+    *ws_bytes = total(part);
     return LOCAL_OK;
   }
-  if (*ws_bytes < total)
-    return local_fail(LOCAL_ERR_WORKSPACE, "%s: workspace %zu < %zu", who, *ws_bytes, total);
+  if (*ws_bytes < total(part)) part = decode_parts(a, B, D, false);
+  if (*ws_bytes < total(part))
+    return local_fail(LOCAL_ERR_WORKSPACE, "%s: workspace %zu < %zu", who, *ws_bytes, total(part));
   if (!n_stale || (B > 0 && !valid_tokens) || (cap > 0 && !stale_pairs))
     return local_fail(LOCAL_ERR_NULL, "%s: NULL version-check output", who);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -884,13 +909,14 @@ extern "C" local_status_t local_paged_attn_decode_checked(
   }
   if ((st = decode_pointers_ok(a, who)) != LOCAL_OK) return st;
   char* base = static_cast<char*>(ws);
-  a.vc_mask = reinterpret_cast<uint64_t*>(base + align256(need));
-  a.vc_valid = reinterpret_cast<int32_t*>(base + align256(need) + align256(masks * 8));
+  a.vc_mask = reinterpret_cast<uint64_t*>(base + align256(part.bytes));
+  a.vc_valid = reinterpret_cast<int32_t*>(base + align256(part.bytes) +
+                                          align256(part.units * sizeof(uint64_t)));
   a.vc_pairs = stale_pairs;
   a.vc_cap = cap;
   a.vc_n_stale = n_stale;
   a.vc_valid_tokens = valid_tokens;
-  return decode_launch(a, B, D, ws, part_elems, stream);
+  return decode_launch(a, B, D, ws, part.elems, stream);
 }
 
 // ---------------------------------------------------------------- no-alloc
@@ -942,20 +968,20 @@ extern "C" local_status_t local_paged_attn_decode_noalloc(
     const int32_t* req_version, float sm_scale, uint16_t* out, float* lse, void* stream) {
   const char* who = "paged_attn_decode_noalloc";
   DecodeArgs a;
-  size_t part_elems = 0, need = 0;
+  DecodeParts part;
   local_status_t st = decode_setup(q, B, Hq, Hkv, D, k_new, v_new, k_cache, v_cache,
                                    num_blocks, block_size, block_table, max_blocks, ctx_lens,
                                    block_version, req_version, sm_scale, out, lse, who, &a,
-                                   &part_elems, &need);
+                                   &part);
   if (st != LOCAL_OK) return st;
-  if (need > kNoAllocBytes)
+  if (part.bytes > kNoAllocBytes)
     return local_fail(LOCAL_ERR_UNSUPPORTED,
                       "%s: B*Hq*ceil(max_blocks/%d)*(D+2)*4 = %zu bytes of partials exceed the "
                       "library's fixed scratch of %zu bytes (use local_paged_attn_decode with a "
-                      "workspace)", who, a.pb, need, kNoAllocBytes);
+                      "workspace)", who, a.pb, part.bytes, kNoAllocBytes);
   if (B == 0) return LOCAL_OK;
   if ((st = decode_pointers_ok(a, who)) != LOCAL_OK) return st;
   void* partials = scratch_of_current_device(&st);
   if (!partials) return st;
-  return decode_launch(a, B, D, partials, part_elems, stream);
+  return decode_launch(a, B, D, partials, part.elems, stream);
 }
