@@ -254,7 +254,9 @@ local_status_t run_prep(hipStream_t s, const PrepArgs& a) {
 // tokens, where v_mfma_f32_16x16x4_f32 takes 16 of 32 cycles (2048 tokens, q,
 // k and v at 4096 x 4096 and rank 16: 24.0 us against 34.7). Every product is
 // exact in float32 either way and the sums are float32; against float64 the
-// gradients are 1.6e-7 off (2.1e-7 with the float32 instruction).
+// gradients are 1.6e-7 off (2.1e-7 with the float32 instruction). The bf16
+// instruction drops results below 2^-126, so the products run 2^24 times too
+// large: what it drops is then less than half the smallest float32.
 //
 // A workgroup owns one adapter's tokens for CT column tiles, UW waves a tile
 // (CT UW = 4): the waves of a tile take every UW-th unit of 64 tokens, and
@@ -277,6 +279,7 @@ struct OuterArgs {
 
 constexpr int kGrWaves = kGrThreads / kWave;
 constexpr int kGrCols = 4;  // columns per lane (E below)
+constexpr float kUp = 0x1p24f, kDown = 0x1p-24f;
 
 template <int JT, int UW>
 __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) {
@@ -291,7 +294,8 @@ __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) 
   constexpr int TILE = TILE_A > TILE_B ? TILE_A : TILE_B;
   __shared__ __attribute__((aligned(16))) float tl[kGrWaves][TILE];
   __shared__ __attribute__((aligned(16))) int tok[kGrWaves][2][kGrUnit];
-  __shared__ __attribute__((aligned(16))) float tsc[kGrWaves][2][kGrUnit];
+  __shared__ __attribute__((aligned(16))) float tsc[kGrWaves][2][kGrUnit];  // times kUp
+  __shared__ float tf[kGrWaves];  // what undoes that in a wave's tile
   using RowT = u32x2;
 
   const int job = blockIdx.y, jbase = 64 * blockIdx.z;  // ranks above 64: 64 rows at a time
@@ -336,7 +340,7 @@ __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) 
   };
   auto put_tokens = [&](int slot, int tk, float ts) {
     tok[wave][slot][lane] = tk;
-    tsc[wave][slot][lane] = ts;
+    tsc[wave][slot][lane] = ts * kUp;
   };
   const uint16_t* Vc = V + (live ? col : P - E);  // columns past P: never stored
   int jc[JT];
@@ -440,17 +444,20 @@ __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) 
         }
         if (more) load_half(slot ^ 1, h);
       }
-      bool bad = false;
+      float zero[4] = {0.f, 0.f, 0.f, 0.f};  // NaN once a value is infinite or NaN
 #pragma unroll
       for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
         for (int e = 0; e < E; ++e)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) bad |= acc[jt][e][i] != acc[jt][e][i];
-      if (__any(bad)) {
-        // a value of the unit is not finite: the parts of a coefficient then
-        // mix infinities with zeros, so the unit runs again as float32
-        // products (16x16x4: lane l gives token l / 16)
+          for (int i = 0; i < 4; ++i) zero[i] += acc[jt][e][i] * 0.f;
+      const float all = (zero[0] + zero[1]) + (zero[2] + zero[3]);
+      if (lane == 0) tf[wave] = kDown;
+      if (__any(all != all)) {
+        // a value of the unit is not finite (the parts of a coefficient then
+        // mix infinities with zeros) or too large to scale, so the unit runs
+        // again as float32 products (16x16x4: lane l gives token l / 16)
+        if (lane == 0) tf[wave] = 1.f;
 #pragma unroll
         for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
@@ -459,10 +466,11 @@ __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) 
         for (int i = k; i < kGrUnit; i += 4) {
           const bool in = i < nt;
           const int64_t t = tok[wave][slot][i];
+          const float st = args.pscale[s0 + kGrUnit * unit + min(i, nt - 1)];
           const RowT r = ld_global<RowT>(Vc + t * P);
 #pragma unroll
           for (int jt = 0; jt < JT; ++jt) {
-            const float cs = in && jok[jt] ? S[t * r_max + jc[jt]] * tsc[wave][slot][i] : 0.f;
+            const float cs = in && jok[jt] ? S[t * r_max + jc[jt]] * st : 0.f;
 #pragma unroll
             for (int e = 0; e < E; ++e) {
               const uint32_t w = in ? r[e / 2] : 0u;
@@ -494,9 +502,10 @@ __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) 
 #pragma unroll
     for (int v = 0; v < UW; ++v)
       if (u0 + v < units) {
+        const float f = tf[ct * UW + v];
 #pragma unroll
         for (int q = 0; q < kSums; ++q)
-          sum[q] += *reinterpret_cast<const f32x4*>(lds_at(ct * UW + v, q));
+          sum[q] += *reinterpret_cast<const f32x4*>(lds_at(ct * UW + v, q)) * f;
       }
     if (u0 + UW < units) __syncthreads();  // the tiles are rewritten by the next round
   }

@@ -84,3 +84,25 @@ def test_values_that_are_not_finite(where):
         assert torch.equal(g.isnan(), r.isnan())
         assert torch.equal(g.isinf(), r.isinf())
         assert torch.equal(g[g.isinf()] > 0, r[r.isinf()] > 0)
+
+
+@pytest.mark.parametrize("T", [1, 70])
+@pytest.mark.parametrize("s,x_std,dy_std", [(1e-34, 1.0, 1.0), (1e-36, 1.0, 1.0),
+                                            (1e10, 1.0, 1e-39), (1e10, 1e-39, 1.0)],
+                         ids=["s1e-34", "s1e-36", "dy1e-39", "x1e-39"])
+def test_values_near_the_smallest(T, s, x_std, dy_std):
+    # coefficients whose low parts, and rows whose values, are below the smallest
+    # normal number (2^-126): no product may lose them. Every intermediate may be
+    # off by half the smallest float32 (2^-150) besides, times its partner.
+    say("grad products, small values", T, s, x_std, dy_std)
+    x, dy, A, B, ranks, idx, scale = _inputs(T, 64, 64, 2, 16, 31)
+    idx = torch.arange(T, dtype=torch.int32) % 2
+    x, dy = (x.double() * x_std).bfloat16(), (dy.double() * dy_std).bfloat16()
+    inp = (x, dy, A, B, ranks, idx, scale * s)
+    got = _run(*inp)
+    ref = _reference(*inp, cast=lambda t: t.double())
+    mag = _reference(*inp, cast=lambda t: t.double().abs())
+    for g, r, m, v in zip(got, ref, mag, (x, dy)):
+        small = (T + 72) * 2.0 ** -149 * (1 + max(s, 1.0) * float(v.double().abs().max())) \
+            * (1 + 8.0 * T)
+        assert torch.all((g.double() - r).abs() <= (T + 72) * 2.0 ** -24 * m + small)
