@@ -28,6 +28,8 @@
 //    limit skip its arithmetic (the wave still takes part in the loads).
 #include <utility>
 
+#include <climits>
+
 #include "common.hpp"
 
 namespace localk {
@@ -50,11 +52,12 @@ __device__ __forceinline__ float max3f(float a, float b, float c) {
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
-// Tiles whose causal range spans more than kPaSplitBlocks blocks are split
-// into up to kPaMaxSplit key ranges of equal length, each its own workgroup;
-// a merge launch combines their partial results. (With the units dispatched
-// longest first, a high threshold pays: the partial results cost HBM
-// traffic, and a long unit that starts first does not set the end.)
+// Tiles whose causal range spans more than kPaSplitBlocks blocks (less in calls
+// of few tiles: few_ranges below) are split into up to kPaMaxSplit key ranges of
+// equal length, each its own workgroup; a merge launch combines their partial
+// results. (With the units dispatched longest first, a
+// high threshold pays: the partial results cost HBM traffic, and a long unit
+// that starts first does not set the end.)
 #ifndef LOCAL_PA_SPLIT_BLOCKS
 #define LOCAL_PA_SPLIT_BLOCKS 96
 #endif
@@ -63,7 +66,13 @@ __device__ __forceinline__ float max3f(float a, float b, float c) {
 #endif
 constexpr int kPaSplitBlocks = LOCAL_PA_SPLIT_BLOCKS;
 constexpr int kPaMaxSplit = LOCAL_PA_MAX_SPLIT;
-constexpr int kPaSlots = 512;  // workgroups that run at once: two per compute unit
+
+// The key ranges of a tile: 2, 3 or 4 when it sees more than two, three or four
+// blocks, in a call whose longest tile sees more than `from` of them and no more
+// than `upto`.
+struct KeyRanges {
+  int from, upto, two, three, four;
+};
 
 struct PrefillArgs {
   const uint16_t* q;
@@ -86,6 +95,7 @@ struct PrefillArgs {
   int B, Hq, Hkv, group, max_blocks;
   float scale_log2;  // |sm_scale| * log2(e)
   uint32_t q_sign;   // 0x80008000 when sm_scale < 0 (q's sign bits flipped), else 0
+  KeyRanges few;     // the key ranges of a call of few tiles
 };
 
 __device__ __forceinline__ bool id_ok(int p, int64_t num_blocks) {
@@ -198,19 +208,20 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 constexpr int kPlanThreads = 256;  // threads of the workgroup that plans the units
+template <bool FEW>
 __device__ void plan_units(const PrefillArgs& a);
 
 // Append. Workgroup = (one block that request b's chunk writes, KV head g),
 // mapped from a 1D grid (heads fastest); the block's slots [lo, hi) are new
 // (positions P_b .. L_b - 1). Thread t handles slot t / (D/8), dims
 // 8 (t % (D/8)) .. +8.
-template <int D>
+template <int D, bool FEW>
 __global__ __launch_bounds__(256) void prefill_append_kernel(PrefillArgs a) {
   constexpr int C8 = D / 8;
   __shared__ uint16_t vt[D][kBlockSize + 2];  // V of the block, dim-major (+2: banks)
   // workgroup 0 (dispatched first) plans the attention grid's units
   if (blockIdx.x == 0) {
-    plan_units(a);
+    plan_units<FEW>(a);
     return;
   }
   const unsigned bid = blockIdx.x - 1;
@@ -284,23 +295,11 @@ __device__ __forceinline__ int tile_blocks(int P, int n_b, int t, int max_blocks
   return lim < 0 ? 0 : min(lim / kBlockSize + 1, max_blocks);
 }
 
-// Key ranges a tile of nbl blocks is split into, `limit` blocks each at most
-// (kPaMaxSplit ranges at most): without a division, one thread counts many tiles.
-__device__ __forceinline__ int tile_splits(int nbl, int limit) {
-  int ns = 1;
-#pragma unroll
-  for (int i = 1; i < kPaMaxSplit; ++i) ns += nbl > i * limit ? 1 : 0;
-  return ns;
-}
-
-// The limit of a call whose tiles see `blocks` blocks in all, over its heads.
-// From 24 blocks for each workgroup that the chip holds (two per compute unit)
-// kPaSplitBlocks: the longest units start first, and partial results cost
-// traffic. Below, the chip is not full and the longest unit sets the end, so the
-// ranges go down to that mean load, at least 16 blocks.
-__device__ __forceinline__ int split_limit(unsigned long long blocks) {
-  const unsigned long long mean = blocks / kPaSlots;
-  return mean >= 24 ? kPaSplitBlocks : max(static_cast<int>(mean), 16);
+// Key ranges a tile of nbl blocks is split into (no division: one thread counts
+// many tiles).
+__device__ __forceinline__ int tile_splits(int nbl, const KeyRanges& r) {
+  static_assert(kPaMaxSplit == 4, "up to four ranges");
+  return 1 + (nbl > r.two ? 1 : 0) + (nbl > r.three ? 1 : 0) + (nbl > r.four ? 1 : 0);
 }
 
 // Partial-result slot of (tile t of request b with rows from r0, head h,
@@ -328,15 +327,17 @@ __device__ __forceinline__ int tile_class(int nbl, int ns) {
 // from the last request backwards, a request's tiles from its last one, a
 // tile's key ranges ascending. So the longest units start first, whatever
 // request they belong to, and the grid ends on the short ones; an attention
-// workgroup reads its unit with one load instead of deriving it.
+// workgroup reads its unit with one load instead of deriving it. FEW: the call
+// may take the key ranges of few tiles (code of its own, since one workgroup runs
+// the planner from cold instruction caches).
+template <bool FEW>
 __device__ void plan_units(const PrefillArgs& a) {
   __shared__ int scan[kPaClasses][kPlanThreads];
   __shared__ int totals[kPaClasses];
-  __shared__ int n_split_tiles;
-  __shared__ unsigned long long all_blocks;
+  __shared__ int n_split_tiles, longest;
   const int tid = threadIdx.x;
   // request bb's first row, rows and prefix (false: no rows, or a bad range)
-  auto rows = [&](int bb, int* r0, int* n, int* P) {
+  auto read_rows = [&](int bb, int* r0, int* n, int* P) {
     const int q0 = a.q_indptr[bb], q1 = a.q_indptr[bb + 1];
     if (!rows_ok(q0, q1, a.T) || q1 == q0) return false;
     *r0 = q0;
@@ -344,10 +345,22 @@ __device__ void plan_units(const PrefillArgs& a) {
     *P = a.ctx_lens[bb] - *n;
     return true;
   };
-  int limit = 0;
+  // a call of few tiles has at most kPlanThreads requests, read once: thread i
+  // has the i-th from the end
+  int my_r0 = 0, my_n = 0, my_P = 0;
+  bool mine = false;
+  if (FEW) mine = tid < a.B && read_rows(a.B - 1 - tid, &my_r0, &my_n, &my_P);
+  auto rows = [&](int bb, int* r0, int* n, int* P) {
+    if (!FEW) return read_rows(bb, r0, n, P);
+    *r0 = my_r0;
+    *n = my_n;
+    *P = my_P;
+    return mine;
+  };
+  KeyRanges kr = {0, INT_MAX, kPaSplitBlocks, 2 * kPaSplitBlocks, 3 * kPaSplitBlocks};
   auto count = [&](int P, int n, int (&cnt)[kPaClasses]) {
     for (int t = 0; t * kPaRows < n; ++t) {
-      const int nbl = tile_blocks(P, n, t, a.max_blocks), ns = tile_splits(nbl, limit);
+      const int nbl = tile_blocks(P, n, t, a.max_blocks), ns = tile_splits(nbl, kr);
       const int c = tile_class(nbl, ns);
 #pragma unroll
       for (int cc = 0; cc < kPaClasses; ++cc) cnt[cc] += c == cc ? ns : 0;
@@ -356,31 +369,28 @@ __device__ void plan_units(const PrefillArgs& a) {
   if (tid < kPaClasses) totals[tid] = 0;
   if (tid == 0) {
     n_split_tiles = 0;
-    all_blocks = 0ull;
+    if (FEW) longest = 0;
   }
   __syncthreads();
-  for (int bb = tid; bb < a.B; bb += kPlanThreads) {
-    int r0, n, P;
-    if (!rows(bb, &r0, &n, &P)) continue;
-    // the mean of the first and the last tile for each of them
-    const int last = (n - 1) / kPaRows;
-    const unsigned long long ends =
-        tile_blocks(P, n, 0, a.max_blocks) + tile_blocks(P, n, last, a.max_blocks);
-    atomicAdd(&all_blocks, ends * (last + 1) / 2);
-  }
-  __syncthreads();
-  limit = split_limit(all_blocks * a.Hq);
-  for (int bb = tid; bb < a.B; bb += kPlanThreads) {
-    int r0, n, P, cnt[kPaClasses];
+  // counted again where the longest tile asks for the key ranges of few tiles
+  for (bool again = false;; again = true) {
+    for (int i = tid; i < a.B; i += kPlanThreads) {
+      int r0, n, P, cnt[kPaClasses];
 #pragma unroll
-    for (int c = 0; c < kPaClasses; ++c) cnt[c] = 0;
-    if (!rows(bb, &r0, &n, &P)) continue;
-    count(P, n, cnt);
+      for (int c = 0; c < kPaClasses; ++c) cnt[c] = 0;
+      if (!rows(a.B - 1 - i, &r0, &n, &P)) continue;
+      count(P, n, cnt);
 #pragma unroll
-    for (int c = 0; c < kPaClasses; ++c)
-      if (cnt[c]) atomicAdd(&totals[c], cnt[c]);
+      for (int c = 0; c < kPaClasses; ++c)
+        if (cnt[c]) atomicAdd(&totals[c], cnt[c]);
+      if (FEW) atomicMax(&longest, tile_blocks(P, n, (n - 1) / kPaRows, a.max_blocks));
+    }
+    __syncthreads();
+    if (!FEW || again || longest <= a.few.from || longest > a.few.upto) break;
+    kr = a.few;
+    if (tid < kPaClasses) totals[tid] = 0;
+    __syncthreads();
   }
-  __syncthreads();
   int first[kPaClasses];  // next entry of each class
   {
     int acc = 0;
@@ -417,7 +427,7 @@ __device__ void plan_units(const PrefillArgs& a) {
     for (int c = 0; c < kPaClasses; ++c) pos[c] = first[c] + scan[c][tid] - cnt[c];
     if (ok) {
       for (int t = (n - 1) / kPaRows; t >= 0; --t) {
-        const int nbl = tile_blocks(P, n, t, a.max_blocks), ns = tile_splits(nbl, limit);
+        const int nbl = tile_blocks(P, n, t, a.max_blocks), ns = tile_splits(nbl, kr);
         const int c = tile_class(nbl, ns);
         int e = 0;
 #pragma unroll
@@ -442,8 +452,9 @@ __device__ void plan_units(const PrefillArgs& a) {
 }
 
 // The planner alone, for calls without an append.
+template <bool FEW>
 __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PrefillArgs a) {
-  plan_units(a);
+  plan_units<FEW>(a);
 }
 
 template <int D>
@@ -924,17 +935,49 @@ size_t prefill_ws_bytes(int64_t T, int B, int Hq) {
          static_cast<size_t>(tiles) * (2 * kPaMaxSplit + 1) * sizeof(int4);
 }
 
+// The key ranges of a call of few tiles. It leaves compute units idle and its
+// longest unit sets the end, so shorter ranges pay where they save more than the
+// partial results add: those grow with the (tile, head) pairs and D, and ranges
+// past two workgroups per compute unit wait for a second round. The pairs are
+// those that the workspace is sized for, since the host knows no lengths; the
+// planner compares the longest tile (with tiles just below the limit left whole,
+// splitting the others gains nothing). From 129 pairs on, calls that the common
+// rule splits too keep to it: more ranges there gained 10% or lost 5%. Measured,
+// whole calls in us by the common rule / these ranges: 32 pairs, 16 rows on 300 /
+// 1000 tokens 18.8 / 16.4 and 36.2 / 20.5; 64 pairs, 200 rows on 450 / 1000 tokens
+// 29.4 / 28.5 and 41.9 / 31.0; 128 pairs, 4 x 16 rows on 1000 / 2000 tokens 36.1 /
+// 27.6 and 41.5 / 38.8; 192 pairs, 3 x 128 rows on 300 / 1000 tokens 25.4 (in 2
+// ranges 27.2) and 41.6 / 33.6; 256 pairs, 4 x 250 rows on 2000 tokens 68, in 4
+// ranges 77; 384 pairs, 12 x 128 rows on 224 tokens 34, in 2 ranges 49.
+KeyRanges few_ranges(int64_t T, int B, int Hq, int D) {
+  const int64_t pairs = (T / kPaRows + B) * Hq;
+  if (pairs * D <= 32 * 128) return {19, INT_MAX, 16, 32, 48};
+  if (pairs <= 64) return {40, INT_MAX, 32, 64, 64};
+  if (pairs <= 128) return {56, INT_MAX, 40, 80, 80};
+  if (pairs <= 192) return {64, 96, 48, INT_MAX, INT_MAX};
+  return {INT_MAX, 0, 0, 0, 0};
+}
+
 template <int D>
 local_status_t launch_prefill(const PrefillArgs& a, hipStream_t s) {
+  const bool maybe_few = a.few.from < a.max_blocks;  // no tile sees more
+  static_assert(kPlanThreads >= 192, "one request per planner thread in calls of few tiles");
   if (a.k_new) {
     // a chunk of n rows spans at most n / 16 + 2 blocks: T / 16 + 2 B in all;
     // workgroup 0 plans the attention units
     const int64_t units = a.T / kBlockSize + 2LL * a.B;
-    prefill_append_kernel<D><<<static_cast<unsigned>(units * a.Hkv + 1), 256, 0, s>>>(a);
+    const unsigned grid = static_cast<unsigned>(units * a.Hkv + 1);
+    if (maybe_few)
+      prefill_append_kernel<D, true><<<grid, 256, 0, s>>>(a);
+    else
+      prefill_append_kernel<D, false><<<grid, 256, 0, s>>>(a);
     local_status_t st = local_check_launch("paged_attn_prefill (append)");
     if (st != LOCAL_OK) return st;
   } else {
-    prefill_plan_kernel<<<1, kPlanThreads, 0, s>>>(a);
+    if (maybe_few)
+      prefill_plan_kernel<true><<<1, kPlanThreads, 0, s>>>(a);
+    else
+      prefill_plan_kernel<false><<<1, kPlanThreads, 0, s>>>(a);
     local_status_t st = local_check_launch("paged_attn_prefill (plan)");
     if (st != LOCAL_OK) return st;
   }
@@ -1017,6 +1060,7 @@ extern "C" local_status_t local_paged_attn_prefill(
   a.Hkv = Hkv;
   a.group = Hq / Hkv;
   a.max_blocks = max_blocks;
+  a.few = few_ranges(T, B, Hq, D);
   a.part = static_cast<float*>(ws);
   {
     const size_t pb = D == 64 ? prefill_part_bytes<64>(T, B, Hq) : prefill_part_bytes<128>(T, B, Hq);
