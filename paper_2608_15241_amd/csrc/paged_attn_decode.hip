@@ -7,13 +7,14 @@
 //  * Split-KV. A workgroup owns a partition of 16 to 64 logical blocks of one
 //    request and one KV head; it is one wave, or two or four where there are
 //    few partitions (its valid blocks are dealt to the waves, whose results
-//    meet in LDS). Partitions are
-//    counted from the end of the context and their index is the slowest grid
-//    dimension, so full partitions are dispatched first and each request's
-//    partial one (its oldest blocks) last, which shortens the tail when
-//    context lengths vary. A wave reads the partition's table entries and tags
-//    first, keeps the non-stale blocks and walks them
-//    in order through a ring of DEPTH register sets, so that DEPTH-1 blocks'
+//    meet in LDS). Partitions are counted from the end of the context. Up to
+//    512 requests the dispatch slots take every full partition first, request
+//    by request, then the requests' partial ones (their oldest blocks), longest
+//    first, which shortens the tail when context lengths vary; with more
+//    requests the partition index is the slowest grid dimension and the partial
+//    ones come last in the order of the requests. A wave reads the partition's
+//    table entries and tags first, keeps the non-stale blocks and walks them in
+//    order through a ring of DEPTH register sets, so that DEPTH-1 blocks'
 //    K/V loads are in flight while one block is computed. Block loads are
 //    buffer loads issued unconditionally (a block past the end gets a
 //    zero-size descriptor: zeros, no traffic) and the new token is merged in
@@ -708,20 +709,22 @@ void launch_ranked(const DecodeArgs& a, int B, unsigned grid, int W, hipStream_t
 // Waves that share a partition. What a wave does before its first block (three
 // dependent loads) and its in-flight blocks bound a partition, so few units
 // want more waves each, and many units want one (three waves of one unit hold
-// the registers of three units). Measured in us with 1 / 2 / 4 waves, units as
-// counted here (half of them or less run; the table is as wide as the longest
-// context): grouped heads 248 units 31 / 21 / 17; 512 (16-block table rows of
-// 44) 22 / 16 / 13; 1024 38 / 37 / 36, but 26 / 25 / 27 with tables of 19 blocks;
-// 2048 62 / 59 / 58; 4096 112 / 107 / 108; 16384 719 / 715 / 725; with 64-block
-// partitions (2560 units) 148 / 152 / 142. One query head
-// per KV head: 96 units 30 / 19 / 15; 512 31 / 22 / 27; 2816 111 / 107 / 114; 4096
-// 109 / 106 / 124, but 76 / 99 / 156 with tables of 19 blocks; 8192 199 / 202 / 238.
+// the registers of three units). Units are counted from the table's width, since
+// the host knows no lengths: half of them or less run. Measured in us with 1 / 2 / 4
+// waves: one query head per KV head: 96 units 30 / 19 / 15; 512 31 / 22 / 27; 1536 to
+// 3072 44 / 50 / 61, 79 / 82 / 99, 85 / 91 / 116, and with contexts of 10 blocks in
+// tables of 64 19 / 22 / 28; 8192 199 / 202 / 238. Grouped heads: 248 units 31 / 21 /
+// 17; 384 20 / 18 / 17; 768 33 / 28 / 26; 1024 33 / 34 / 33; 1280 37 / 42 / 40; 1536 to
+// 2560 46 / 46 / 47, 54 / 51 / 53, 63 / 58 / 60, 76 / 72 / 75 (contexts that fill a
+// third of the table 32 / 28, 34 / 36, 40 / 42, 52 / 50; with 64-block partitions 148 /
+// 152 / 142); 3072 to 4096 84 / 87 / 86, 95 / 97 / 99, 117 / 111 / 112; 16384 719 / 715 /
+// 725. So one wave from 768 units on, two for grouped heads from 1536 to 2560.
 int waves_of(const DecodeArgs& a, int B) {
   const int64_t units = static_cast<int64_t>(a.Hkv) * B * a.n_parts;
   const bool mha = a.group == 1;
   if (units < (mha ? 257 : kFewUnits)) return 4;
   if (units < kFewUnits) return 2;
-  const bool pair = units >= 1536 && units <= (mha ? 3072 : 4096);
+  const bool pair = !mha && units >= 1536 && units <= 2560;
   return pair && a.max_blocks >= 64 && a.pb < 64 ? 2 : 1;
 }
 
@@ -860,6 +863,17 @@ extern "C" local_status_t local_paged_attn_decode(
   if (B == 0) return LOCAL_OK;
   if ((st = decode_pointers_ok(a, who)) != LOCAL_OK) return st;
   return decode_launch(a, B, D, ws, part.elems, stream);
+}
+
+// The partition length and waves that a call's size selects, as blocks + 256 x
+// waves (for the tests, which name the form that they mean; not in local.h).
+extern "C" int32_t localk_decode_form(int32_t B, int32_t Hq, int32_t Hkv, int32_t max_blocks) {
+  DecodeArgs a{};
+  a.Hkv = Hkv;
+  a.group = Hq / Hkv;
+  a.max_blocks = max_blocks;
+  decode_parts(a, B, 128, true);
+  return a.pb + 256 * waves_of(a, B);
 }
 
 // ---------------------------------------------------------------- checked

@@ -74,25 +74,38 @@ def test_smallest_workspace_is_accepted(B, hkv, group, D, mb, checked):
     assert status(least - 1) == 4  # LOCAL_ERR_WORKSPACE
 
 
-# (batch, Hq, Hkv, D, longest context, table width or None)
+# (batch, Hq, Hkv, D, longest context, table width or None, blocks of a partition, waves)
 CASES = [
-    (1, 4, 4, 64, 1, None),        # one block
-    (3, 32, 8, 128, 256, None),    # one partition of 16 blocks, full
-    (4, 32, 8, 128, 4100, None),   # 257-block table: 48 -> 16 blocks
-    (5, 8, 8, 128, 8192, None),    # 512-block table, one query head per KV head
-    (2, 32, 8, 128, 16384, None),  # 64 -> 32 blocks, four waves
-    (1, 16, 1, 64, 9000, None),    # 16 query heads per KV head (the largest merge)
-    (12, 32, 32, 128, 500, None),  # two waves
-    (24, 32, 32, 128, 700, None),  # one wave, 32-block partitions
-    (50, 32, 32, 128, 60, 64),     # two waves, most of them without a block
-    (65, 12, 4, 64, 1500, None),   # ranked over two registers of requests
-    (130, 8, 4, 64, 1100, None),   # ... three, two waves
-    (520, 1, 1, 64, 90, None),     # too many requests to rank
+    (1, 4, 4, 64, 1, None, 16, 4),        # one block
+    (3, 32, 8, 128, 256, None, 16, 4),    # one partition of 16 blocks, full
+    (4, 32, 8, 128, 4100, None, 16, 4),   # 257-block table: 48 -> 16 blocks
+    (5, 8, 8, 128, 8192, None, 16, 1),    # 512-block table, one query head per KV head
+    (2, 32, 8, 128, 16384, None, 32, 4),  # 64 -> 32 blocks
+    (1, 16, 1, 64, 9000, None, 32, 4),    # 16 query heads per KV head (the largest merge)
+    (11, 32, 32, 128, 500, None, 16, 2),  # 704 units
+    (12, 32, 32, 128, 500, None, 16, 1),  # 768 units
+    (20, 32, 32, 128, 60, 16, 16, 2),     # two waves, most of them without a block
+    (24, 32, 32, 128, 700, None, 32, 1),
+    (50, 32, 32, 128, 60, 64, 32, 1),     # partitions mostly without a block
+    (40, 32, 32, 128, 300, 64, 32, 1),    # one query head per KV head: no pairs of waves
+    (24, 32, 8, 128, 3000, 256, 32, 2),   # grouped heads, 1536 units: pairs
+    (40, 32, 8, 128, 400, 256, 32, 2),    # ... 2560, most partitions not there
+    (41, 32, 8, 128, 400, 256, 32, 1),    # ... 2624
+    (65, 12, 4, 64, 1500, None, 32, 1),   # ranked over two registers of requests
+    (130, 8, 4, 64, 1100, None, 32, 2),   # ... three, two waves
+    (520, 1, 1, 64, 90, None, 16, 2),     # too many requests to rank
 ]
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,D,longest,width,blocks,waves", CASES)
+def test_decode_forms_are_the_named_ones(B, Hq, Hkv, D, longest, width, blocks, waves):
+    lib = ctypes.CDLL(os.path.join(ROOT, "paper_2608_15241_amd", "liblocal.so"))
+    form = lib.localk_decode_form(B, Hq, Hkv, width or -(-longest // 16))
+    assert (form % 256, form // 256) == (blocks, waves)
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("B,Hq,Hkv,D,longest,width", CASES)
+@pytest.mark.parametrize("B,Hq,Hkv,D,longest,width", [c[:6] for c in CASES])
 def test_decode_partition_forms(B, Hq, Hkv, D, longest, width):
     say("decode partitions", B, Hq, Hkv, D, longest, width)
     rng = np.random.default_rng(B * 1000 + longest)
