@@ -1215,18 +1215,20 @@ using Pf64x64 = PfShape<64, 64, 2, 2, 4>;
 // third of the chip or less is busy and `full` us when all of it is (the
 // clock falls and the caches are shared). Measured at K = 4096 (tile: us of a
 // round that is nearly empty / full): 128x256: 44 / 58, 128x128: 28 / 36,
-// 64x128: 24 / 41, 64x64: 23 / 26. So, at 4096 features, 2048 tokens take
+// 64x128: 24 / 41, 64x64: 23 / 26; of one of several full rounds 66, 40, 48 and
+// -, so 64x128 is priced at 43. So, at 4096 features, 2048 tokens take
 // 128x256 (58 us; 128x128: 70), 1000 tokens 128x128 (37 us; 128x256: 49) and
-// 300 tokens 64x64 (24 us; 128x256: 44). (Larger tiles are no faster where
-// they would fill the chip: a full round of 256x256 takes twice that of
-// 128x256, the clock being what gives.)
+// 300 tokens 64x128 (24 us; 128x256: 44); at 12288, 1300 tokens 128x256 (whole
+// call 169 us; 64x128: 188). (Larger tiles are no faster where they would fill
+// the chip: a full round of 256x256 takes twice that of 128x256, the clock being
+// what gives.)
 struct PfCost {
   int m, n, slots;
   double fixed, few, full, knee;  // knee: the load from which a step takes `full`
 };
 constexpr PfCost kPfCosts[] = {{128, 256, 256, 5.0, 0.62, 0.83, 1.0},
                                {128, 128, 256, 4.0, 0.37, 0.51, 1.0},
-                               {64, 128, 512, 3.2, 0.32, 0.57, 0.75},
+                               {64, 128, 512, 3.2, 0.32, 0.62, 0.75},
                                {64, 64, 512, 3.0, 0.31, 0.35, 1.0}};
 
 int prefill_tile(int64_t T, int64_t K, int G, const Proj* p) {
@@ -1255,6 +1257,19 @@ int prefill_tile(int64_t T, int64_t K, int G, const Proj* p) {
   }
   return best;
 }
+
+}  // namespace
+
+// The tile of a long chunk's product that a call's sizes select: 0 to 3 = 128 x
+// 256, 128 x 128, 64 x 128, 64 x 64 (for the tests, which name the tile that they
+// mean; not in local.h).
+extern "C" int32_t localk_prefill_tile(int64_t T, int64_t K, int32_t G, const int64_t* N) {
+  Proj p[kMaxGroup] = {};
+  for (int g = 0; g < G; ++g) p[g].N = N[g];
+  return prefill_tile(T, K, G, p);
+}
+
+namespace {
 
 local_status_t run_prefill(const GemmArgs& a, int tile, hipStream_t s) {
   switch (tile) {
