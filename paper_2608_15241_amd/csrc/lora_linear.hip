@@ -503,20 +503,22 @@ local_status_t run_sgmv_shrink(const GemmArgs& a, hipStream_t s) {
 // so a value that is not finite stays with its adapter. Measured (whole calls,
 // a thread's own loads / matrix cores): rank 64, 64 tokens x 6144 features over
 // 16 adapters 35.1 / 32.3 us (this kernel 14.8 / 11.8), 256 tokens x 12288 144 /
-// 130; rank 32, 256 tokens x 4096 45.5 / 41.6; rank 16, 32 tokens x 6144 19.7 /
-// 20.5 (the list of adapters comes first).
+// 130; rank 32, 256 tokens x 4096 45.5 / 41.6, 3 tokens 14.6 / 14.4; rank 24, 3
+// tokens x 4096 14.0 / 14.6, 12 x 6144 18.2 / 19.0, 256 x 6144 44.9 / 51.9; rank 16, 32
+// tokens x 6144 19.7 / 20.5 (the list of adapters comes first).
 constexpr int kEpThreads = 256;
 constexpr int kEpTokens = 16;
 constexpr int kEpFeatures = 64;
 
-constexpr int kEpFewColumns = 16;
+constexpr int kEpFewColumns = 24;
 constexpr int kEpBatch = 16;      // B operands in flight per wave
 constexpr int kEpUsRow = 128 + 8;  // bf16 values of an LDS row of U_s (padded: bank spread)
 
-// r_max <= kEpFewColumns, or no adapters.
-template <int KSB>
+// r_max <= 8 STEPS, or no adapters (its registers grow with STEPS).
+template <int KSB, int STEPS>
 __global__ __launch_bounds__(kEpThreads) void lora_epilogue_kernel(GemmArgs a) {
-  __shared__ float us[kEpTokens][kEpFewColumns + 1];
+  constexpr int kSteps = STEPS;
+  __shared__ float us[kEpTokens][8 * STEPS + 1];
   const int tid = threadIdx.x;
   const int tt = tid / (kEpFeatures / 4), ng = tid % (kEpFeatures / 4);
   const int64_t t0 = static_cast<int64_t>(blockIdx.y) * kEpTokens;
@@ -544,7 +546,6 @@ __global__ __launch_bounds__(kEpThreads) void lora_epilogue_kernel(GemmArgs a) {
   const int my_ad = (lora && live) ? token_adapter(a, t) : -1;
   const uint16_t* brow =
       pick(a.gb, g) + (static_cast<int64_t>(my_ad >= 0 ? my_ad : 0) * Ng + n) * a.r_max;
-  constexpr int kSteps = kEpFewColumns / 8;
   u32x4 bv[kSteps][4];  // [8-column step][feature]
   if (my_ad >= 0) {
 #pragma unroll
@@ -763,8 +764,10 @@ local_status_t launch_epilogue(const GemmArgs& a, hipStream_t s) {
             static_cast<unsigned>((a.T + kEpTokens - 1) / kEpTokens));
   if (a.n_ad > 0 && a.r_max > kEpFewColumns)
     lora_epilogue_wide_kernel<KSB><<<grid, kEpThreads, 0, s>>>(a);
+  else if (a.n_ad > 0 && a.r_max > 16)
+    lora_epilogue_kernel<KSB, 3><<<grid, kEpThreads, 0, s>>>(a);
   else
-    lora_epilogue_kernel<KSB><<<grid, kEpThreads, 0, s>>>(a);
+    lora_epilogue_kernel<KSB, 2><<<grid, kEpThreads, 0, s>>>(a);
   return local_check_launch("lora_linear (epilogue)");
 }
 

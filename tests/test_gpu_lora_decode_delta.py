@@ -27,6 +27,10 @@ CASES = [
     (65, 64, 576, 70, 128, [128] * 70),                     # 64 steps in a tile
     (129, 128, 64, 12, 16, None),
     (256, 512, 256, 256, 8, None),
+    # 24 columns: a thread's own loads of B, as up to 16
+    (1, 64, 64, 1, 24, [24]),
+    (33, 128, 192, 5, 24, [24, 0, 17, 9, 24]),
+    (256, 64, 320, 40, 24, None),
     # more than 64 tokens: tiles of 3, 6, 6 and 4 x 16 features, 1 to 4 extra row tiles
     (100, 128, 6144, 5, 16, None),
     (129, 128, 12288, 3, 16, None),
