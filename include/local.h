@@ -204,9 +204,10 @@ local_status_t local_lora_linear_grouped(
  *  Sizes: T >= 0 (T = 0 writes zero gradients), K and N positive multiples
  *  of 64, 1 <= n_adapters <= 256, r_max a multiple of 8 in [8, 128].
  *  u and g are float32 (not rounded); every sum is float32, over chunks of 64
- *  tokens of one adapter (taken in token order), chunks added in order: the
- *  result does not depend on the launch. Outputs must not alias
- *  the inputs. Errors as for local_lora_linear.
+ *  tokens of one adapter (taken in token order), chunks added in order, those of
+ *  every 2048 tokens apart and their sums in order: the result does not depend on
+ *  the launch or on the other adapters. Outputs must not alias the inputs.
+ *  Errors as for local_lora_linear.
  */
 local_status_t local_lora_grad(
     const uint16_t* x, int64_t T, int64_t K,

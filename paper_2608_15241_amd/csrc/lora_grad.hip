@@ -7,14 +7,15 @@
 //   dx_t = dy_t W + g_t A_a.
 //
 // Design (HBM-bound for the adapter gradients: 4 T r (K + N) flop, shrinks
-// included, against T (K + N) bf16 read), three launches:
+// included, against T (K + N) bf16 read), three launches (four above 2048 tokens):
 //  * set-up: the tokens bucketed by adapter (a stable counting sort in one
 //    workgroup, as in SGMV) while the other workgroups transpose B per
 //    adapter to [r_max][N];
 //  * u = x A^T and dy B for every projection in one launch (lora_shrink.hip);
 //  * dB and dA as segmented outer products in one launch, each workgroup over
-//    all of one adapter's tokens: sums of 64 tokens added in token order,
-//    deterministic, no partial sums in memory, no atomics.
+//    up to 2048 tokens of one adapter: sums of 64 tokens added in token order,
+//    deterministic, no partial sums in memory, no atomics. A fourth launch adds
+//    the sums of an adapter of more tokens.
 //  dx runs the forward fused projection on the transposed weights: with
 //  x := dy, W := W^T, A := B^T and B := A^T, its shrink is dy B and its
 //  delta s (dy B) A, so dx needs no kernel of its own.
@@ -58,9 +59,39 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
 constexpr int kPrepThreads = 1024;
 constexpr int kPrepWaves = kPrepThreads / kWave;
 
+// The tokens of an adapter with more than few_tokens of them are also listed in
+// spans of kGrSpan for the outer products: {adapter, first position, tokens,
+// whether it is the adapter's only span}; an adapter of several spans in the
+// list of those, {adapter, first span, spans, 0}.
+constexpr int kGrSpan = 2048;
+
+// Tokens up to which an adapter is not listed in spans (it does not change the
+// result): one unit, or two where adapters have fewer than two on average and the
+// grid, which has room for every adapter that could be listed, matters more
+// (with one unit / two: 512 tokens of 4 adapters at 1024 x 1024 18.0 / 21.7 us, 256 of
+// 4 at 4096 x 4096 34.9 / 32.7, 2048 of 64 97.5 / 95.2).
+int few_tokens(int64_t T, int n_ad) { return T < 2 * kGrUnit * n_ad ? 2 * kGrUnit : kGrUnit; }
+
+// The most entries of either list.
+int64_t max_spans(int64_t T, int n_ad) {
+  return T / kGrSpan + std::min<int64_t>(n_ad, T / (few_tokens(T, n_ad) + 1));
+}
+int64_t max_long(int64_t T, int n_ad) { return std::min<int64_t>(n_ad, T / (kGrSpan + 1)); }
+
+struct Buckets {
+  int32_t* perm;   // [T]
+  float* pscale;   // [T]
+  int32_t* seg;    // [n_ad + 1]
+  int32_t* n_list; // entries of spans and of longs
+  i32x4 *spans, *longs;
+  int few;         // few_tokens
+};
+
 __device__ void bucket_tokens(const int32_t* __restrict__ idx, int64_t T, int n_ad,
-                              const float* __restrict__ scale, int32_t* __restrict__ perm,
-                              float* __restrict__ pscale, int32_t* __restrict__ seg) {
+                              const float* __restrict__ scale, const Buckets& bk) {
+  int32_t* __restrict__ perm = bk.perm;
+  float* __restrict__ pscale = bk.pscale;
+  int32_t* __restrict__ seg = bk.seg;
   __shared__ int cnt[kPrepWaves][kGrMaxAdapters];  // per wave: count, then running offset
   __shared__ int tot[kGrMaxAdapters];
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
@@ -92,19 +123,32 @@ __device__ void bucket_tokens(const int32_t* __restrict__ idx, int64_t T, int n_
   }
   __syncthreads();
   if (wave == 0) {
-    int run = 0;
+    int run = 0, run_span = 0, run_long = 0;
     for (int a0 = 0; a0 < n_ad; a0 += kWave) {
       const int a = a0 + lane;
       const int c = a < n_ad ? tot[a] : 0;
       const int ic = wave_incl_scan(c);
+      const int ns = c > bk.few ? (c + kGrSpan - 1) / kGrSpan : 0;
+      const int is = wave_incl_scan(ns);
+      const uint64_t several = __ballot(ns > 1);
+      const int s0 = run + ic - c, sp0 = run_span + is - ns;
       if (a < n_ad) {
-        const int s0 = run + ic - c;
         seg[a] = s0;
         tot[a] = s0;
       }
+      for (int i = 0; i < ns; ++i)
+        bk.spans[sp0 + i] = i32x4{a, s0 + i * kGrSpan, min(kGrSpan, c - i * kGrSpan), ns == 1};
+      if (ns > 1)
+        bk.longs[run_long + __popcll(several & ((1ull << lane) - 1ull))] = i32x4{a, sp0, ns, 0};
       run += __shfl(ic, kWave - 1);
+      run_span += __shfl(is, kWave - 1);
+      run_long += __popcll(several);
     }
-    if (lane == 0) seg[n_ad] = run;
+    if (lane == 0) {
+      seg[n_ad] = run;
+      bk.n_list[0] = run_span;
+      bk.n_list[1] = run_long;
+    }
   }
   __syncthreads();
   for (int a = tid; a < n_ad; a += kPrepThreads) {
@@ -208,8 +252,7 @@ struct PrepArgs {
   const float* scale;
   int64_t T;
   int n_ad;
-  int32_t *perm, *seg;
-  float* pscale;
+  Buckets bk;
 };
 
 __global__ __launch_bounds__(kPrepThreads) void grad_prep_kernel(PrepArgs a) {
@@ -217,7 +260,7 @@ __global__ __launch_bounds__(kPrepThreads) void grad_prep_kernel(PrepArgs a) {
   int wg = blockIdx.x;
   if (a.idx) {
     if (wg == 0) {
-      bucket_tokens(a.idx, a.T, a.n_ad, a.scale, a.perm, a.pscale, a.seg);
+      bucket_tokens(a.idx, a.T, a.n_ad, a.scale, a.bk);
       return;
     }
     --wg;
@@ -258,22 +301,35 @@ local_status_t run_prep(hipStream_t s, const PrepArgs& a) {
 // instruction drops results below 2^-126, so the products run 2^24 times too
 // large: what it drops is then less than half the smallest float32.
 //
-// A workgroup owns one adapter's tokens for CT column tiles, UW waves a tile
-// (CT UW = 4): the waves of a tile take every UW-th unit of 64 tokens, and
-// after each round their tiles are added through LDS in unit order to sums
-// that stay in registers until the adapter's last unit, so no partial sum
-// goes through memory (with a workgroup per unit, the partial sums of 2048
-// tokens at 4096 x 4096 x 3 were 56 MB written and read back: 43 us and a
-// 10.8 us reduce launch). Units are added in order whatever UW is.
+// A workgroup takes one span of an adapter's tokens for one column tile, its
+// four waves every fourth unit of 64 tokens; after each round their tiles are
+// added through LDS in unit order to sums that stay in registers until the
+// span's last unit, so no partial sum goes through memory (with a workgroup per
+// unit, the partial sums of 2048 tokens at 4096 x 4096 x 3 were 56 MB written and
+// read back: 43 us and a 10.8 us reduce launch). An adapter of few tokens or none
+// gives each wave a column tile instead, which keeps its sum in LDS (a bank's
+// unused adapters only have zeros to write): 256 adapters in runs of 512 tokens
+// 150 us, 199 with every workgroup on one tile. Which of the two follows from the
+// adapter's own tokens, whatever the size of the bank: 2048 tokens of one adapter
+// of 64 take 76 us (128 with the waves per tile chosen by the bank's tokens per
+// adapter), and 33 at 1024 x 1024 (103).
+//
+// Spans of 2048 tokens: one workgroup over all of an adapter's tokens left the
+// chip idle where the columns are few (32768 tokens of one adapter at 256 x 256 x 3:
+// 24 workgroups, 257 us). The sums of an adapter of several spans go through
+// memory, in 2048-token pieces, and a reduce launch adds them in order. Units
+// are added in order within a span and spans in order, whatever the launch.
 struct OuterArgs {
   const uint16_t* V[kGrJobs];
   const float* S[kGrJobs];  // low-rank products [T][r_max], unscaled
   float* out[kGrJobs];
+  float* part[kGrJobs];     // sums of the spans of adapters with several
   int64_t P[kGrJobs];
   const int32_t* ranks[kGrJobs];  // the projection's ranks, or NULL
-  const int32_t *perm, *seg;
-  const float* pscale;  // scales in the order of perm
-  int64_t tiles;  // column-tile groups of the widest job
+  Buckets bk;
+  int n_jobs, n_ad;
+  int tiles4;     // groups of four column tiles of the widest job
+  int max_spans;  // items of spans; those of adapters of few tokens follow
   int r_max;
 };
 
@@ -281,14 +337,13 @@ constexpr int kGrWaves = kGrThreads / kWave;
 constexpr int kGrCols = 4;  // columns per lane (E below)
 constexpr float kUp = 0x1p24f, kDown = 0x1p-24f;
 
-template <int JT, int UW>
+template <int JT>
 __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) {
   constexpr int E = kGrCols;
-  static_assert(JT * E % UW == 0, "sums per thread");
-  constexpr int CT = kGrWaves / UW;
   constexpr int RJ = 16 * JT, CW = 16 * E;  // rank rows and columns of a tile
   constexpr int kLaneTok = kGrUnit / 4;  // tokens of a unit in a lane's group
-  constexpr int kSums = JT * E / UW;        // f32x4 of sums per thread
+  constexpr int kSums = JT * E / kGrWaves;  // f32x4 of sums per thread
+  static_assert(JT * E % kGrWaves == 0, "sums per thread");
   // a wave's tile in LDS: [RJ][CW + 4] for dA, [CW][RJ + 4] for dB
   constexpr int TILE_A = RJ * (CW + 4), TILE_B = CW * (RJ + 4);
   constexpr int TILE = TILE_A > TILE_B ? TILE_A : TILE_B;
@@ -298,22 +353,55 @@ __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) 
   __shared__ float tf[kGrWaves];  // what undoes that in a wave's tile
   using RowT = u32x2;
 
-  const int job = blockIdx.y, jbase = 64 * blockIdx.z;  // ranks above 64: 64 rows at a time
+  // The workgroup's item: a span, or (`single`) an adapter of few tokens, four of
+  // these in place of one span. Items vary slowest, so that those that turn out
+  // empty come after those with work: between them they would leave the work
+  // unevenly over the compute units (2048 tokens of one adapter 24.5 -> 29 us).
+  // Every branch is uniform.
+  const int jx = blockIdx.y, n_jobs = args.n_jobs;
+  const int jbase = jx < n_jobs ? 0 : 64;  // ranks above 64: 64 rows at a time
+  const int job = jx < n_jobs ? jx : jx - n_jobs;
+  const bool single = static_cast<int>(blockIdx.z) >= args.max_spans;
+  const int waves = single ? 1 : kGrWaves;  // that share a tile
+  int i = blockIdx.z, tg = blockIdx.x;      // the span or adapter; its (group of) column tiles
+  if (single) {
+    const int t4 = args.tiles4, q = (tg >= t4) + (tg >= 2 * t4) + (tg >= 3 * t4);
+    i = kGrWaves * (i - args.max_spans) + q;
+    tg -= q * t4;
+    if (i >= args.n_ad) return;
+  }
+
   const int64_t P = args.P[job];
   const int r_max = args.r_max;
-  const int a = static_cast<int>(blockIdx.x / args.tiles);
-  const int64_t tg = blockIdx.x % args.tiles;
-  if (tg * CT * CW >= P) return;  // uniform: the whole group is past P
   const int tid = threadIdx.x, lane = tid % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int ct = wave / UW, uw = wave % UW;
   const int n = lane % 16, k = lane / 16;
-  const int64_t wcol = (tg * CT + ct) * CW;  // the tile's first column
-  const int64_t col = wcol + E * n;          // this lane's columns
+  // its tokens [s0, s0 + count) of adapter a, the wave's column tile and first
+  // unit, and where the result goes
+  const int64_t wcol = static_cast<int64_t>(single ? tg * kGrWaves + wave : tg) * CW;
+  const int uw = single ? 0 : wave;
+  int a, s0, count;
+  float* out = args.out[job];
+  if (single) {
+    a = i;
+    s0 = args.bk.seg[i];
+    count = args.bk.seg[i + 1] - s0;
+    if (count > args.bk.few || static_cast<int64_t>(tg) * kGrWaves * CW >= P) return;
+    out += static_cast<int64_t>(a) * P * r_max;
+  } else {
+    const int n_spans = args.bk.n_list[0];
+    const i32x4 e = args.bk.spans[i];  // (beside the count: not one after the other)
+    if (i >= n_spans || wcol >= P) return;
+    a = e[0];
+    s0 = e[1];
+    count = e[2];
+    out = e[3] ? out + static_cast<int64_t>(a) * P * r_max
+               : args.part[job] + static_cast<int64_t>(i) * P * r_max;
+  }
+  const int64_t col = wcol + E * n;  // this lane's columns
   const bool live = col < P;
   const int32_t* ranks = args.ranks[job];
   const int rk = ranks ? min(max(ranks[a], 0), r_max) : r_max;
-  const int s0 = args.seg[a], count = args.seg[a + 1] - s0;
   const int units = (count + kGrUnit - 1) / kGrUnit;
   const uint16_t* V = args.V[job];
   const float* S = args.S[job];
@@ -321,10 +409,8 @@ __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) 
   f32x4 sum[kSums];
 #pragma unroll
   for (int q = 0; q < kSums; ++q) sum[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // thread item q of the tile: 4 consecutive floats of the output order
-  const int it0 = uw * kWave + lane;
-  auto lds_at = [&](int w, int q) {
-    const int e = 4 * (it0 + q * UW * kWave);
+  // 4 consecutive floats of a tile from element e of the output order on
+  auto lds_at = [&](int w, int e) {
     if (job & 1) return &tl[w][(e / CW) * (CW + 4) + e % CW];
     return &tl[w][(e / RJ) * (RJ + 4) + e % RJ];
   };
@@ -335,8 +421,8 @@ __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) 
     const int left = count - kGrUnit * (u0 + uw);
     if (left <= 0) return;
     const int at = s0 + kGrUnit * (u0 + uw) + min(lane, left - 1);
-    *tk = args.perm[at];
-    *ts = args.pscale[at];
+    *tk = args.bk.perm[at];
+    *ts = args.bk.pscale[at];
   };
   auto put_tokens = [&](int slot, int tk, float ts) {
     tok[wave][slot][lane] = tk;
@@ -371,24 +457,23 @@ __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) 
   if (uw < units) {
     unit_tokens(0, &tk, &ts);
     put_tokens(0, tk, ts);
-    unit_tokens(UW, &tk, &ts);
+    unit_tokens(waves, &tk, &ts);
     load_half(0, 0);
     load_half(0, 1);
   }
-  for (int u0 = 0; u0 < units; u0 += UW) {
+  for (int u0 = 0, slot = 0; u0 < units; u0 += waves, slot ^= 1) {
     const int unit = u0 + uw;
     if (unit < units) {
       const int nt = min(kGrUnit, count - kGrUnit * unit);
-      const int slot = (u0 / UW) & 1;
       f32x4 acc[JT][E];
 #pragma unroll
       for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[jt][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-      const bool more = unit + UW < units;  // uniform
+      const bool more = unit + waves < units;  // uniform
       if (more) {
         put_tokens(slot ^ 1, tk, ts);
-        unit_tokens(u0 + 2 * UW, &tk, &ts);
+        unit_tokens(u0 + 2 * waves, &tk, &ts);
       }
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -452,12 +537,12 @@ __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) 
 #pragma unroll
           for (int i = 0; i < 4; ++i) zero[i] += acc[jt][e][i] * 0.f;
       const float all = (zero[0] + zero[1]) + (zero[2] + zero[3]);
-      if (lane == 0) tf[wave] = kDown;
+      float down = kDown;
       if (__any(all != all)) {
         // a value of the unit is not finite (the parts of a coefficient then
         // mix infinities with zeros) or too large to scale, so the unit runs
         // again as float32 products (16x16x4: lane l gives token l / 16)
-        if (lane == 0) tf[wave] = 1.f;
+        down = 1.f;
 #pragma unroll
         for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
@@ -466,7 +551,7 @@ __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) 
         for (int i = k; i < kGrUnit; i += 4) {
           const bool in = i < nt;
           const int64_t t = tok[wave][slot][i];
-          const float st = args.pscale[s0 + kGrUnit * unit + min(i, nt - 1)];
+          const float st = args.bk.pscale[s0 + kGrUnit * unit + min(i, nt - 1)];
           const RowT r = ld_global<RowT>(Vc + t * P);
 #pragma unroll
           for (int jt = 0; jt < JT; ++jt) {
@@ -480,7 +565,16 @@ __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) 
           }
         }
       }
+      if (lane == 0) tf[wave] = down;
       float* w = tl[wave];
+      // a wave that has the tile alone keeps the sum there
+      auto put = [&](float* p, f32x4 v) {
+        if (single) {
+          v *= down;
+          if (u0) v += *reinterpret_cast<const f32x4*>(p);
+        }
+        *reinterpret_cast<f32x4*>(p) = v;
+      };
 #pragma unroll
       for (int jt = 0; jt < JT; ++jt) {
         const int j0 = 16 * jt + 4 * k;  // this lane's rows j0 .. j0 + 3
@@ -489,74 +583,98 @@ __global__ __launch_bounds__(kGrThreads) void grad_outer_kernel(OuterArgs args) 
           for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int e = 0; e < E; e += 4)
-              *reinterpret_cast<f32x4*>(w + (j0 + i) * (CW + 4) + E * n + e) =
-                  f32x4{acc[jt][e][i], acc[jt][e + 1][i], acc[jt][e + 2][i], acc[jt][e + 3][i]};
+              put(w + (j0 + i) * (CW + 4) + E * n + e,
+                  f32x4{acc[jt][e][i], acc[jt][e + 1][i], acc[jt][e + 2][i], acc[jt][e + 3][i]});
         } else {
 #pragma unroll
           for (int e = 0; e < E; ++e)
-            *reinterpret_cast<f32x4*>(w + (E * n + e) * (RJ + 4) + j0) = acc[jt][e];
+            put(w + (E * n + e) * (RJ + 4) + j0, acc[jt][e]);
         }
       }
     }
     __syncthreads();
+    if (single) continue;
 #pragma unroll
-    for (int v = 0; v < UW; ++v)
+    for (int v = 0; v < kGrWaves; ++v)
       if (u0 + v < units) {
-        const float f = tf[ct * UW + v];
+        const float f = tf[v];
 #pragma unroll
         for (int q = 0; q < kSums; ++q)
-          sum[q] += *reinterpret_cast<const f32x4*>(lds_at(ct * UW + v, q)) * f;
+          sum[q] += *reinterpret_cast<const f32x4*>(lds_at(v, 4 * (tid + q * kGrThreads))) * f;
       }
-    if (u0 + UW < units) __syncthreads();  // the tiles are rewritten by the next round
+    if (u0 + waves < units) __syncthreads();  // the tiles are rewritten by the next round
   }
 
   // out: zero at or past the rank (and for an adapter without tokens)
-  float* out = args.out[job] + static_cast<int64_t>(a) * P * r_max;
-#pragma unroll
-  for (int q = 0; q < kSums; ++q) {
-    const int e = 4 * (it0 + q * UW * kWave);
+  auto store = [&](int e, f32x4 v) {
     if (job & 1) {
       const int j = jbase + e / CW;
       const int64_t p = wcol + e % CW;
       if (j < r_max && p < P)
         *reinterpret_cast<f32x4*>(out + static_cast<int64_t>(j) * P + p) =
-            j < rk ? sum[q] : f32x4{0.f, 0.f, 0.f, 0.f};
+            j < rk ? v : f32x4{0.f, 0.f, 0.f, 0.f};
     } else {
       const int j = jbase + e % RJ;
       const int64_t p = wcol + e / RJ;
       if (j < r_max && p < P) {
-        f32x4 v = sum[q];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           if (j + i >= rk) v[i] = 0.f;
         *reinterpret_cast<f32x4*>(out + p * r_max + j) = v;
       }
     }
+  };
+  if (single) {  // each wave its own tile
+#pragma unroll
+    for (int q = 0; q < JT * E; ++q) {
+      const int e = 4 * (lane + q * kWave);
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      if (units) v = *reinterpret_cast<const f32x4*>(lds_at(wave, e));
+      store(e, v);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < kSums; ++q) store(4 * (tid + q * kGrThreads), sum[q]);
   }
 }
 
-template <int JT, int UW>
-local_status_t launch_outer_uw(OuterArgs o, int n_jobs, int n_ad, hipStream_t s) {
-  int64_t pmax = 0;
-  for (int q = 0; q < n_jobs; ++q) pmax = std::max(pmax, o.P[q]);
-  constexpr int64_t cols = 16 * kGrCols * (kGrWaves / UW);
-  o.tiles = (pmax + cols - 1) / cols;
-  const unsigned jz = static_cast<unsigned>((o.r_max + 63) / 64);
-  grad_outer_kernel<JT, UW>
-      <<<dim3(static_cast<unsigned>(n_ad * o.tiles), static_cast<unsigned>(n_jobs), jz), kGrThreads,
-         0, s>>>(o);
-  return local_check_launch("lora_grad (outer)");
+// The sums of an adapter's spans, added in order.
+__global__ __launch_bounds__(kGrThreads) void grad_reduce_kernel(OuterArgs args) {
+  if (static_cast<int>(blockIdx.y) >= args.bk.n_list[1]) return;
+  const i32x4 l = args.bk.longs[blockIdx.y];
+  const int job = blockIdx.z;
+  const int64_t elems = args.P[job] * args.r_max;
+  const int64_t e = 4 * (static_cast<int64_t>(blockIdx.x) * kGrThreads + threadIdx.x);
+  if (e >= elems) return;
+  const float* p = args.part[job] + l[1] * elems + e;
+  f32x4 v = *reinterpret_cast<const f32x4*>(p);
+  for (int i = 1; i < l[2]; ++i) v += *reinterpret_cast<const f32x4*>(p + i * elems);
+  *reinterpret_cast<f32x4*>(args.out[job] + l[0] * elems + e) = v;
 }
 
-// Waves per column tile: enough for the mean number of 64-token units of an
-// adapter (a wave without a unit idles; a unit without a wave waits a round).
 template <int JT>
-local_status_t launch_outer_jt(const OuterArgs& o, int n_jobs, int64_t T, int n_ad,
-                               hipStream_t s) {
-  const int64_t units = (T + kGrUnit - 1) / kGrUnit;
-  if (units > n_ad) return launch_outer_uw<JT, 4>(o, n_jobs, n_ad, s);
-  if (2 * units > n_ad) return launch_outer_uw<JT, 2>(o, n_jobs, n_ad, s);
-  return launch_outer_uw<JT, 1>(o, n_jobs, n_ad, s);
+local_status_t launch_outer_jt(OuterArgs o, int n_jobs, int64_t T, int n_ad, hipStream_t s) {
+  int64_t pmax = 0;
+  for (int q = 0; q < n_jobs; ++q) pmax = std::max(pmax, o.P[q]);
+  constexpr int64_t cols = 16 * kGrCols;
+  o.tiles4 = static_cast<int>((pmax + kGrWaves * cols - 1) / (kGrWaves * cols));
+  o.n_jobs = n_jobs;
+  o.n_ad = n_ad;
+  o.max_spans = static_cast<int>(max_spans(T, n_ad));
+  const dim3 grid(static_cast<unsigned>(kGrWaves * o.tiles4),
+                  static_cast<unsigned>(n_jobs * ((o.r_max + 63) / 64)),
+                  static_cast<unsigned>(o.max_spans + (n_ad + kGrWaves - 1) / kGrWaves));
+  if (grid.z > 65535)
+    return local_fail(LOCAL_ERR_UNSUPPORTED, "lora_grad: T=%lld", (long long)T);
+  grad_outer_kernel<JT><<<grid, kGrThreads, 0, s>>>(o);
+  const local_status_t st = local_check_launch("lora_grad (outer)");
+  const int64_t longs = max_long(T, n_ad);
+  if (st != LOCAL_OK || longs == 0) return st;
+  const int64_t threads = pmax * o.r_max / 4;
+  grad_reduce_kernel<<<dim3(static_cast<unsigned>((threads + kGrThreads - 1) / kGrThreads),
+                            static_cast<unsigned>(longs), static_cast<unsigned>(n_jobs)),
+                       kGrThreads, 0, s>>>(o);
+  return local_check_launch("lora_grad (reduce)");
 }
 
 local_status_t launch_outer(const OuterArgs& o, int n_jobs, int64_t T, int n_ad,
@@ -601,8 +719,8 @@ local_status_t grad_impl(const char* who, const uint16_t* x, int64_t T, int64_t 
   for (int g = 0; g < G; ++g)
     if ((st = grad_checks(who, T, K, N[g], n_adapters, r_max)) != LOCAL_OK) return st;
   const int64_t Tw = T > 0 ? T : 1;
-  // workspace: token order, adapter offsets, B_g^T, the low-rank products u_g
-  // and dy_g B_g
+  // workspace: token order, adapter offsets, the lists of spans, B_g^T, the
+  // low-rank products u_g and dy_g B_g, the sums of spans
   size_t o = 0;
   auto take = [&](size_t bytes) {
     const size_t at = o;
@@ -612,11 +730,17 @@ local_status_t grad_impl(const char* who, const uint16_t* x, int64_t T, int64_t 
   const size_t o_perm = take(static_cast<size_t>(Tw) * 4);
   const size_t o_psc = take(static_cast<size_t>(Tw) * 4);
   const size_t o_seg = take(static_cast<size_t>(n_adapters + 1) * 4);
-  size_t o_bt[kGrGroup], o_u[kGrGroup], o_g[kGrGroup];
+  const size_t o_list = take(2 * sizeof(int32_t));
+  const int64_t n_spans = max_spans(Tw, n_adapters), n_longs = max_long(Tw, n_adapters);
+  const size_t o_spans = take(static_cast<size_t>(n_spans) * sizeof(i32x4));
+  const size_t o_longs = take(static_cast<size_t>(n_longs) * sizeof(i32x4));
+  size_t o_bt[kGrGroup], o_u[kGrGroup], o_g[kGrGroup], o_pb[kGrGroup], o_pa[kGrGroup];
   for (int g = 0; g < G; ++g) {
     o_bt[g] = take(static_cast<size_t>(n_adapters) * r_max * N[g] * 2);
     o_u[g] = take(static_cast<size_t>(Tw) * r_max * 4);
     o_g[g] = take(static_cast<size_t>(Tw) * r_max * 4);
+    o_pb[g] = take(n_longs > 0 ? static_cast<size_t>(n_spans) * N[g] * r_max * 4 : 0);
+    o_pa[g] = take(n_longs > 0 ? static_cast<size_t>(n_spans) * K * r_max * 4 : 0);
   }
   // The size is the one that callers have always been told, which these parts
   // fit: token order, two lists of adapter offsets, 16 bytes for each of at
@@ -649,8 +773,6 @@ local_status_t grad_impl(const char* who, const uint16_t* x, int64_t T, int64_t 
   if (T > 0 && (!x || !adapter_idx || !scale))
     return local_fail(LOCAL_ERR_NULL, "%s: NULL pointer argument", who);
   char* w = static_cast<char*>(ws);
-  int32_t* perm = reinterpret_cast<int32_t*>(w + o_perm);
-  int32_t* seg = reinterpret_cast<int32_t*>(w + o_seg);
   const uint16_t* Bt[kGrGroup];
   // tokens bucketed by adapter and every B_g transposed per adapter to
   // [r_max][N_g], in one launch. T = 0: every adapter is empty and the outer
@@ -666,9 +788,10 @@ local_status_t grad_impl(const char* who, const uint16_t* x, int64_t T, int64_t 
   pr.T = T;
   pr.n_ad = n_adapters;
   pr.scale = scale;
-  pr.perm = perm;
-  pr.pscale = reinterpret_cast<float*>(w + o_psc);
-  pr.seg = seg;
+  pr.bk = Buckets{reinterpret_cast<int32_t*>(w + o_perm), reinterpret_cast<float*>(w + o_psc),
+                  reinterpret_cast<int32_t*>(w + o_seg), reinterpret_cast<int32_t*>(w + o_list),
+                  reinterpret_cast<i32x4*>(w + o_spans), reinterpret_cast<i32x4*>(w + o_longs),
+                  few_tokens(Tw, n_adapters)};
   if ((st = run_prep(s, pr)) != LOCAL_OK) return st;
   if (T > 0) {  // u_g = x A_g^T and dy_g B_g, one launch
     ShrinkJob jobs[kGrJobs];
@@ -689,15 +812,15 @@ local_status_t grad_impl(const char* who, const uint16_t* x, int64_t T, int64_t 
     oa.out[2 * g] = dB[g];
     oa.P[2 * g] = N[g];
     oa.ranks[2 * g] = rg;
+    oa.part[2 * g] = reinterpret_cast<float*>(w + o_pb[g]);
+    oa.part[2 * g + 1] = reinterpret_cast<float*>(w + o_pa[g]);
     oa.V[2 * g + 1] = x;
     oa.S[2 * g + 1] = reinterpret_cast<const float*>(w + o_g[g]);
     oa.out[2 * g + 1] = dA[g];
     oa.P[2 * g + 1] = K;
     oa.ranks[2 * g + 1] = rg;
   }
-  oa.perm = perm;
-  oa.seg = seg;
-  oa.pscale = pr.pscale;
+  oa.bk = pr.bk;
   oa.r_max = r_max;
   return launch_outer(oa, 2 * G, T, n_adapters, s);
 }

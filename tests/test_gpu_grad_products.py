@@ -1,7 +1,7 @@
 """The adapter gradients at the edges of their tiles: 16-token shrink tiles,
-64-token units, one to four waves per column tile, column tiles that end
-inside a wave, ranks on both sides of every rank tile, K slices of a wave that
-are empty, and values that are not finite.
+64-token units, adapters of one unit and of several, spans of 2048 tokens, column
+tiles that end inside a wave, ranks on both sides of every rank tile, K slices of
+a wave that are empty, and values that are not finite.
 
 Against plain float64. The bound is that of float32 sums: a gradient entry is
 a sum of at most T products with u (or dy B), itself a sum of at most D = K or
@@ -52,7 +52,8 @@ def _reference(x, dy, A, B, ranks, idx, scale, cast):
 
 CASES = [(1, 64, 64, 1, 8), (15, 64, 192, 2, 16), (16, 128, 64, 1, 24), (17, 192, 128, 3, 32),
          (63, 320, 64, 1, 40), (64, 256, 64, 64, 8), (65, 256, 192, 1, 64), (257, 128, 256, 1, 72),
-         (300, 192, 320, 9, 128), (700, 64, 128, 3, 16), (1030, 128, 64, 1, 16)]
+         (300, 192, 320, 9, 128), (700, 64, 128, 3, 16), (1030, 128, 64, 1, 16),
+         (4030, 64, 128, 1, 8), (4200, 192, 64, 1, 24), (6700, 64, 64, 2, 72)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "T%d_K%d_N%d_ad%d_r%d" % c)
@@ -65,6 +66,20 @@ def test_edges_against_float64(case):
     mag = _reference(*inp, cast=lambda t: t.double().abs())
     for g, r, m, D in zip(got, ref, mag, (N, K)):
         assert torch.all((g.double() - r).abs() <= (T + D + 8) * 2.0 ** -24 * m)
+
+
+@pytest.mark.parametrize("T", [1, 64, 65, 128, 2048, 2049, 4100])
+def test_size_of_the_bank_does_not_matter(T):
+    # one adapter's tokens, alone and in a bank of 70: the same bits, zeros elsewhere
+    say("grad products, one adapter of a bank", T)
+    x, dy, A, B, ranks, idx, scale = _inputs(T, 128, 64, 70, 16, T)
+    idx[:] = 33
+    dA, dB = _run(x, dy, A, B, ranks, idx, scale)
+    one = slice(33, 34)
+    dA1, dB1 = _run(x, dy, A[one], B[one], ranks[one], idx - 33, scale)
+    assert torch.equal(dA[one], dA1) and torch.equal(dB[one], dB1)
+    for d in (dA, dB):
+        assert not d[:33].any() and not d[34:].any()
 
 
 @pytest.mark.parametrize("where", ["x", "dy", "scale"])
