@@ -3,26 +3,34 @@
 // (u = x A^T and dy B), for several (x, A) pairs in one launch.
 //
 // Bound by the reads of x and A (2 r flop per byte). A workgroup takes 16
-// tokens and one pair; its waves cut K between them, so that no partial sum
-// leaves the compute unit (with few tiles K is also cut into slices, each its
-// own workgroups and output, which the reader adds in order). Each wave streams its K slice of the 16 token rows
-// and of 16 RT adapter rows through a ring of its own in LDS (64 k a stage,
-// no barrier in the loop) and runs S^T = A X^T on the matrix cores; the
-// waves' tiles are added through LDS in wave order. Direct global-to-LDS
-// loads, because the matrix-core lane layout (16 rows side by side) is the
-// one the load path cannot merge. The six products of a q/k/v backward (2048
-// tokens, 4096 x 4096, rank 16; 196 MB out of the caches): 23.4 us, 38.0 us
-// with the operands loaded straight into registers, 41 us as four launches of
-// the K-sliced shrink whose slices the reader summed. Tokens of other adapters
-// in the tile are computed and dropped: adapters come in runs (a request's
-// chunk), so a tile rarely holds more than two.
+// tokens of one adapter and one pair; its waves cut K between them, so that no
+// partial sum leaves the compute unit (with few tiles K is also cut into slices,
+// each its own workgroups and output, which the reader adds in order). Each wave
+// streams its K slice of the 16 token rows and of 16 RT adapter rows through a
+// ring of its own in LDS (64 k a stage, no barrier in the loop) and runs
+// S^T = A X^T on the matrix cores; the waves' tiles are added through LDS in wave
+// order. Direct global-to-LDS loads, because the matrix-core lane layout (16 rows
+// side by side) is the one the load path cannot merge. The six products of a
+// q/k/v backward (2048 tokens, 4096 x 4096, rank 16; 196 MB out of the caches):
+// 22 to 27 us, 38 us with the operands loaded straight into registers, 41 us as
+// four launches of a K-sliced shrink whose slices the reader summed.
+//
+// The tiles are gathered from groups of 64 tokens, adapter by adapter in the
+// order of their first tokens, four workgroups a group (tile i to workgroup
+// i % 4). Requests' chunks (runs of one adapter) make four full tiles, as 16
+// tokens in order would; with an adapter per token, 16 tokens in order hold up
+// to 16 adapters and stream x and A again for each: q, k and v of 2048 tokens at
+// 4096 x 4096 / 1024 / 1024 over 8 adapters at random 156 -> 122 us a call. A sum
+// does not depend on the tile that it is formed in.
 #include "common.hpp"
 #include "lora_internal.hpp"
 
 namespace localk {
 namespace {
 
-constexpr int kSkTokens = 16;
+constexpr int kSkTokens = 16;  // tokens of a tile
+constexpr int kSkGroup = kWave;  // tokens that tiles are gathered from
+constexpr int kSkSplit = kSkGroup / kSkTokens;  // workgroups of a group
 
 struct SkArgs {
   ShrinkJob job[kShrinkJobs];
@@ -64,11 +72,11 @@ __global__ __launch_bounds__(SK::W * kWave) void token_shrink_kernel(SkArgs a) {
     return reinterpret_cast<f32x4*>(sk_lds + w * S * SK::STAGE) + rt * kWave + lane;
   };
   const int z = static_cast<int>(blockIdx.x) % a.ks;
-  const int64_t t0 = static_cast<int64_t>(blockIdx.x / a.ks) * kSkTokens;
-  const int64_t t = t0 + col;
+  const int wg = static_cast<int>(blockIdx.x) / a.ks, sub = wg % kSkSplit;
+  const int64_t t0 = static_cast<int64_t>(wg / kSkSplit) * kSkGroup;
   const ShrinkJob& jb = a.job[blockIdx.y];
 
-  int my = t < a.T ? a.idx[t] : -1;
+  int my = t0 + lane < a.T ? a.idx[t0 + lane] : -1;  // the adapter of the group's token `lane`
   if (my < 0 || my >= a.n_ad) my = -1;
   // the wave's 64-k steps [s_lo, s_lo + n)
   const int64_t K = jb.K;
@@ -79,85 +87,100 @@ __global__ __launch_bounds__(SK::W * kWave) void token_shrink_kernel(SkArgs a) {
   // position l % 8, which holds chunk (l % 8) ^ (l / 8) of that row
   const int lrow = lane / 8;
   const int64_t loff = 64 * static_cast<int64_t>(s_lo) + 8 * ((lane % 8) ^ lrow);
-  const uint16_t* xs[2];
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int64_t tr = t0 + 8 * q + lrow;  // rows past T repeat row t0, never stored
-    xs[q] = jb.x + (tr < a.T ? tr : t0) * K + loff;
-  }
   const int rd0 = col * 128 + 16 * (kgrp ^ (col % 8));
 
-  uint64_t pending = __ballot(my >= 0) & 0xffffull;
   if (a.zero16 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && tid < 8)
     a.zero16[tid] = 0;
   const int j0 = 16 * RT * blockIdx.z;
   bool again = false;
-  while (pending) {
+  int first = 0;  // the adapter's first tile of the group
+  for (uint64_t pending = __ballot(my >= 0); pending;) {
     const int ad = __builtin_amdgcn_readlane(my, __ffsll(static_cast<long long>(pending)) - 1);
-    pending &= ~__ballot(my == ad);
-    if (again) __syncthreads();  // the previous adapter's tiles have been read
-    again = true;
-    const uint16_t* as[2 * RT];
+    const uint64_t m = __ballot(my == ad);
+    pending &= ~m;
+    const int cnt = __popcll(m);
+    // the group's tokens in the order: this adapter's, then the others'
+    const int below = __builtin_amdgcn_mbcnt_hi(
+        static_cast<uint32_t>(m >> 32),
+        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+    const int order =
+        __builtin_amdgcn_ds_permute(4 * (my == ad ? below : cnt + lane - below), lane);
+    const int tile0 = first;
+    first += (cnt + kSkTokens - 1) / kSkTokens;
+    for (int i = (sub - tile0) & (kSkSplit - 1); kSkTokens * i < cnt; i += kSkSplit) {
+      if (again) __syncthreads();  // the previous tile's sums have been read
+      again = true;
+      // token c of the tile (past the last one: that again, never stored)
+      const int left = cnt - kSkTokens * i;
+      auto token = [&](int c) {
+        return t0 + __shfl(order, kSkTokens * i + min(c, left - 1));
+      };
+      const int64_t t = token(col);
+      const uint16_t* xs[2];
 #pragma unroll
-    for (int q = 0; q < 2 * RT; ++q) {  // rows past r_max repeat its last, never stored
-      const int j = min(j0 + 8 * q + lrow, a.r_max - 1);
-      as[q] = jb.A + (static_cast<int64_t>(ad) * a.r_max + j) * K + loff;
-    }
-    auto issue = [&](int s) {
-      uint8_t* st = ring + (s % S) * SK::STAGE;
-      const int64_t k = 64 * static_cast<int64_t>(s);
+      for (int q = 0; q < 2; ++q) xs[q] = jb.x + token(8 * q + lrow) * K + loff;
+      const uint16_t* as[2 * RT];
 #pragma unroll
-      for (int q = 0; q < 2; ++q) sk_load16(xs[q] + k, st + 1024 * q);
-#pragma unroll
-      for (int q = 0; q < 2 * RT; ++q) sk_load16(as[q] + k, st + 2048 + 1024 * q);
-    };
-    f32x4 acc[2][RT];  // the two halves of the steps apart: shorter sums
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) acc[0][rt] = acc[1][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < min(S - 1, n); ++s) issue(s);
-    for (int s = 0; s < n; ++s) {
-      // stage s % S has landed; stage (s - 1) % S was read before the last
-      // step's products, so the loads of step s + S - 1 may refill it
-      if (s + S - 1 < n) {
-        sk_wait_loads<D * (S - 2)>();
-        issue(s + S - 1);
-      } else {
-        sk_wait_loads<0>();
+      for (int q = 0; q < 2 * RT; ++q) {  // rows past r_max repeat its last, never stored
+        const int j = min(j0 + 8 * q + lrow, a.r_max - 1);
+        as[q] = jb.A + (static_cast<int64_t>(ad) * a.r_max + j) * K + loff;
       }
-      const uint8_t* st = ring + (s % S) * SK::STAGE;
-      u32x4 xf[2], af[2][RT];
+      auto issue = [&](int s) {
+        uint8_t* st = ring + (s % S) * SK::STAGE;
+        const int64_t k = 64 * static_cast<int64_t>(s);
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        xf[m] = *reinterpret_cast<const u32x4*>(st + (rd0 ^ (64 * m)));
+        for (int q = 0; q < 2; ++q) sk_load16(xs[q] + k, st + 1024 * q);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-          af[m][rt] = *reinterpret_cast<const u32x4*>(st + 2048 * (1 + rt) + (rd0 ^ (64 * m)));
+        for (int q = 0; q < 2 * RT; ++q) sk_load16(as[q] + k, st + 2048 + 1024 * q);
+      };
+      f32x4 acc[2][RT];  // the two halves of the steps apart: shorter sums
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) acc[0][rt] = acc[1][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int s = 0; s < min(S - 1, n); ++s) issue(s);
+      for (int s = 0; s < n; ++s) {
+        // stage s % S has landed; stage (s - 1) % S was read before the last
+        // step's products, so the loads of step s + S - 1 may refill it
+        if (s + S - 1 < n) {
+          sk_wait_loads<D * (S - 2)>();
+          issue(s + S - 1);
+        } else {
+          sk_wait_loads<0>();
+        }
+        const uint8_t* st = ring + (s % S) * SK::STAGE;
+        u32x4 xf[2], af[2][RT];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          xf[m] = *reinterpret_cast<const u32x4*>(st + (rd0 ^ (64 * m)));
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+            af[m][rt] = *reinterpret_cast<const u32x4*>(st + 2048 * (1 + rt) + (rd0 ^ (64 * m)));
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+            acc[m][rt] = mfma16x16x32(as_bf16x8(af[m][rt]), as_bf16x8(xf[m]), acc[m][rt]);
       }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-      for (int m = 0; m < 2; ++m)
+      for (int rt = 0; rt < RT; ++rt) *red(wave, rt) = acc[0][rt] + acc[1][rt];
+      __syncthreads();
+      for (int rt = wave; rt < RT; rt += W) {
+        f32x4 v = *red(0, rt);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-          acc[m][rt] = mfma16x16x32(as_bf16x8(af[m][rt]), as_bf16x8(xf[m]), acc[m][rt]);
-    }
+        for (int w = 1; w < W; ++w) v += *red(w, rt);
+        const int j = j0 + 16 * rt + 4 * kgrp;
+        if (col >= left || j >= a.r_max) continue;
+        if (jb.u) {
+          *reinterpret_cast<f32x4*>(jb.u + (z * a.T + t) * a.r_max + j) = v;
+        } else {
+          const int rk = jb.ranks ? jb.ranks[ad] : a.r_max;
+          const float sc = a.scale[t];
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) *red(wave, rt) = acc[0][rt] + acc[1][rt];
-    __syncthreads();
-    for (int rt = wave; rt < RT; rt += W) {
-      f32x4 v = *red(0, rt);
-#pragma unroll
-      for (int w = 1; w < W; ++w) v += *red(w, rt);
-      const int j = j0 + 16 * rt + 4 * kgrp;
-      if (my != ad || j >= a.r_max) continue;
-      if (jb.u) {
-        *reinterpret_cast<f32x4*>(jb.u + (z * a.T + t) * a.r_max + j) = v;
-      } else {
-        const int rk = jb.ranks ? jb.ranks[ad] : a.r_max;
-        const float sc = a.scale[t];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = j + q < rk ? sc * v[q] : 0.f;
-        *reinterpret_cast<u32x2*>(jb.us + t * a.r_max + j) =
-            u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+          for (int q = 0; q < 4; ++q) v[q] = j + q < rk ? sc * v[q] : 0.f;
+          *reinterpret_cast<u32x2*>(jb.us + t * a.r_max + j) =
+              u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+        }
       }
     }
   }
@@ -171,7 +194,7 @@ local_status_t launch_sk(const SkArgs& a, int n_jobs, hipStream_t s) {
                               hipFuncAttributeMaxDynamicSharedMemorySize, SK::LDS);
     done = true;
   }
-  const dim3 grid(static_cast<unsigned>((a.T + kSkTokens - 1) / kSkTokens * a.ks),
+  const dim3 grid(static_cast<unsigned>((a.T + kSkGroup - 1) / kSkGroup * kSkSplit * a.ks),
                   static_cast<unsigned>(n_jobs),
                   static_cast<unsigned>((a.r_max + 16 * SK::RT - 1) / (16 * SK::RT)));
   token_shrink_kernel<SK><<<grid, SK::W * kWave, SK::LDS, s>>>(a);

@@ -110,3 +110,29 @@ def test_tiles_against_float64(case, residual):
                 terms[t] += ua @ b.abs()
         bound = 2.0 ** -8 * (ref.abs() + delta) + (K + r_max + 4) * 2.0 ** -24 * terms
         assert torch.all((y.cpu().double() - ref).abs() <= 1.01 * bound)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T,n_ad", [(257, 1), (320, 3), (700, 70)])
+def test_order_of_the_tokens_does_not_matter(T, n_ad):
+    # the shrink gathers tokens of one adapter from groups of 64: runs of tokens and
+    # the same tokens in any order give the same bits
+    say("lora tiles, order of the tokens", T, n_ad)
+    g = torch.Generator().manual_seed(T)
+    K, N, r = 192, 128, 24
+    x = torch.randn(T, K, generator=g).bfloat16()
+    W = (torch.randn(N, K, generator=g) * 0.02).bfloat16()
+    A = torch.randn(n_ad, r, K, generator=g).bfloat16()
+    B = torch.randn(n_ad, N, r, generator=g).bfloat16()
+    idx = torch.randint(-1, n_ad, (T,), generator=g).sort().values.int()
+    scale = torch.rand(T, generator=g) + 0.5
+    ranks = torch.tensor([r - a % 20 for a in range(n_ad)], dtype=torch.int32)
+    rest = [t.cuda() for t in (W, A, B, ranks)]
+
+    def run(order):
+        return lk.local_lora_linear(x[order].cuda(), *rest, idx[order].cuda(),
+                                    scale[order].cuda()).cpu()
+
+    y = run(torch.arange(T))
+    mixed = torch.randperm(T, generator=g)
+    assert torch.equal(run(mixed).view(torch.int16), y[mixed].view(torch.int16))
