@@ -95,7 +95,6 @@ struct PrefillArgs {
   int B, Hq, Hkv, group, max_blocks;
   float scale_log2;  // |sm_scale| * log2(e)
   uint32_t q_sign;   // 0x80008000 when sm_scale < 0 (q's sign bits flipped), else 0
-  KeyRanges few;     // the key ranges of a call of few tiles
 };
 
 __device__ __forceinline__ bool id_ok(int p, int64_t num_blocks) {
@@ -209,19 +208,19 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 constexpr int kPlanThreads = 256;  // threads of the workgroup that plans the units
 template <bool FEW>
-__device__ void plan_units(const PrefillArgs& a);
+__device__ void plan_units(const PrefillArgs& a, const KeyRanges& few);
 
 // Append. Workgroup = (one block that request b's chunk writes, KV head g),
 // mapped from a 1D grid (heads fastest); the block's slots [lo, hi) are new
 // (positions P_b .. L_b - 1). Thread t handles slot t / (D/8), dims
 // 8 (t % (D/8)) .. +8.
 template <int D, bool FEW>
-__global__ __launch_bounds__(256) void prefill_append_kernel(PrefillArgs a) {
+__global__ __launch_bounds__(256) void prefill_append_kernel(PrefillArgs a, KeyRanges few) {
   constexpr int C8 = D / 8;
   __shared__ uint16_t vt[D][kBlockSize + 2];  // V of the block, dim-major (+2: banks)
   // workgroup 0 (dispatched first) plans the attention grid's units
   if (blockIdx.x == 0) {
-    plan_units<FEW>(a);
+    plan_units<FEW>(a, few);
     return;
   }
   const unsigned bid = blockIdx.x - 1;
@@ -331,7 +330,7 @@ __device__ __forceinline__ int tile_class(int nbl, int ns) {
 // may take the key ranges of few tiles (code of its own, since one workgroup runs
 // the planner from cold instruction caches).
 template <bool FEW>
-__device__ void plan_units(const PrefillArgs& a) {
+__device__ void plan_units(const PrefillArgs& a, const KeyRanges& few) {
   __shared__ int scan[kPaClasses][kPlanThreads];
   __shared__ int totals[kPaClasses];
   __shared__ int n_split_tiles, longest;
@@ -386,8 +385,8 @@ __device__ void plan_units(const PrefillArgs& a) {
       if (FEW) atomicMax(&longest, tile_blocks(P, n, (n - 1) / kPaRows, a.max_blocks));
     }
     __syncthreads();
-    if (!FEW || again || longest <= a.few.from || longest > a.few.upto) break;
-    kr = a.few;
+    if (!FEW || again || longest <= few.from || longest > few.upto) break;
+    kr = few;
     if (tid < kPaClasses) totals[tid] = 0;
     __syncthreads();
   }
@@ -453,8 +452,8 @@ __device__ void plan_units(const PrefillArgs& a) {
 
 // The planner alone, for calls without an append.
 template <bool FEW>
-__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PrefillArgs a) {
-  plan_units<FEW>(a);
+__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PrefillArgs a, KeyRanges few) {
+  plan_units<FEW>(a, few);
 }
 
 template <int D>
@@ -960,7 +959,8 @@ KeyRanges few_ranges(int64_t T, int B, int Hq, int D) {
 
 template <int D>
 local_status_t launch_prefill(const PrefillArgs& a, hipStream_t s) {
-  const bool maybe_few = a.few.from < a.max_blocks;  // no tile sees more
+  const KeyRanges few = few_ranges(a.T, a.B, a.Hq, D);
+  const bool maybe_few = few.from < a.max_blocks;  // no tile sees more
   static_assert(kPlanThreads >= 192, "one request per planner thread in calls of few tiles");
   if (a.k_new) {
     // a chunk of n rows spans at most n / 16 + 2 blocks: T / 16 + 2 B in all;
@@ -968,16 +968,16 @@ local_status_t launch_prefill(const PrefillArgs& a, hipStream_t s) {
     const int64_t units = a.T / kBlockSize + 2LL * a.B;
     const unsigned grid = static_cast<unsigned>(units * a.Hkv + 1);
     if (maybe_few)
-      prefill_append_kernel<D, true><<<grid, 256, 0, s>>>(a);
+      prefill_append_kernel<D, true><<<grid, 256, 0, s>>>(a, few);
     else
-      prefill_append_kernel<D, false><<<grid, 256, 0, s>>>(a);
+      prefill_append_kernel<D, false><<<grid, 256, 0, s>>>(a, few);
     local_status_t st = local_check_launch("paged_attn_prefill (append)");
     if (st != LOCAL_OK) return st;
   } else {
     if (maybe_few)
-      prefill_plan_kernel<true><<<1, kPlanThreads, 0, s>>>(a);
+      prefill_plan_kernel<true><<<1, kPlanThreads, 0, s>>>(a, few);
     else
-      prefill_plan_kernel<false><<<1, kPlanThreads, 0, s>>>(a);
+      prefill_plan_kernel<false><<<1, kPlanThreads, 0, s>>>(a, few);
     local_status_t st = local_check_launch("paged_attn_prefill (plan)");
     if (st != LOCAL_OK) return st;
   }
@@ -1060,7 +1060,6 @@ extern "C" local_status_t local_paged_attn_prefill(
   a.Hkv = Hkv;
   a.group = Hq / Hkv;
   a.max_blocks = max_blocks;
-  a.few = few_ranges(T, B, Hq, D);
   a.part = static_cast<float*>(ws);
   {
     const size_t pb = D == 64 ? prefill_part_bytes<64>(T, B, Hq) : prefill_part_bytes<128>(T, B, Hq);
