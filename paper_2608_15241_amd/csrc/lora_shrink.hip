@@ -16,8 +16,8 @@
 // four launches of a K-sliced shrink whose slices the reader summed.
 //
 // The tiles are gathered from groups of 64 tokens, adapter by adapter in the
-// order of their first tokens, four workgroups a group (tile i to workgroup
-// i % 4). Requests' chunks (runs of one adapter) make four full tiles, as 16
+// order of their first tokens, four or eight workgroups a group (tile i to
+// workgroup i % 4 or i % 8). Requests' chunks (runs of one adapter) make four full tiles, as 16
 // tokens in order would; with an adapter per token, 16 tokens in order hold up
 // to 16 adapters and stream x and A again for each: q, k and v of 2048 tokens at
 // 4096 x 4096 / 1024 / 1024 over 8 adapters at random 156 -> 122 us a call. A sum
@@ -30,14 +30,14 @@ namespace {
 
 constexpr int kSkTokens = 16;  // tokens of a tile
 constexpr int kSkGroup = kWave;  // tokens that tiles are gathered from
-constexpr int kSkSplit = kSkGroup / kSkTokens;  // workgroups of a group
 
 struct SkArgs {
   ShrinkJob job[kShrinkJobs];
   int64_t T;
   int n_ad, r_max;
   const int32_t* idx;
-  int ks;  // K slices (each its own workgroups and output)
+  int ks;     // K slices (each its own workgroups and output)
+  int split;  // workgroups of a group, a power of two
   const float* scale;  // for bf16 outputs
   uint16_t* zero16;    // 16 bytes or null
 };
@@ -72,8 +72,8 @@ __global__ __launch_bounds__(SK::W * kWave) void token_shrink_kernel(SkArgs a) {
     return reinterpret_cast<f32x4*>(sk_lds + w * S * SK::STAGE) + rt * kWave + lane;
   };
   const int z = static_cast<int>(blockIdx.x) % a.ks;
-  const int wg = static_cast<int>(blockIdx.x) / a.ks, sub = wg % kSkSplit;
-  const int64_t t0 = static_cast<int64_t>(wg / kSkSplit) * kSkGroup;
+  const int wg = static_cast<int>(blockIdx.x) / a.ks, sub = wg & (a.split - 1);
+  const int64_t t0 = static_cast<int64_t>(wg / a.split) * kSkGroup;
   const ShrinkJob& jb = a.job[blockIdx.y];
 
   int my = t0 + lane < a.T ? a.idx[t0 + lane] : -1;  // the adapter of the group's token `lane`
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(SK::W * kWave) void token_shrink_kernel(SkArgs a) {
         __builtin_amdgcn_ds_permute(4 * (my == ad ? below : cnt + lane - below), lane);
     const int tile0 = first;
     first += (cnt + kSkTokens - 1) / kSkTokens;
-    for (int i = (sub - tile0) & (kSkSplit - 1); kSkTokens * i < cnt; i += kSkSplit) {
+    for (int i = (sub - tile0) & (a.split - 1); kSkTokens * i < cnt; i += a.split) {
       if (again) __syncthreads();  // the previous tile's sums have been read
       again = true;
       // token c of the tile (past the last one: that again, never stored)
@@ -194,7 +194,7 @@ local_status_t launch_sk(const SkArgs& a, int n_jobs, hipStream_t s) {
                               hipFuncAttributeMaxDynamicSharedMemorySize, SK::LDS);
     done = true;
   }
-  const dim3 grid(static_cast<unsigned>((a.T + kSkGroup - 1) / kSkGroup * kSkSplit * a.ks),
+  const dim3 grid(static_cast<unsigned>((a.T + kSkGroup - 1) / kSkGroup * a.split * a.ks),
                   static_cast<unsigned>(n_jobs),
                   static_cast<unsigned>((a.r_max + 16 * SK::RT - 1) / (16 * SK::RT)));
   token_shrink_kernel<SK><<<grid, SK::W * kWave, SK::LDS, s>>>(a);
@@ -221,6 +221,9 @@ local_status_t token_shrink(const ShrinkJob* jobs, int n_jobs, int64_t T, int n_
   // 18.5, 15.4 and 17.4 with 16, 32 and 64; rank 64, 768 tiles: 72.9, 60.1
   // and 55.7.
   const bool full = (T + kSkTokens - 1) / kSkTokens * n_jobs * ks >= 256;
+  // A group holds four tiles, and more where its tokens have several adapters:
+  // room for eight at once where compute units are idle.
+  a.split = full ? 4 : 8;
   if (r_max <= 16 || (r_max <= 32 && !full)) return launch_sk<SkShape<1, 8, 2>>(a, n_jobs, s);
   if (r_max <= 32 || !full) return launch_sk<SkShape<2, 8, 3>>(a, n_jobs, s);
   return launch_sk<SkShape<4, 8, 2>>(a, n_jobs, s);
