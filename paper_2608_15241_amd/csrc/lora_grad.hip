@@ -66,11 +66,13 @@ constexpr int kPrepWaves = kPrepThreads / kWave;
 constexpr int kGrSpan = 2048;
 
 // Tokens up to which an adapter is not listed in spans (it does not change the
-// result): one unit, or two where adapters have fewer than two on average and the
-// grid, which has room for every adapter that could be listed, matters more
-// (with one unit / two: 512 tokens of 4 adapters at 1024 x 1024 18.0 / 21.7 us, 256 of
-// 4 at 4096 x 4096 34.9 / 32.7, 2048 of 64 97.5 / 95.2).
-int few_tokens(int64_t T, int n_ad) { return T < 2 * kGrUnit * n_ad ? 2 * kGrUnit : kGrUnit; }
+// result): one unit, or two in banks where adapters have fewer than two on average
+// and the grid, which has room for every adapter that could be listed, matters
+// more (with one unit / two: 512 tokens of 4 adapters at 1024 x 1024 18.0 / 21.7 us,
+// 2048 of 64 at 4096 x 4096 97.5 / 95.2, 512 of 64 57.4 / 56.0).
+int few_tokens(int64_t T, int n_ad) {
+  return n_ad >= 16 && T < 2 * kGrUnit * n_ad ? 2 * kGrUnit : kGrUnit;
+}
 
 // The most entries of either list.
 int64_t max_spans(int64_t T, int n_ad) {
