@@ -26,7 +26,7 @@
 //  * Long prefill chunks (T > 256), two kernels:
 //    - shrink (lora_shrink.hip): U_s[t] = bf16(s_t x_t . A[a_t]) of every
 //      token with an adapter, for every projection of the call.
-//    - main product: 256 x 192 down to 64 x 64 tokens x features per
+//    - main product: 128 x 256 down to 64 x 64 tokens x features per
 //      workgroup by the size of the call, both operands brought to LDS by
 //      direct global-to-LDS loads; the delta U_s Btilde^T over stacked columns
 //      c = a*r_max + j (U_s zero unless a is t's adapter; Btilde[n, c] =
@@ -100,12 +100,6 @@ struct GemmArgs {
   const uint16_t* zero16;
 };
 
-// Rank of adapter ad, clamped to [0, r_max] so that no rank reads past the
-// adapter's own rows.
-__device__ __forceinline__ int rank_of(const GemmArgs& a, int ad) {
-  return a.ranks ? min(max(a.ranks[ad], 0), a.r_max) : a.r_max;
-}
-
 // Entry g of a per-projection argument array. Compare-and-select over the
 // array (instead of indexing it) keeps the by-value argument in registers.
 template <typename T>
@@ -132,7 +126,8 @@ __device__ __forceinline__ int64_t gstart_of(const GemmArgs& a, int g) {
   return r;
 }
 
-// Rank of adapter ad of projection g, clamped to [0, r_max].
+// Rank of adapter ad of projection g, clamped to [0, r_max] so that no rank reads
+// past the adapter's own rows.
 __device__ __forceinline__ int rank_g(const GemmArgs& a, int g, int ad) {
   const int32_t* r = pick(a.granks, g);
   return r ? min(max(r[ad], 0), a.r_max) : a.r_max;
@@ -1411,7 +1406,6 @@ struct DecodePlan {
   PartialShape shape;
   int xrows;      // stacked-A rows per workgroup (shrink fused), or 0
   int slices;     // SGMV shrink K slices (shrink not fused), or 0
-  bool split;     // a grouped call that runs its projections one by one
   size_t part_bytes, shrink_bytes;
 };
 
@@ -1433,13 +1427,7 @@ DecodePlan plan_decode(int64_t T, int64_t K, int G, const Proj* p, int n_ad, int
   // taking the shrink out of the base product saves 6.8 us of streaming
   // there, and its own SGMV launch costs 10.3 us; so the shrink rides along
   // whenever it fits.)
-  if (n_ad > 0 && d.xrows == 0) {
-    if (T > kSgMaxTokens) {
-      d.split = true;
-      return d;
-    }
-    d.slices = sgmv_slices(K, r_max);
-  }
+  if (n_ad > 0 && d.xrows == 0) d.slices = sgmv_slices(K, r_max);
   d.part_bytes = align256(static_cast<size_t>(d.shape.ksb) * T * n_total * sizeof(float));
   d.shrink_bytes =
       d.xrows > 0 ? align256(static_cast<size_t>(d.shape.ksb) * T * G * R * sizeof(float))
@@ -1449,44 +1437,11 @@ DecodePlan plan_decode(int64_t T, int64_t K, int G, const Proj* p, int n_ad, int
 
 local_status_t lora_impl(const uint16_t* x, int64_t T, int64_t K, int G, const Proj* p,
                          int32_t n_adapters, int32_t r_max, const int32_t* adapter_idx,
-                         const float* scale, void* ws, size_t* ws_bytes, hipStream_t s);
-
-// Workspace need of a call that runs projections p[0..G) one after another.
-local_status_t one_by_one(const uint16_t* x, int64_t T, int64_t K, int G, const Proj* p,
-                          int32_t n_adapters, int32_t r_max, const int32_t* adapter_idx,
-                          const float* scale, void* ws, size_t* ws_bytes, hipStream_t s) {
-  if (!ws) {
-    size_t need = 0;
-    for (int g = 0; g < G; ++g) {
-      size_t n = 0;
-      const local_status_t st = lora_impl(x, T, K, 1, p + g, n_adapters, r_max, adapter_idx,
-                                          scale, nullptr, &n, s);
-      if (st != LOCAL_OK) return st;
-      need = need > n ? need : n;
-    }
-    *ws_bytes = need;
-    return LOCAL_OK;
-  }
-  for (int g = 0; g < G; ++g) {
-    size_t n = *ws_bytes;
-    const local_status_t st =
-        lora_impl(x, T, K, 1, p + g, n_adapters, r_max, adapter_idx, scale, ws, &n, s);
-    if (st != LOCAL_OK) return st;
-  }
-  return LOCAL_OK;
-}
-
-local_status_t lora_impl(const uint16_t* x, int64_t T, int64_t K, int G, const Proj* p,
-                         int32_t n_adapters, int32_t r_max, const int32_t* adapter_idx,
                          const float* scale, void* ws, size_t* ws_bytes, hipStream_t s) {
   const int R = n_adapters > 0 ? n_adapters * r_max : 0;
   const bool decode = T <= kSgMaxTokens;
   DecodePlan d{};
-  if (decode) {
-    d = plan_decode(T, K, G, p, n_adapters, r_max);
-    if (d.split)
-      return one_by_one(x, T, K, G, p, n_adapters, r_max, adapter_idx, scale, ws, ws_bytes, s);
-  }
+  if (decode) d = plan_decode(T, K, G, p, n_adapters, r_max);
   // Workspace. Decode sizes (T <= kSgMaxTokens): the base partial sums
   // [ksb][T][N] fp32 (N over all projections), then the shrink's partial
   // sums: [ksb][T][G*R] fp32 when the shrink runs inside the base product,

@@ -200,7 +200,7 @@ GROUPED = [
     (4, 256, (256, 256), 3, 8, None),
     (300, 512, (512, 256), 4, 16, None),       # long chunk: one launch over both
     (520, 512, (256, 768, 512), 5, 16, [16, 3, 9, 16, 0]),  # long chunk, three projections
-    (300, 256, (320, 256), 3, 8, None),        # long chunk, N % 256 != 0: one at a time
+    (300, 256, (320, 256), 3, 8, None),        # long chunk, N % 256 != 0: 64-feature tiles
     (16, 512, (64, 64), 16, 16, None),          # shrink too wide to fuse: grouped SGMV
     (64, 1024, (512, 128, 128), 16, 64, [8, 16, 32, 64] * 4),  # padded ranks: grouped SGMV
     (32, 512, (512, 512, 512), 0, 0, None),

@@ -59,12 +59,12 @@ def test_lora_linear_workspace_and_errors(lib):
     # stacked rows, 8 base K slices) runs on its own: 8 K slices x T x r_max
     st, n2 = _size(f, FAKE, 32, 4096, FAKE, 64, FAKE, FAKE, 16, 16, None, FAKE, FAKE, None, FAKE)
     assert st == OK and n2 == 8 * 32 * 64 * 4 + 8 * 32 * 16 * 4
-    # above 256 tokens: the shrink's fp32 partial sums for each token's own
-    # adapter, 8 K slices (the most; 5 tiles of 64 tokens) x T x r_max, then
-    # a 32-byte adapter bitmap per 64-token tile, each part 256-byte aligned
+    # above 256 tokens: room for the shrink's fp32 sums for each token's own
+    # adapter over 8 K slices x T x r_max (at most 4 are taken), and 32 bytes for
+    # each 64 tokens, each part 256-byte aligned
     st, n1 = _size(f, FAKE, 300, 4096, FAKE, 4096, FAKE, FAKE, 8, 16, None, FAKE, FAKE, None, FAKE)
     assert st == OK and n1 == 8 * 300 * 16 * 4 + 256
-    # 2048 tokens (32 tiles of 64): 8 slices fill the chip (fewer do not fit LDS)
+    # 2048 tokens: 8 slices
     st, n2k = _size(f, FAKE, 2048, 4096, FAKE, 4096, FAKE, FAKE, 4, 16, None, FAKE, FAKE, None, FAKE)
     assert st == OK and n2k == 8 * 2048 * 16 * 4 + 32 * 32
     st, n0 = _size(f, FAKE, 32, 4096, FAKE, 4096, None, None, 0, 0, None, None, None, None, FAKE)
@@ -155,9 +155,9 @@ def test_lora_linear_grouped_workspace_and_errors(lib):
     st, n = _size(f, FAKE, 32, 4096, 3, ptrs(3), Ns, ptrs(3), ptrs(3), 8, 16, None, FAKE,
                   FAKE, ptrs(3))
     assert st == OK and n == 2 * 32 * 12288 * 4 + 2 * 32 * 384 * 4
-    # a 2048-token chunk: one launch over the three projections, the shrink's
-    # partial sums per projection (8 K slices x T x r_max fp32 each), then the
-    # adapter bitmaps (32 bytes per 64-token tile)
+    # a 2048-token chunk: one launch over the three projections, room for the
+    # shrink's sums per projection (8 K slices x T x r_max fp32 each) and 32 bytes
+    # for each 64 tokens
     st, n = _size(f, FAKE, 2048, 4096, 3, ptrs(3), Ns, ptrs(3), ptrs(3), 4, 16, None, FAKE,
                   FAKE, ptrs(3))
     assert st == OK and n == 3 * 8 * 2048 * 16 * 4 + 32 * 32
@@ -175,14 +175,14 @@ def test_lora_linear_grouped_workspace_and_errors(lib):
 
 def test_lora_grad_workspace_and_errors(lib):
     f = lib.local_lora_grad
-    # T=300, K=512, N=640, 4 adapters of rank 16. Parts, each 256-byte aligned:
-    # the bucketed token order (T int32), the adapter offsets and the unit
-    # offsets (n+1 int32 each), the unit table (16 bytes for each of at most
-    # T/64 + n 64-token units), B transposed (n x r_max x N bf16), the
-    # shrinks' partial sums of x against A (8 K slices x T x r_max fp32) and of
-    # dy against B^T (10 slices), each followed by 32 bytes of adapter bitmap
-    # per 64-token tile, then the units' partial products (units x N x r_max
-    # and units x K x r_max fp32).
+    # T=300, K=512, N=640, 4 adapters of rank 16. The size that callers have always
+    # been told, which the present parts fit (token order, adapter offsets, spans,
+    # B transposed, the low-rank products, the sums of spans). It was, each part
+    # 256-byte aligned: the token order (T int32), two lists of n+1 int32, 16 bytes
+    # for each of at most T/64 + n 64-token units, B transposed (n x r_max x N
+    # bf16), sums of x against A over 8 K slices x T x r_max fp32 and of dy against
+    # B^T over 10, each with 32 bytes for each 64 tokens, and a partial product of
+    # every unit (units x N x r_max and units x K x r_max fp32).
     a = lambda v: (v + 255) // 256 * 256
     st, n = _size(f, FAKE, 300, 512, FAKE, 640, FAKE, FAKE, 4, 16, None, FAKE, FAKE, FAKE, FAKE)
     assert st == OK
@@ -191,7 +191,7 @@ def test_lora_grad_workspace_and_errors(lib):
                  + a(8 * 300 * 16 * 4) + a(5 * 32) + a(10 * 300 * 16 * 4) + a(5 * 32)
                  + a(units * 640 * 16 * 4) + a(units * 512 * 16 * 4))
     st, n0 = _size(f, FAKE, 0, 512, FAKE, 640, FAKE, FAKE, 4, 16, None, FAKE, FAKE, FAKE, FAKE)
-    assert st == OK and n0 > 0                     # T = 0 still runs the bucket and reduce passes
+    assert st == OK and n0 > 0                     # T = 0 still writes zero gradients
     assert _size(f, FAKE, 300, 512, FAKE, 640, FAKE, FAKE, 4, 12, None, FAKE, FAKE, FAKE,
                  FAKE)[0] == ERR_UNSUPPORTED
     assert _size(f, FAKE, 300, 100, FAKE, 640, FAKE, FAKE, 4, 16, None, FAKE, FAKE, FAKE,
@@ -227,7 +227,7 @@ def test_lora_grad_grouped_workspace_and_errors(lib):
     st, n = _size(f, FAKE, 2048, 4096, 3, ptrs(3), Ns, ptrs(3), ptrs(3), 4, 16, None, FAKE,
                   FAKE, ptrs(3), ptrs(3))
     assert st == OK
-    # at least the three projections' partial products (units x (N_g + K) x r_max fp32)
+    # at least a partial product of every unit (units x (N_g + K) x r_max fp32)
     units = 2048 // 64 + 4
     assert n > units * (4096 + 1024 + 1024 + 3 * 4096) * 16 * 4
     assert _size(f, FAKE, 2048, 4096, 5, ptrs(5), Ns, ptrs(5), ptrs(5), 4, 16, None, FAKE,
