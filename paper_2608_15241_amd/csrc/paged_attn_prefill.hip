@@ -29,6 +29,7 @@
 #include <utility>
 
 #include <climits>
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -207,20 +208,20 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 constexpr int kPlanThreads = 256;  // threads of the workgroup that plans the units
-template <bool FEW>
-__device__ void plan_units(const PrefillArgs& a, const KeyRanges& few);
+template <class... Few>
+__device__ void plan_units(const PrefillArgs& a, const Few&... few);
 
 // Append. Workgroup = (one block that request b's chunk writes, KV head g),
 // mapped from a 1D grid (heads fastest); the block's slots [lo, hi) are new
 // (positions P_b .. L_b - 1). Thread t handles slot t / (D/8), dims
 // 8 (t % (D/8)) .. +8.
-template <int D, bool FEW>
-__global__ __launch_bounds__(256) void prefill_append_kernel(PrefillArgs a, KeyRanges few) {
+template <int D, class... Few>
+__global__ __launch_bounds__(256) void prefill_append_kernel(PrefillArgs a, Few... few) {
   constexpr int C8 = D / 8;
   __shared__ uint16_t vt[D][kBlockSize + 2];  // V of the block, dim-major (+2: banks)
   // workgroup 0 (dispatched first) plans the attention grid's units
   if (blockIdx.x == 0) {
-    plan_units<FEW>(a, few);
+    plan_units(a, few...);
     return;
   }
   const unsigned bid = blockIdx.x - 1;
@@ -294,6 +295,29 @@ __device__ __forceinline__ int tile_blocks(int P, int n_b, int t, int max_blocks
   return lim < 0 ? 0 : min(lim / kBlockSize + 1, max_blocks);
 }
 
+// The key ranges of a call of few tiles. It leaves compute units idle and its
+// longest unit sets the end, so shorter ranges pay where they save more than the
+// partial results add: those grow with the (tile, head) pairs and D, and ranges
+// past two workgroups per compute unit wait for a second round. The pairs are
+// those that the workspace is sized for, since the host knows no lengths; the
+// planner compares the longest tile (with tiles just below the limit left whole,
+// splitting the others gains nothing). From 129 pairs on, calls that the common
+// rule splits too keep to it: more ranges there gained 10% or lost 5%. Measured,
+// whole calls in us by the common rule / these ranges: 32 pairs, 16 rows on 300 /
+// 1000 tokens 18.8 / 16.4 and 36.2 / 20.5; 64 pairs, 200 rows on 450 / 1000 tokens
+// 29.4 / 28.5 and 41.9 / 31.0; 128 pairs, 4 x 16 rows on 1000 / 2000 tokens 36.1 /
+// 27.6 and 41.5 / 38.8; 192 pairs, 3 x 128 rows on 300 / 1000 tokens 25.4 (in 2
+// ranges 27.2) and 41.6 / 33.6; 256 pairs, 4 x 250 rows on 2000 tokens 68, in 4
+// ranges 77; 384 pairs, 12 x 128 rows on 224 tokens 34, in 2 ranges 49.
+KeyRanges few_ranges(int64_t T, int B, int Hq, int D) {
+  const int64_t pairs = (T / kPaRows + B) * Hq;
+  if (pairs * D <= 32 * 128) return {19, INT_MAX, 16, 32, 48};
+  if (pairs <= 64) return {40, INT_MAX, 32, 64, 64};
+  if (pairs <= 128) return {56, INT_MAX, 40, 80, 80};
+  if (pairs <= 192) return {64, 96, 48, INT_MAX, INT_MAX};
+  return {INT_MAX, 0, 0, 0, 0};
+}
+
 // Key ranges a tile of nbl blocks is split into (no division: one thread counts
 // many tiles).
 __device__ __forceinline__ int tile_splits(int nbl, const KeyRanges& r) {
@@ -326,11 +350,13 @@ __device__ __forceinline__ int tile_class(int nbl, int ns) {
 // from the last request backwards, a request's tiles from its last one, a
 // tile's key ranges ascending. So the longest units start first, whatever
 // request they belong to, and the grid ends on the short ones; an attention
-// workgroup reads its unit with one load instead of deriving it. FEW: the call
-// may take the key ranges of few tiles (code of its own, since one workgroup runs
-// the planner from cold instruction caches).
-template <bool FEW>
-__device__ void plan_units(const PrefillArgs& a, const KeyRanges& few) {
+// workgroup reads its unit with one load instead of deriving it. A call that may
+// take the key ranges of few tiles gives them; others run code without, and with
+// no such argument (one workgroup runs the planner from cold instruction caches,
+// and the argument alone cost the append 0.7 us of 17).
+template <class... Few>
+__device__ void plan_units(const PrefillArgs& a, const Few&... maybe) {
+  constexpr bool FEW = sizeof...(Few) > 0;
   __shared__ int scan[kPaClasses][kPlanThreads];
   __shared__ int totals[kPaClasses];
   __shared__ int n_split_tiles, longest;
@@ -356,7 +382,8 @@ __device__ void plan_units(const PrefillArgs& a, const KeyRanges& few) {
     *P = my_P;
     return mine;
   };
-  KeyRanges kr = {0, INT_MAX, kPaSplitBlocks, 2 * kPaSplitBlocks, 3 * kPaSplitBlocks};
+  std::conditional_t<FEW, KeyRanges, const KeyRanges> kr = {
+      0, INT_MAX, kPaSplitBlocks, 2 * kPaSplitBlocks, 3 * kPaSplitBlocks};
   auto count = [&](int P, int n, int (&cnt)[kPaClasses]) {
     for (int t = 0; t * kPaRows < n; ++t) {
       const int nbl = tile_blocks(P, n, t, a.max_blocks), ns = tile_splits(nbl, kr);
@@ -371,8 +398,7 @@ __device__ void plan_units(const PrefillArgs& a, const KeyRanges& few) {
     if (FEW) longest = 0;
   }
   __syncthreads();
-  // counted again where the longest tile asks for the key ranges of few tiles
-  for (bool again = false;; again = true) {
+  auto count_all = [&]() {
     for (int i = tid; i < a.B; i += kPlanThreads) {
       int r0, n, P, cnt[kPaClasses];
 #pragma unroll
@@ -385,10 +411,18 @@ __device__ void plan_units(const PrefillArgs& a, const KeyRanges& few) {
       if (FEW) atomicMax(&longest, tile_blocks(P, n, (n - 1) / kPaRows, a.max_blocks));
     }
     __syncthreads();
-    if (!FEW || again || longest <= few.from || longest > few.upto) break;
-    kr = few;
-    if (tid < kPaClasses) totals[tid] = 0;
-    __syncthreads();
+  };
+  if constexpr (FEW) {  // counted again where the longest tile asks for shorter ranges
+    const KeyRanges few = (maybe, ...);
+    for (bool again = false;; again = true) {
+      count_all();
+      if (again || longest <= few.from || longest > few.upto) break;
+      kr = few;
+      if (tid < kPaClasses) totals[tid] = 0;
+      __syncthreads();
+    }
+  } else {
+    count_all();
   }
   int first[kPaClasses];  // next entry of each class
   {
@@ -451,9 +485,9 @@ __device__ void plan_units(const PrefillArgs& a, const KeyRanges& few) {
 }
 
 // The planner alone, for calls without an append.
-template <bool FEW>
-__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PrefillArgs a, KeyRanges few) {
-  plan_units<FEW>(a, few);
+template <class... Few>
+__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PrefillArgs a, Few... few) {
+  plan_units(a, few...);
 }
 
 template <int D>
@@ -934,29 +968,6 @@ size_t prefill_ws_bytes(int64_t T, int B, int Hq) {
          static_cast<size_t>(tiles) * (2 * kPaMaxSplit + 1) * sizeof(int4);
 }
 
-// The key ranges of a call of few tiles. It leaves compute units idle and its
-// longest unit sets the end, so shorter ranges pay where they save more than the
-// partial results add: those grow with the (tile, head) pairs and D, and ranges
-// past two workgroups per compute unit wait for a second round. The pairs are
-// those that the workspace is sized for, since the host knows no lengths; the
-// planner compares the longest tile (with tiles just below the limit left whole,
-// splitting the others gains nothing). From 129 pairs on, calls that the common
-// rule splits too keep to it: more ranges there gained 10% or lost 5%. Measured,
-// whole calls in us by the common rule / these ranges: 32 pairs, 16 rows on 300 /
-// 1000 tokens 18.8 / 16.4 and 36.2 / 20.5; 64 pairs, 200 rows on 450 / 1000 tokens
-// 29.4 / 28.5 and 41.9 / 31.0; 128 pairs, 4 x 16 rows on 1000 / 2000 tokens 36.1 /
-// 27.6 and 41.5 / 38.8; 192 pairs, 3 x 128 rows on 300 / 1000 tokens 25.4 (in 2
-// ranges 27.2) and 41.6 / 33.6; 256 pairs, 4 x 250 rows on 2000 tokens 68, in 4
-// ranges 77; 384 pairs, 12 x 128 rows on 224 tokens 34, in 2 ranges 49.
-KeyRanges few_ranges(int64_t T, int B, int Hq, int D) {
-  const int64_t pairs = (T / kPaRows + B) * Hq;
-  if (pairs * D <= 32 * 128) return {19, INT_MAX, 16, 32, 48};
-  if (pairs <= 64) return {40, INT_MAX, 32, 64, 64};
-  if (pairs <= 128) return {56, INT_MAX, 40, 80, 80};
-  if (pairs <= 192) return {64, 96, 48, INT_MAX, INT_MAX};
-  return {INT_MAX, 0, 0, 0, 0};
-}
-
 template <int D>
 local_status_t launch_prefill(const PrefillArgs& a, hipStream_t s) {
   const KeyRanges few = few_ranges(a.T, a.B, a.Hq, D);
@@ -968,16 +979,16 @@ local_status_t launch_prefill(const PrefillArgs& a, hipStream_t s) {
     const int64_t units = a.T / kBlockSize + 2LL * a.B;
     const unsigned grid = static_cast<unsigned>(units * a.Hkv + 1);
     if (maybe_few)
-      prefill_append_kernel<D, true><<<grid, 256, 0, s>>>(a, few);
+      prefill_append_kernel<D, KeyRanges><<<grid, 256, 0, s>>>(a, few);
     else
-      prefill_append_kernel<D, false><<<grid, 256, 0, s>>>(a, few);
+      prefill_append_kernel<D><<<grid, 256, 0, s>>>(a);
     local_status_t st = local_check_launch("paged_attn_prefill (append)");
     if (st != LOCAL_OK) return st;
   } else {
     if (maybe_few)
-      prefill_plan_kernel<true><<<1, kPlanThreads, 0, s>>>(a, few);
+      prefill_plan_kernel<KeyRanges><<<1, kPlanThreads, 0, s>>>(a, few);
     else
-      prefill_plan_kernel<false><<<1, kPlanThreads, 0, s>>>(a, few);
+      prefill_plan_kernel<><<<1, kPlanThreads, 0, s>>>(a);
     local_status_t st = local_check_launch("paged_attn_prefill (plan)");
     if (st != LOCAL_OK) return st;
   }
