@@ -301,19 +301,22 @@ __device__ __forceinline__ int tile_blocks(int P, int n_b, int t, int max_blocks
 // past two workgroups per compute unit wait for a second round. The pairs are
 // those that the workspace is sized for, since the host knows no lengths; the
 // planner compares the longest tile (with tiles just below the limit left whole,
-// splitting the others gains nothing). From 129 pairs on, calls that the common
-// rule splits too keep to it: more ranges there gained 10% or lost 5%. Measured,
-// whole calls in us by the common rule / these ranges: 32 pairs, 16 rows on 300 /
-// 1000 tokens 18.8 / 16.4 and 36.2 / 20.5; 64 pairs, 200 rows on 450 / 1000 tokens
-// 29.4 / 28.5 and 41.9 / 31.0; 128 pairs, 4 x 16 rows on 1000 / 2000 tokens 36.1 /
-// 27.6 and 41.5 / 38.8; 192 pairs, 3 x 128 rows on 300 / 1000 tokens 25.4 (in 2
-// ranges 27.2) and 41.6 / 33.6; 256 pairs, 4 x 250 rows on 2000 tokens 68, in 4
-// ranges 77; 384 pairs, 12 x 128 rows on 224 tokens 34, in 2 ranges 49.
+// splitting the others gains nothing). Above 160 pairs, calls that the common rule
+// splits too keep to it: more ranges there gained 10% or lost 5%. Measured, whole
+// calls in us by the common rule / these ranges: 32 pairs, 16 rows on 300 / 1000
+// tokens 18.9 / 16.4 and 36.1 / 20.5; 64 pairs, 200 rows on 350 tokens 26.8 (by 16
+// blocks 28.2), on 450 / 1000 29.4 / 28.7 and 41.9 / 30.6; 128 pairs, 3 chunks of up to
+// 72 rows on up to 1135 tokens 36.6 / 24.2, 4 x 16 rows on 1000 36.0 / 30.3, 400 rows on
+// 250 31.0 (by 16 blocks 34.1); 160 pairs, 512 rows on 1000 tokens 52.2 / 40.7; 192
+// pairs, 3 x 128 rows on 300 / 1000 tokens 25.4 (in 2 ranges 27.2) and 41.4 / 33.7; 256
+// pairs, 4 x 250 rows on 2000 tokens 68, in 4 ranges 77; 384 pairs, 12 x 128 rows on
+// 224 tokens 34, in 2 ranges 49.
 KeyRanges few_ranges(int64_t T, int B, int Hq, int D) {
   const int64_t pairs = (T / kPaRows + B) * Hq;
   if (pairs * D <= 32 * 128) return {19, INT_MAX, 16, 32, 48};
-  if (pairs <= 64) return {40, INT_MAX, 32, 64, 64};
-  if (pairs <= 128) return {56, INT_MAX, 40, 80, 80};
+  if (pairs <= 64) return {38, INT_MAX, 16, 32, 48};
+  if (pairs <= 128) return {50, INT_MAX, 16, 32, 48};
+  if (pairs <= 160) return {48, 288, 32, 64, INT_MAX};
   if (pairs <= 192) return {64, 96, 48, INT_MAX, INT_MAX};
   return {INT_MAX, 0, 0, 0, 0};
 }

@@ -22,13 +22,17 @@ CASES = [
     (4, 1, 64, [239, 241, 289], [16, 16, 16], 5, 2),            # 16, 17, 20
     (4, 4, 128, [496, 497, 752, 1000], [16, 16, 16, 40], 12, 4),  # 32, 33, 48, 65
     (2, 2, 64, [4000], [1], 4, 1),                              # one row, four ranges
-    # up to 64, the longest above 40: 2 and 4 above 32 and 64
-    (8, 2, 128, [0, 3], [700, 129], 10, 2),                     # 8, 16 .. 40, 44 | 9, 9
-    (32, 8, 128, [624, 500], [16, 16], 2, 0),                   # 40, 33
-    (32, 8, 128, [641, 1040], [16, 16], 6, 2),                  # 42, 66
-    # up to 128, the longest above 56: 2 and 4 above 40 and 80
-    (32, 8, 128, [880, 650, 10, 10], [16] * 4, 4, 0),           # 56, 42
-    (32, 8, 128, [700, 624, 480, 1300], [28, 16, 22, 12], 8, 2),  # 46, 40, 32, 82
+    # up to 64, the longest above 38
+    (8, 2, 128, [0, 3], [700, 129], 14, 4),                     # 8, 16 .. 40, 44 | 9, 9
+    (32, 8, 128, [592, 256], [16, 16], 2, 0),                   # 38, 17
+    (32, 8, 128, [593, 752], [16, 16], 6, 2),                   # 39, 48
+    # up to 128, the longest above 50
+    (32, 8, 128, [784, 250, 10, 10], [16] * 4, 4, 0),           # 50, 17
+    (32, 8, 128, [785, 250, 768, 10], [28, 6, 22, 12], 10, 2),  # 51, 16, 50
+    # up to 160, the longest above 48 and not above 288: 2 and 3 above 32 and 64
+    (32, 8, 128, [752, 600, 10, 10, 10], [16] * 5, 5, 0),       # 48, 39
+    (32, 8, 128, [753, 496, 1009, 10, 10], [16] * 5, 8, 2),     # 49, 32, 65
+    (32, 8, 128, [4593, 496, 1009, 10, 10], [16] * 5, 8, 1),    # 289, 32, 65
     # up to 192, the longest above 64 and not above 96: 2 above 48
     (32, 8, 128, [1008, 760, 753, 5, 10, 30], [16] * 6, 6, 0),  # 64, 49, 49
     (32, 8, 128, [1024, 752, 753, 1520, 10, 30], [16] * 6, 9, 3),  # 65, 48, 49, 96
